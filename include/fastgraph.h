@@ -106,12 +106,15 @@ typedef struct {
 /* Options of the query stage; none changes the result.  A NULL pointer means all defaults. */
 typedef struct {
     const int32_t* dir;        /* [n] direction flags in ORIGINAL row order (see fg_binned_select_knn_dir), or NULL */
-    int32_t algo;              /* 0: tile kernel + list kernel (default); 1: the one-lane-per-query shell walk for
-                                  every query (slower; kept for cross-checking); 2: as 0, with the tile kernel's
-                                  flattened scan on every tile instead of the uneven ones only (for tests) */
+    int32_t algo;              /* 0: the default: tile kernel + list kernel, from six dimensions on the leaf kernel;
+                                  1: the one-lane-per-query shell walk for every query (slower; kept for
+                                  cross-checking); 2: tile kernel + list kernel with the tile kernel's flattened scan on
+                                  every tile instead of the uneven ones only (for tests); 3: leaf kernel; 4: tile
+                                  kernel + list kernel.  Calls that count candidates take 3 as 4 */
     int32_t defer_lanes;       /* after shell 1 a wavefront of the tile kernel goes on to the next shell only while
                                   more than this many of its 64 queries are unfinished, the rest go to the list
-                                  kernel; 0..64, negative: the default (64 for d <= 5, 6 beyond) */
+                                  kernel; 0..64, negative: the default (64 for d <= 5, 6 beyond).  With algo 0 a value
+                                  that is not negative asks for the tile kernel */
 } fg_query_options;
 
 /* Spatial partition + counting sort (Section 3, second paragraph: bins per row split, points ordered by bin,

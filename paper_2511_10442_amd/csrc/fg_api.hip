@@ -323,8 +323,9 @@ fg_status fg_query_binned(const fg_binning* view, const int32_t* row_splits, int
     a.work_list = (int32_t*)(sc + S.work_list); a.work_count = (int32_t*)(sc + S.work_count);
     a.handed = (uint64_t*)(sc + S.rank);       // the counting sort is done with its ranks
     a.bin_idx = view->bin_idx; a.tile_order = (int32_t*)(sc + S.tile_order);
-    a.algo = (options && (options->algo == 1 || options->algo == 2)) ? options->algo : 0;
+    a.algo = (options && (options->algo >= 1 && options->algo <= 4)) ? options->algo : 0;
     a.defer_lanes = defer > 64 ? 64 : defer;
+    if (a.algo == 0 && options && options->defer_lanes >= 0) a.algo = 4;      // a hand-over rule is one of the tile kernel
     hipError_t e = launch_query(a, d, view->d_bin, (hipStream_t)stream);
     return e == hipSuccess ? FG_OK : FG_ERR_LAUNCH;
 }

@@ -3,6 +3,7 @@
 #include "fg_query.hpp"
 #include "fg_query_tile.hpp"
 #include "fg_query_list.hpp"
+#include "fg_query_leaf.hpp"
 
 namespace fg {
 
@@ -258,6 +259,17 @@ static void launch_query_pass(const QueryArgs& a_in, hipStream_t stream)
     hipLaunchKernelGGL((k_query_list_wave<D, DB, COUNT>), dim3(list_grid), dim3(kQueryBlock), 0, stream, a);
 }
 
+// From this many dimensions on the leaf kernel is the default.  Query stage, tile + list kernel against leaf kernel:
+//   200k uniform points, d = 6, K = 40      3.69 against  2.32 ms     1M the same                     13.0 against 11.5 ms
+//   400k, d = 6, K = 10                     3.68 against  2.92 ms     400k, d = 7, K = 16              6.2 against  6.1 ms
+//   500k, d = 8, K = 64                    21.6  against 15.8 ms      60k, d = 10, K = 40              7.4 against  1.25 ms
+//   2k, d = 6, K = 10                       0.28 against  0.09 ms     2k, d = 10, K = 40               1.31 against 0.19 ms
+//   100k Gaussian mixture, d = 6, K = 60    5.3  against  2.9 ms
+//   below: 1M uniform points, d = 5, K = 40 3.2  against  9.0 ms      100k mixture, d = 4, K = 40      0.65 against 1.27 ms
+// Below, bins of one shell leave a query few hundred candidates and the tile kernel's scan is cheap next to the leaf
+// kernel's fixed cost per tile.
+constexpr int kLeafMinD = 6;
+
 // Lists of more than 64 neighbours (K - 1 up to 127) take two passes: the first finds the 64 nearest, the second
 // the rest, counting only keys above the 64th (keys are unique, so the split is exact).  A sorted list of more
 // than 64 keys does not fit the 256 architectural registers of a wavefront next to everything else: held partly
@@ -277,6 +289,17 @@ static hipError_t launch_query_impl(const QueryArgs& a_in, hipStream_t stream)
     const int32_t cap = a.k - 1;
     a.slot0 = 0;
     a.k_list = cap < 64 ? cap : 64;
+    if constexpr (!COUNT) {
+        if (a.algo == 3 || (a.algo == 0 && D >= kLeafMinD)) {
+            launch_leaf_pass<D, false>(a, stream);
+            if (cap > 64) {
+                a.slot0 = 64;
+                a.k_list = cap - 64;
+                launch_leaf_pass<D, true>(a, stream);
+            }
+            return hipGetLastError();
+        }
+    }
     launch_query_pass<D, DB, COUNT, false>(a, stream);
     if (cap > 64) {
         a.slot0 = 64;

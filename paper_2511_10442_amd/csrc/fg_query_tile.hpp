@@ -78,6 +78,70 @@ __device__ __forceinline__ void store_row_from_registers(const uint64_t (&best)[
     }
 }
 
+// The 64 finished rows of a tile, from the lists in the lanes' registers.  mask: lanes handed over to the list kernel,
+// whose slot 0 of the distance row carries resume_word.  lds64: (KC * kDumpStride + 64) words of scratch.
+template <int KC>
+__device__ __forceinline__ void write_tile_rows(const QueryArgs& a, const uint64_t (&best)[KC], uint64_t* lds64, int32_t my_row,
+                                                bool valid, bool asks, int32_t cap, uint64_t mask, uint32_t resume_word)
+{
+    const int lane = threadIdx.x;
+    // Rows of exactly KC words (K = 16, 32, 48, 64) leave straight from the registers: every lane writes its own
+    // row in 16-byte pieces (the pieces of a 128-byte line arrive within a few instructions of each other and are
+    // joined in the L2 cache).  A sixteenth of the instructions of the transposition below: query stage -8 % at
+    // K = 16, -4 % at K = 32, +-0 at K = 64.  Rows that do not start on a 64-byte boundary (K = 40: 160 bytes)
+    // were 3 % slower this way and keep the transposition.
+    const bool direct_rows = a.slot0 == 0 && a.k == KC && cap == KC - 1 &&
+                             (((uintptr_t)a.out_idx | (uintptr_t)a.out_d2) & 15) == 0;
+    if (direct_rows) {
+        if (valid) {
+            int32_t* oi = a.out_idx + (int64_t)my_row * a.k;
+            float* od = a.out_d2 + (int64_t)my_row * a.k;
+            const int32_t idx0 = asks ? my_row : -1;
+            const uint32_t d2_0 = ((mask >> lane) & 1) ? resume_word : 0u;     // handed over: where to resume
+            store_row_from_registers<KC, 1>(best, oi, od, idx0, d2_0);
+        }
+    } else {
+    // otherwise: registers -> LDS -> contiguous row writes
+    __syncthreads();
+    // two passes (indices, then distances) so the transposition needs KC x 64 words, not keys
+    int32_t* rows_lds = reinterpret_cast<int32_t*>(lds64);
+    uint32_t* dump = reinterpret_cast<uint32_t*>(lds64) + kQueryBlock;     // [KC][64] after the 64 row words
+    rows_lds[lane] = valid ? (asks ? my_row : -2 - my_row) : -1;   // -1: nothing to write; <= -2: all-padding row
+    const int32_t k = a.k;
+    const int32_t kk = cap + 1;                                         // words written per row: slot 0 and this pass's slots
+    const int32_t per_iter = kk >= kQueryBlock ? 1 : kQueryBlock / kk;  // rows written per pass
+    const int32_t sub = lane / kk;                                      // which of them this lane serves
+    const int32_t j0 = lane - sub * kk;                                 // word inside the row
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+        if (pass) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < KC; ++i) {
+            const bool real = best[i] < kEmptyKey;
+            const uint32_t word = pass == 0 ? (real ? (uint32_t)best[i] : 0xffffffffu)      // index or -1
+                                            : (real ? (uint32_t)(best[i] >> 32) : 0u);       // distance bits or 0.0f
+            dump[i * kDumpStride + lane] = word;
+        }
+        __syncthreads();
+        for (int32_t r0 = 0; r0 < kQueryBlock; r0 += per_iter) {
+            const int32_t ql = r0 + sub;
+            if (sub >= per_iter || ql >= kQueryBlock) continue;
+            const int32_t enc = rows_lds[ql];
+            if (enc == -1) continue;
+            const int32_t row = enc >= 0 ? enc : -2 - enc;
+            for (int32_t j = j0; j < kk; j += kQueryBlock) {
+                uint32_t word = pass == 0 ? (enc >= 0 ? (uint32_t)row : 0xffffffffu) : 0u;   // slot 0: the row itself at distance 0
+                if (pass == 1 && ((mask >> ql) & 1)) word = resume_word;                     // handed over: where to resume
+                if (j > 0) word = dump[(KC - cap + j - 1) * kDumpStride + ql];
+                const int32_t slot = j > 0 ? a.slot0 + j : 0;
+                if (pass == 0) a.out_idx[(int64_t)row * k + slot] = (int32_t)word;
+                else a.out_d2[(int64_t)row * k + slot] = __uint_as_float(word);
+            }
+        }
+    }
+    }
+}
+
 constexpr int kTileFlatBit = 6;   // in a tile's class word: the ordering kernels found the tile uneven
 constexpr int kOrderFlagBit = 30;  // the same flag in the tile's entry of the order (tiles number below 2^25)
 // LDS of a workgroup (one wavefront): the pending buffers (8 KB), the stage, and for the flattened scan its tables.
@@ -513,64 +577,8 @@ __device__ __forceinline__ void tile_body(const QueryArgs& a, const int32_t tile
     // to search travels in slot 0 of the distance row
     const uint64_t mask = __ballot(active);
     if (lane == 0) a.handed[tile] = mask;
-    const uint32_t resume_word = (uint32_t)(R + 1);
-    // Rows of exactly KC words (K = 16, 32, 48, 64) leave straight from the registers: every lane writes its own
-    // row in 16-byte pieces (the pieces of a 128-byte line arrive within a few instructions of each other and are
-    // joined in the L2 cache).  A sixteenth of the instructions of the transposition below: query stage -8 % at
-    // K = 16, -4 % at K = 32, +-0 at K = 64.  Rows that do not start on a 64-byte boundary (K = 40: 160 bytes)
-    // were 3 % slower this way and keep the transposition.
-    const bool direct_rows = a.slot0 == 0 && a.k == KC && cap == KC - 1 &&
-                             (((uintptr_t)a.out_idx | (uintptr_t)a.out_d2) & 15) == 0;
-    if (direct_rows) {
-        if (COUNT && valid) a.out_cand[my_row] = LOWER ? a.out_cand[my_row] + cand : cand;
-        if (valid) {
-            int32_t* oi = a.out_idx + (int64_t)my_row * a.k;
-            float* od = a.out_d2 + (int64_t)my_row * a.k;
-            const int32_t idx0 = asks ? my_row : -1;
-            const uint32_t d2_0 = ((mask >> lane) & 1) ? resume_word : 0u;     // handed over: where to resume
-            store_row_from_registers<KC, 1>(best, oi, od, idx0, d2_0);
-        }
-    } else {
-    // otherwise: registers -> LDS -> contiguous row writes
-    __syncthreads();
-    // two passes (indices, then distances) so the transposition needs KC x 64 words, not keys
-    int32_t* rows_lds = reinterpret_cast<int32_t*>(lds64);
-    uint32_t* dump = reinterpret_cast<uint32_t*>(lds64) + kQueryBlock;     // [KC][64] after the 64 row words
-    rows_lds[lane] = valid ? (asks ? my_row : -2 - my_row) : -1;   // -1: nothing to write; <= -2: all-padding row
     if (COUNT && valid) a.out_cand[my_row] = LOWER ? a.out_cand[my_row] + cand : cand;
-    const int32_t k = a.k;
-    const int32_t kk = cap + 1;                                         // words written per row: slot 0 and this pass's slots
-    const int32_t per_iter = kk >= kQueryBlock ? 1 : kQueryBlock / kk;  // rows written per pass
-    const int32_t sub = lane / kk;                                      // which of them this lane serves
-    const int32_t j0 = lane - sub * kk;                                 // word inside the row
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        if (pass) __syncthreads();
-#pragma unroll
-        for (int i = 0; i < KC; ++i) {
-            const bool real = best[i] < kEmptyKey;
-            const uint32_t word = pass == 0 ? (real ? (uint32_t)best[i] : 0xffffffffu)      // index or -1
-                                            : (real ? (uint32_t)(best[i] >> 32) : 0u);       // distance bits or 0.0f
-            dump[i * kDumpStride + lane] = word;
-        }
-        __syncthreads();
-        for (int32_t r0 = 0; r0 < kQueryBlock; r0 += per_iter) {
-            const int32_t ql = r0 + sub;
-            if (sub >= per_iter || ql >= kQueryBlock) continue;
-            const int32_t enc = rows_lds[ql];
-            if (enc == -1) continue;
-            const int32_t row = enc >= 0 ? enc : -2 - enc;
-            for (int32_t j = j0; j < kk; j += kQueryBlock) {
-                uint32_t word = pass == 0 ? (enc >= 0 ? (uint32_t)row : 0xffffffffu) : 0u;   // slot 0: the row itself at distance 0
-                if (pass == 1 && ((mask >> ql) & 1)) word = resume_word;                     // handed over: where to resume
-                if (j > 0) word = dump[(KC - cap + j - 1) * kDumpStride + ql];
-                const int32_t slot = j > 0 ? a.slot0 + j : 0;
-                if (pass == 0) a.out_idx[(int64_t)row * k + slot] = (int32_t)word;
-                else a.out_d2[(int64_t)row * k + slot] = __uint_as_float(word);
-            }
-        }
-    }
-    }
+    write_tile_rows<KC>(a, best, lds64, my_row, valid, asks, cap, mask, (uint32_t)(R + 1));
 }
 
 // The kernel: one workgroup of one wavefront per tile.  Tiles the ordering kernels marked as uneven take the

@@ -1,0 +1,73 @@
+"""GPU parity of the leaf kernel (boxes over runs of 32 sorted points, half-precision matrix pre-filter, exact
+re-evaluation) against the CPU oracle, bit for bit, at the sizes where it can go wrong, and against the plain walk on
+coordinates that strain the pre-filter's scaling."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2511_10442_amd import binding as B
+from paper_2511_10442_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def run(x, rs, k, direction=None, algo=3):
+    xt, rt = torch.from_numpy(x).to(DEV), torch.from_numpy(rs).to(DEV)
+    dt = None if direction is None else torch.from_numpy(direction).to(DEV)
+    idx, d2 = B.fg_query_binned(B.fg_bin_points(xt, rt, k), rt, k, direction=dt, algo=algo)
+    torch.cuda.synchronize()
+    return idx.cpu().numpy(), d2.cpu().numpy().view(np.uint32)
+
+
+def check(x, rs, k, direction=None):
+    oi, od = oracle.knn(x, rs, k, direction=direction)
+    gi, gd = run(x, rs, k, direction)
+    assert np.array_equal(gi, oi) and np.array_equal(gd, od.view(np.uint32))
+
+
+# list sizes and both passes of a long list; splits of one leaf less, equal and one more, empty and tiny ones; ties
+@pytest.mark.parametrize("d", range(2, 11))
+@pytest.mark.parametrize("k", [1, 2, 17, 18, 33, 49, 64, 65, 66, 100, 128])
+def test_matches_oracle(d, k):
+    sizes = [1300, 5, 0, 31, 32, 33, 63, 64, 65, 900, 1, 70]
+    x, rs = W.uniform(sum(sizes), d, seed=900 + 11 * d + k, sizes=sizes)
+    x[100:300] = x[100]                                      # duplicates: ties on distance 0
+    x[1600:2000] = x[1600] + 0.01 * (x[1600:2000] - 0.5)     # a dense cluster among sparse points
+    x = np.ascontiguousarray(x)
+    check(x, rs, k)
+    rng = np.random.Generator(np.random.PCG64(d * 131 + k))
+    check(x, rs, k, rng.integers(0, 4, size=x.shape[0]).astype(np.int32))
+
+
+@pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 64, 65, 2048, 2049, 4097])
+@pytest.mark.parametrize("d", [6, 9, 10])
+def test_small_sizes(n, d):
+    x, rs = W.uniform(n, d, seed=n + d)
+    check(x, rs, min(20, n + 2))
+
+
+# far from the origin, tiny and huge scales, a lattice (many equal distances), one far outlier, squares that overflow
+# and squares that underflow
+@pytest.mark.parametrize("d", [2, 6, 10])
+@pytest.mark.parametrize("kind", ["shifted", "tiny", "huge", "lattice", "outlier", "overflow", "underflow", "line"])
+def test_coordinates_that_strain_the_filter(d, kind):
+    x, rs = W.uniform(1500, d, seed=77 + d)
+    if kind == "shifted": x = x + np.float32(1000.0)
+    if kind == "tiny": x = x * np.float32(1e-12)
+    if kind == "huge": x = x * np.float32(1e15)
+    if kind == "lattice": x = np.floor(x * 4).astype(np.float32)
+    if kind == "outlier": x[7] = 1e6
+    if kind == "overflow": x = x * np.float32(1e30)
+    if kind == "underflow": x = x * np.float32(1e-24)
+    if kind == "line": x[:, 1:] = 0.25
+    check(np.ascontiguousarray(x.astype(np.float32)), rs, 24)
+
+
+# three levels of boxes (more than 131 072 points): every row against the plain walk
+@pytest.mark.parametrize("d,k", [(3, 16), (6, 20)])
+def test_three_levels(d, k):
+    x, rs = W.uniform(140_001, d, seed=3, sizes=[100_000, 40_001])
+    a, b = run(x, rs, k), run(x, rs, k, algo=1)
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
