@@ -246,6 +246,7 @@ k_query_leaf(QueryArgs a, LeafTree tree)
     if (__any(active)) {
     // boxes of the four groups, and the tile's
     float hext = 0.0f;         // largest half extent of the tile
+    float zmax = 0.0f;         // largest coordinate of its centre
 #pragma unroll
     for (int c = 0; c < D; ++c) {
         const float mx = row16_fmax_to_last(active ? x[c] : -3.4028235e38f);
@@ -258,6 +259,7 @@ k_query_leaf(QueryArgs a, LeafTree tree)
         const float zc = tmn * 0.5f + tmx * 0.5f;
         if (lane == 0) centre[c] = zc;
         hext = fmaxf(hext, fmaxf(tmx - zc, zc - tmn));
+        zmax = fmaxf(zmax, fabsf(zc));
     }
     __syncthreads();
 
@@ -285,7 +287,9 @@ k_query_leaf(QueryArgs a, LeafTree tree)
 #pragma unroll
         for (int g = 0; g < 4; ++g) gtau[g] = __builtin_amdgcn_readlane(gm, 16 * g + 15);
         const int32_t rb = wave_max_i32(active && full ? __float_as_int(rho) : 0);
-        const float reach = hext + __int_as_float(rb);
+        // (not finer than the spacing of floats at the centre: a lone point has no extent, and a scale without bound would
+        // overflow the scaled centre)
+        const float reach = fmaxf(hext + __int_as_float(rb), zmax * 5.9604645e-8f);
         int32_t se = 258 - (int32_t)(__float_as_uint(reach) >> 23);     // reach < 2^(e - 126): scale * reach < 32
         se = se > 254 ? 254 : (se < 1 ? 1 : se);
         scale = __int_as_float(se << 23);
@@ -547,7 +551,9 @@ k_query_leaf(QueryArgs a, LeafTree tree)
                 swap_halves(s0, s1);
                 uint32_t m = s0 | (s1 << 16);
                 const int32_t base = leaf * kLeafPts;
-                if (several) {                           // only the query's own row split
+                // Only the query's own row split: where the tile spans several, and at either end (there the filter has
+                // refused what lies outside already; this keeps a position beyond the last point out of the queue by itself)
+                if (several || base < pa || base + kLeafPts > pb) {
                     const int32_t from = sa > base ? sa - base : 0, to = sb - base < 32 ? sb - base : 32;
                     const uint64_t range = to > from ? ((1ull << to) - 1) & ~((1ull << from) - 1) : 0ull;
                     m &= (uint32_t)range;

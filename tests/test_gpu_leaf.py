@@ -41,11 +41,15 @@ def test_matches_oracle(d, k):
     check(x, rs, k, rng.integers(0, 4, size=x.shape[0]).astype(np.int32))
 
 
+# at an offset of 4096 a lone point or a set of equal ones has no extent to scale by
 @pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 64, 65, 2048, 2049, 4097])
 @pytest.mark.parametrize("d", [6, 9, 10])
-def test_small_sizes(n, d):
+@pytest.mark.parametrize("offset", [0.0, 4096.0, 1e30])
+def test_small_sizes(n, d, offset):
     x, rs = W.uniform(n, d, seed=n + d)
-    check(x, rs, min(20, n + 2))
+    check(np.ascontiguousarray(x + np.float32(offset)), rs, min(20, n + 2))
+    if n <= 65:
+        check(np.ascontiguousarray(x + np.float32(offset)), rs, 128)
 
 
 # far from the origin, tiny and huge scales, a lattice (many equal distances), one far outlier, squares that overflow
