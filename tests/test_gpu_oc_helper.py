@@ -38,3 +38,36 @@ def test_detector_sized_batch():
     M, Mn = run_gpu(asso, uq, uqrs, rs, n_maxuq, n_maxrs, True, 256)
     oM, oMn = oracle.oc_helper(asso, uq, uqrs, rs, n_maxuq, n_maxrs, True, 256)
     assert np.array_equal(M, oM) and np.array_equal(Mn, oMn)
+
+
+# what the row writer can get wrong: long runs of members (many steps at one row), an object that owns every vertex or
+# none, the same label asked for twice, objects per store (multiples of four and not), more members than rows of M
+@pytest.mark.parametrize("objs", [4, 7, 64, 66, 260])
+@pytest.mark.parametrize("kind", ["runs", "one_owner", "shuffled", "repeated"])
+def test_rows_from_member_lists(objs, kind):
+    rng = np.random.Generator(np.random.PCG64(objs))
+    sizes = [1300, 0, 700, 257]
+    rs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    asso = np.empty(rs[-1], dtype=np.int32)
+    unique, unique_rs = [], []
+    for s, m in enumerate(sizes):
+        if m == 0:
+            continue
+        labels = (rs[s] + np.sort(rng.choice(m, size=min(objs, m), replace=False))).astype(np.int32)
+        which = rng.integers(0, len(labels), size=m)
+        if kind == "runs":
+            which = np.sort(which)
+        if kind == "one_owner":
+            which[:] = len(labels) // 2
+        a = labels[which]
+        a[rng.random(m) < 0.1] = -1
+        asso[rs[s]:rs[s + 1]] = a
+        if kind == "repeated":
+            labels[::2] = labels[0]
+        unique.append(labels)
+        unique_rs.append(np.full(len(labels), s, dtype=np.int32))
+    unique, unique_rs = np.concatenate(unique), np.concatenate(unique_rs)
+    for n_maxuq, n_maxrs, rot in [(1300, 1300, 1), (1301, 1001, 5), (3, 1300, 1), (1300, 1400, 64)]:
+        oM, oMn = oracle.oc_helper(asso, unique, unique_rs, rs, n_maxuq, n_maxrs, True, rot)
+        M, Mn = run_gpu(asso, unique, unique_rs, rs, n_maxuq, n_maxrs, True, rot)
+        assert np.array_equal(M, oM) and np.array_equal(Mn, oMn)
