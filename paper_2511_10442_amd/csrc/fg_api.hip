@@ -251,10 +251,10 @@ static int32_t backward_morton_bits(int64_t n, int32_t d, int32_t n_segments, in
     return bits;
 }
 
-// n_bins, d_bin resolved and validated by the caller
+// n_bins, d_bin resolved and validated by the caller; check_only: everything but the launches
 static fg_status bin_points_impl(const float* coords, const int32_t* row_splits, int64_t n, int32_t d,
                                  int32_t n_segments, int32_t n_bins, int32_t d_bin, int32_t morton_bits,
-                                 void* workspace, size_t workspace_bytes, fg_binning* view, void* stream)
+                                 void* workspace, size_t workspace_bytes, bool check_only, fg_binning* view, void* stream)
 {
     if (!coords && n > 0) return FG_ERR_NULL;
     if (!row_splits || !workspace) return FG_ERR_NULL;
@@ -272,7 +272,7 @@ static fg_status bin_points_impl(const float* coords, const int32_t* row_splits,
     view->d_bin = d_bin;
     view->sub_bins = 1 << sub_shift;
     view->scratch = ws + L.scratch;
-    if (n == 0) return FG_OK;
+    if (n == 0 || check_only) return FG_OK;
     hipError_t e = launch_binning(coords, row_splits, (int32_t)n, d, n_segments, n_bins, d_bin, sub_shift, L.total_bins,
                                   (uint32_t*)(ws + L.keys), (float*)(ws + L.geom), (int32_t*)(ws + L.bin_idx),
                                   (int32_t*)(ws + L.scratch + scratch_layout(n).rank), (int32_t*)(ws + L.perm), (float*)(ws + L.rec),
@@ -290,7 +290,7 @@ fg_status fg_bin_points(const float* coords, const int32_t* row_splits, int64_t 
     if (st != FG_OK) return st;
     st = resolve_bins(n, d, n_segments, k_hint, &n_bins, &d_bin);
     if (st != FG_OK) return st;
-    return bin_points_impl(coords, row_splits, n, d, n_segments, n_bins, d_bin, 0, workspace, workspace_bytes, view,
+    return bin_points_impl(coords, row_splits, n, d, n_segments, n_bins, d_bin, 0, workspace, workspace_bytes, false, view,
                            stream);
 }
 
@@ -310,7 +310,7 @@ fg_status fg_query_binned(const fg_binning* view, const int32_t* row_splits, int
     if (view->n_bins < 1 || view->cells_per_segment < 1 ||
         view->cells_per_segment * (int64_t)n_segments > FG_MAX_TOTAL_BINS || view->record_floats != 4 * rec_vecs(d))
         return FG_ERR_BAD_SHAPE;
-    QueryArgs a;
+    QueryArgs a = {};
     a.rec = reinterpret_cast<const float4*>(view->sorted_points); a.bounds = view->bin_bounds; a.geom = view->seg_geom;
     const ScratchLayout S = scratch_layout(n);
     char* sc = (char*)view->scratch;
@@ -339,6 +339,16 @@ static fg_status knn_impl(const float* coords, const int32_t* row_splits, const 
     if (n == 0) return FG_OK;
     if (!out_idx || !out_d2) return FG_ERR_NULL;
     fg_binning view;
+    if (!out_candidates && takes_small_path(n, k)) {     // every pair is compared: the same checks, but nothing is binned
+        st = resolve_bins(n, d, n_segments, k, &n_bins, &d_bin);
+        if (st == FG_OK)
+            st = bin_points_impl(coords, row_splits, n, d, n_segments, n_bins, d_bin, 0, workspace, workspace_bytes, true, &view, stream);
+        if (st != FG_OK) return st;
+        QueryArgs a = {};
+        a.coords = coords; a.row_splits = row_splits; a.dir = dir; a.out_idx = out_idx; a.out_d2 = out_d2;
+        a.n = (int32_t)n; a.d = d; a.n_segments = n_segments; a.k = k;
+        return launch_query(a, d, d_bin, (hipStream_t)stream) == hipSuccess ? FG_OK : FG_ERR_LAUNCH;
+    }
     st = fg_bin_points(coords, row_splits, n, d, n_segments, k, n_bins, d_bin, workspace, workspace_bytes, &view,
                        stream);
     if (st != FG_OK) return st;
@@ -434,7 +444,7 @@ fg_status fg_knn_backward(const float* grad_d2, const int32_t* idx, const float*
         int32_t db = 0;
         const int32_t bits = backward_morton_bits(n, d, n_segments, k, &db);
         if (bits < 1) return FG_ERR_BAD_SHAPE;
-        st = bin_points_impl(coords, row_splits, n, d, n_segments, 1 << bits, db, bits, workspace, workspace_bytes, &view,
+        st = bin_points_impl(coords, row_splits, n, d, n_segments, 1 << bits, db, bits, workspace, workspace_bytes, false, &view,
                              stream);
         if (st != FG_OK) return st;
         perm = (const int32_t*)((const char*)workspace + make_layout(n, d, n_segments, 1 << bits, db, 0).perm);

@@ -15,6 +15,7 @@ struct QueryArgs {
     const float4* rec;         // [n][rec_vecs(d)] bin-ordered point records: coordinates, original row, padding
     const int32_t* bounds;     // [S*T+1], T counted in slices (see sub_shift)
     const float* geom;         // [S][d_bin][4]
+    const float* coords;       // [n][d] the points in their original order: given (and rec not) where nothing was binned, else nullptr
     const int32_t* row_splits; // [S+1]
     const int32_t* dir;        // [n] direction flags in ORIGINAL row order, or nullptr
     int32_t* out_idx;          // [n][k]
@@ -50,6 +51,14 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
                                                  only perm is written, plus for d = 3 a copy of coords in the original
                                                  order padded to float4 in place of the records */,
                           hipStream_t stream);
+
+// Up to this many points and one list of keys (K <= 65) every pair is compared, one wavefront per query, without bins.
+// Whole forward call, one split, against binning and the bins' kernels:
+//   1000 points: d = 3, K = 10  70 -> 11 us; d = 5, K = 40 293 -> 15 us; d = 10, K = 20 122 -> 13 us
+//   4000 points: d = 2, K = 16  53 -> 25 us; d = 3, K = 40 122 -> 35 us; d = 8, K = 64  327 -> 50 us
+// The cost grows with the square of n and two-dimensional bins, the cheapest, meet it at some 6000 points.
+constexpr int32_t kSmallN = 4096;
+inline bool takes_small_path(int64_t n, int32_t k) { return n <= kSmallN && k <= 65; }
 
 // d = 2..10, d_bin = 2..min(d,5)
 hipError_t launch_query(const QueryArgs& a, int32_t d, int32_t d_bin, hipStream_t stream);

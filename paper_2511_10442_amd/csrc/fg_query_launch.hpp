@@ -4,6 +4,7 @@
 #include "fg_query_tile.hpp"
 #include "fg_query_list.hpp"
 #include "fg_query_leaf.hpp"
+#include "fg_query_small.hpp"
 
 namespace fg {
 
@@ -290,6 +291,11 @@ static hipError_t launch_query_impl(const QueryArgs& a_in, hipStream_t stream)
     a.slot0 = 0;
     a.k_list = cap < 64 ? cap : 64;
     if constexpr (!COUNT) {
+        if (a.algo == 0 && takes_small_path(a.n, a.k)) {
+            if (a.coords) hipLaunchKernelGGL((k_query_small<D, false>), dim3(a.n), dim3(kQueryBlock), 0, stream, a);
+            else hipLaunchKernelGGL((k_query_small<D, true>), dim3(a.n), dim3(kQueryBlock), 0, stream, a);
+            return hipGetLastError();
+        }
         if (a.algo == 3 || (a.algo == 0 && D >= kLeafMinD)) {
             launch_leaf_pass<D, false>(a, stream);
             if (cap > 64) {
