@@ -15,7 +15,6 @@ struct QueryArgs {
     const float4* rec;         // [n][rec_vecs(d)] bin-ordered point records: coordinates, original row, padding
     const int32_t* bounds;     // [S*T+1], T counted in slices (see sub_shift)
     const float* geom;         // [S][d_bin][4]
-    const float* coords;       // [n][d] the points in their original order: given (and rec not) where nothing was binned, else nullptr
     const int32_t* row_splits; // [S+1]
     const int32_t* dir;        // [n] direction flags in ORIGINAL row order, or nullptr
     int32_t* out_idx;          // [n][k]
@@ -37,6 +36,9 @@ struct QueryArgs {
     int32_t sub_shift;         // log2 of the slices every bin is cut into along the last binning dimension
     int32_t algo;              // 0: tile kernel + list kernel, 1: one lane per query for everything, 2: as 0 with the flattened scan on every tile
     int32_t defer_lanes;       // tile kernel: go on past shell 1 only while more lanes than this are unfinished
+    // of some kernels only, and last: the fields above keep their places in the other kernels' arguments
+    int32_t dense_class;       // > 0: tiles of this work class and above are the leaf kernel's, the others the tile kernel's
+    const float* coords;       // [n][d] the points in their original order: given (and rec not) where nothing was binned, else nullptr
 };
 
 // Host-side launchers, one per translation unit.  Each returns hipGetLastError() of its launches.

@@ -52,10 +52,12 @@ static inline LeafTree leaf_tree(void* area, int32_t n)
 }
 
 template <int D>
-static __global__ void __launch_bounds__(256) k_leaf_boxes(const float4* __restrict__ rec, int32_t n, float4* __restrict__ boxes,
-                                                           int32_t* __restrict__ work_count)
+static __global__ void __launch_bounds__(256) k_leaf_boxes(QueryArgs a, float4* __restrict__ boxes)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *work_count = 0;        // nothing is handed over on this path
+    const float4* __restrict__ rec = a.rec;
+    const int32_t n = a.n;
+    if (a.dense_class > 0 && dense_tiles(a) == 0) return;
+    if (a.dense_class == 0 && blockIdx.x == 0 && threadIdx.x == 0) *a.work_count = 0;        // nothing is handed over on this path
     const int32_t p = blockIdx.x * 256 + threadIdx.x;
     float x[D];
     int32_t row;
@@ -215,7 +217,10 @@ k_query_leaf(QueryArgs a, LeafTree tree)
     // so that they meet in its L2 (runs of 4 to 256: the same within 3 %; heaviest tiles first, as the tile kernel
     // takes them: 500k uniform points, d = 8, K = 64 17.4 against 15.3 ms).
     int32_t tile = blockIdx.x;
-    if (tile < (int32_t)(gridDim.x & ~127u)) {
+    if (a.dense_class > 0) {                 // only the heaviest tiles, in the order of the ranking kernels
+        if (tile >= dense_tiles(a)) return;
+        tile = a.tile_order[tile] & ((1 << kOrderFlagBit) - 1);
+    } else if (tile < (int32_t)(gridDim.x & ~127u)) {
         const int32_t xcd = tile & 7, j = tile >> 3;
         tile = ((j >> 4) * 8 + xcd) * 16 + (j & 15);
     }
@@ -595,9 +600,9 @@ static void launch_leaf_pass(const QueryArgs& a, hipStream_t stream)
 {
     const LeafTree t = leaf_tree(a.work_list, a.n);
     const int grid = (a.n + kQueryBlock - 1) / kQueryBlock;
-    if (!LOWER) {       // the second pass of a long list finds the boxes of the first
+    if (!LOWER || a.dense_class > 0) {       // the second pass of a long list finds the boxes of the first
         constexpr int NB = box_vecs<D>();
-        hipLaunchKernelGGL(k_leaf_boxes<D>, dim3((a.n + 255) / 256), dim3(256), 0, stream, a.rec, a.n, t.boxes, a.work_count);
+        hipLaunchKernelGGL(k_leaf_boxes<D>, dim3((a.n + 255) / 256), dim3(256), 0, stream, a, t.boxes);
         float4* const box2 = t.boxes + (int64_t)t.n1 * NB;
         if (t.has2) hipLaunchKernelGGL(k_node_boxes<D>, dim3((t.n2 + 3) / 4), dim3(256), 0, stream, t.boxes, t.n1, box2, t.n2);
         if (t.has3) hipLaunchKernelGGL(k_node_boxes<D>, dim3((t.n3 + 3) / 4), dim3(256), 0, stream, box2, t.n2, box2 + (int64_t)t.n2 * NB, t.n3);

@@ -581,6 +581,14 @@ __device__ __forceinline__ void tile_body(const QueryArgs& a, const int32_t tile
     write_tile_rows<KC>(a, best, lds64, my_row, valid, asks, cap, mask, (uint32_t)(R + 1));
 }
 
+// Tiles of class a.dense_class and above, which are the first of the order: summed from the classes' histogram.
+__device__ __forceinline__ int32_t dense_tiles(const QueryArgs& a)
+{
+    const int32_t* const hist = a.tile_order + 2 * ((a.n + kQueryBlock - 1) / kQueryBlock);
+    const int lane = threadIdx.x & (kQueryBlock - 1);
+    return wave_sum_i32(lane >= a.dense_class ? hist[lane] : 0);      // one lane per class
+}
+
 // The kernel: one workgroup of one wavefront per tile.  Tiles the ordering kernels marked as uneven take the
 // flattened scan, all others, and every tile of an unordered launch, the direct one.  One kernel with a branch,
 // not two kernels: a tile alone takes ~0.1 ms from its first shell to its last row whatever runs beside it, so a
@@ -594,6 +602,12 @@ k_query_tile_sorted(QueryArgs a)
     // an entry of the order: the tile, heaviest first, and above it the flag of an uneven tile
     const int32_t entry = a.tile_order ? a.tile_order[blockIdx.x] : (int32_t)blockIdx.x;
     const int32_t tile = entry & ((1 << kOrderFlagBit) - 1);
+    if constexpr (D == 2) {
+        if (a.dense_class > 0 && (int32_t)blockIdx.x < dense_tiles(a)) {      // the leaf kernel has taken it
+            if (threadIdx.x == 0) a.handed[tile] = 0;
+            return;
+        }
+    }
     if constexpr (!COUNT && tile_has_flat<KC, D>()) {
         const bool uneven = a.algo == 2 || ((entry >> kOrderFlagBit) & 1);
         if (uneven) {

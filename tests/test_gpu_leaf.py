@@ -75,3 +75,21 @@ def test_three_levels(d, k):
     x, rs = W.uniform(140_001, d, seed=3, sizes=[100_000, 40_001])
     a, b = run(x, rs, k), run(x, rs, k, algo=1)
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
+# two dimensions and more than 2^22 points: the heaviest tiles are the leaf kernel's, the others the tile kernel's, in both
+# passes of a long list; against the tile kernel alone on every row and the oracle on sampled ones
+@pytest.mark.parametrize("k", [9, 70])
+def test_dense_tiles_of_two_dimensions(k):
+    rng = np.random.Generator(np.random.PCG64(41))
+    n = (1 << 22) + 777
+    r = rng.random(n) ** 3
+    phi = rng.random(n) * 2.0 * np.pi
+    x = np.ascontiguousarray(np.stack([r * np.cos(phi), r * np.sin(phi)], axis=1).astype(np.float32))
+    rs = np.array([0, 2_500_000, 2_500_000, 4_000_000, n], dtype=np.int32)
+    a, b = run(x, rs, k, algo=0), run(x, rs, k, algo=4)
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    near = np.argsort(r)[:20]                                     # inside the densest bin
+    rows = np.unique(np.concatenate([near, rng.choice(n, size=40, replace=False)])).astype(np.int64)
+    oi, od = oracle.knn_rows(x, rs, k, rows)
+    assert np.array_equal(a[0][rows], oi) and np.array_equal(a[1][rows], od.view(np.uint32))
