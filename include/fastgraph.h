@@ -99,14 +99,17 @@ typedef struct {
                                   depend on it) */
     int32_t record_floats;     /* floats per record of sorted_points: d + 1 rounded up to a multiple of 4 */
     void* scratch;             /* opaque: scratch of the query stage inside the workspace.  Its first int32 holds, after
-                                  fg_query_binned, the number of queries the tile kernel handed to the list kernel (a
-                                  diagnostic; nothing else in it is meant to be read) */
+                                  fg_query_binned, the number of queries the tile kernel handed to the list kernel, 0 where
+                                  another kernel served the call (a diagnostic; nothing else in it is meant
+                                  to be read) */
 } fg_binning;
 
 /* Options of the query stage; none changes the result.  A NULL pointer means all defaults. */
 typedef struct {
     const int32_t* dir;        /* [n] direction flags in ORIGINAL row order (see fg_binned_select_knn_dir), or NULL */
-    int32_t algo;              /* 0: the default: tile kernel + list kernel, from six dimensions on the leaf kernel;
+    int32_t algo;              /* 0: the default: every pair compared up to 4096 points and K <= 65, else the
+                                  leaf kernel from six dimensions on (and for the densest tiles of more than 2^22
+                                  points in two), else tile kernel + list kernel;
                                   1: the one-lane-per-query shell walk for every query (slower; kept for
                                   cross-checking); 2: tile kernel + list kernel with the tile kernel's flattened scan on
                                   every tile instead of the uneven ones only (for tests); 3: leaf kernel; 4: tile
