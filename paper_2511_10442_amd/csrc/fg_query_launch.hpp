@@ -278,7 +278,7 @@ static void launch_query_pass(const QueryArgs& a_in, hipStream_t stream)
 // From this many dimensions on the leaf kernel is the default.  Query stage, tile + list kernel against leaf kernel:
 //   200k uniform points, d = 6, K = 40      3.69 against  2.32 ms     1M the same                     13.0 against 11.5 ms
 //   400k, d = 6, K = 10                     3.68 against  2.92 ms     400k, d = 7, K = 16              6.2 against  6.1 ms
-//   500k, d = 8, K = 64                    21.6  against 15.8 ms      60k, d = 10, K = 40              7.4 against  1.25 ms
+//   500k, d = 8, K = 64                    21.6  against 11.5 ms      60k, d = 10, K = 40              7.4 against  1.25 ms
 //   2k, d = 6, K = 10                       0.28 against  0.09 ms     2k, d = 10, K = 40               1.31 against 0.19 ms
 //   100k Gaussian mixture, d = 6, K = 60    5.3  against  2.9 ms
 //   below: 1M uniform points, d = 5, K = 40 3.2  against  9.0 ms      100k mixture, d = 4, K = 40      0.65 against 1.27 ms
