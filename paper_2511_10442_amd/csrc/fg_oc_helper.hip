@@ -27,7 +27,7 @@ namespace fg {
 
 constexpr int kOcBlock = 64;
 constexpr int kOcBatch = 8;       // independent loads kept in flight per lane
-constexpr int kOcChunk = 128;     // walk positions per chunk, and output rows per block of the M_not kernel
+constexpr int kOcChunk = 128;     // walk positions per chunk
 
 struct OcWindow { int32_t uq, start, len, rot; };
 
@@ -228,155 +228,123 @@ k_oc_members(const int32_t* __restrict__ asso_idx, const int32_t* __restrict__ u
     }
 }
 
-// Rows r0 .. r1-1 of one object by walking its vertices: for objects with more members than rows in M, whose later
-// members M does not tell.
-__device__ __forceinline__ void oc_others_walk(const OcWindow& w, int32_t k, int32_t r0, int32_t r1, const int32_t* __restrict__ asso_idx,
-                                               int32_t n_unique, int32_t n_chunks, const int32_t* __restrict__ counts,
-                                               int32_t* __restrict__ M_not)
-{
-    // largest chunk c whose start has at most r0 non-members before it: c*C - members_before(c) <= r0
-    int32_t lo = 0, hi = n_chunks;           // invariant: others_before(lo) <= r0; chunks >= hi are too far (or hi = n_chunks)
-    while (hi - lo > 1) {
-        const int32_t mid = (lo + hi) >> 1;
-        const int32_t before = mid * kOcChunk - counts[(int64_t)mid * n_unique + k];
-        if (before <= r0) lo = mid; else hi = mid;
-    }
-    int32_t p = lo * kOcChunk;
-    int32_t fill = p - counts[(int64_t)lo * n_unique + k];      // non-members before walk position p
-    // phase 1, no stores: advance to the walk position where this object's non-member count reaches r0.
-    // Lanes need different numbers of steps here; keeping it apart from the emission lets the emission
-    // run with every lane at the same output row.
-    while (p < w.len && fill < r0) {
-        int32_t v[kOcBatch];
-#pragma unroll
-        for (int u = 0; u < kOcBatch; ++u) v[u] = p + u < w.len ? asso_idx[oc_vertex(w, p + u)] : w.uq;
-        int32_t adv = 0;
-#pragma unroll
-        for (int u = 0; u < kOcBatch; ++u) {
-            if (fill < r0) { fill += v[u] != w.uq; ++adv; }
-        }
-        p += adv;
-    }
-    // phase 2: emit rows r0 .. r1-1; a lane falls one row behind its neighbours only when it meets a member
-    int32_t r = r0;
-    while (p < w.len && r < r1) {
-        int32_t v[kOcBatch];
-#pragma unroll
-        for (int u = 0; u < kOcBatch; ++u) v[u] = p + u < w.len ? asso_idx[oc_vertex(w, p + u)] : w.uq;   // past the end: skipped like a member
-#pragma unroll
-        for (int u = 0; u < kOcBatch; ++u) {
-            if (v[u] != w.uq && r < r1) { M_not[(int64_t)r * n_unique + k] = oc_vertex(w, p + u); ++r; }
-        }
-        p += kOcBatch;
-    }
-    for (; r < r1; ++r) M_not[(int64_t)r * n_unique + k] = -1;
-}
-
-// One wavefront per 64 * VEC objects and kOcRows output rows of M_not; a lane has VEC neighbouring objects and writes
-// them with one store a row (VEC = 4: 1 KB a wavefront and row; needs n_unique a multiple of four and M_not on a 16-byte
-// boundary, else VEC = 1).
-constexpr int kOcRows = 256;
-constexpr int kOcSteps = 4;       // next steps of an object held in registers
-template <int VEC>
+// One wavefront per 64 objects and `rows` output rows of M_not, a lane each, kOcTile rows at a time: first every lane
+// adds its object's steps to its column of an LDS table (steps[i] = members that come before row i and after row i - 1),
+// then the rows are written with a running sum.  A step is a member of the list in M, or, for an object with more members
+// than M has rows, a member met on a walk over the vertices; each lane goes at its own pace through its own steps, and
+// however unevenly members are spread, all objects write the same row at the same time.  The first steps of the next rows
+// are requested before the present rows are written.
+// (Steps in registers, refilled by the whole wavefront whenever one of its objects had used four: 302 us at 10 x 100,000
+// vertices and 2,000 objects, but 16 times the walk's time with few objects, whose members lie close.)
+constexpr int kOcTile = 32;
+constexpr int kOcAhead = 4;
+constexpr int kOcOthersWaves = 4096;
 __global__ void __launch_bounds__(kOcBlock)
 k_oc_others(const int32_t* __restrict__ asso_idx, const int32_t* __restrict__ unique_idx,
             const int32_t* __restrict__ unique_rs_asso, const int32_t* __restrict__ rs, int32_t n_vert, int32_t n_unique,
-            int32_t n_splits, int32_t n_maxuq, int32_t n_maxrs, int32_t rot_block, int32_t n_chunks,
+            int32_t n_splits, int32_t n_maxuq, int32_t n_maxrs, int32_t rot_block, int32_t n_chunks, int32_t rows,
             const int32_t* __restrict__ counts, const int32_t* __restrict__ M, int32_t* __restrict__ M_not)
 {
-    // n_unique is a multiple of VEC, so a lane's objects all exist or none does; lanes without any shadow the last ones
-    // (the wavefront's minimum below takes every lane) and write nothing
-    const int32_t at_k = (blockIdx.x * kOcBlock + threadIdx.x) * VEC;
-    const bool mine = at_k < n_unique;
-    const int32_t k0 = mine ? at_k : n_unique - VEC;
-    const int32_t r0 = blockIdx.y * kOcRows;
-    const int32_t r1 = r0 + kOcRows < n_maxrs ? r0 + kOcRows : n_maxrs;
-    OcWindow w[VEC];
-    int32_t total[VEC], j[VEC], step[VEC][kOcSteps];
-    bool cut = false;
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) {
-        w[i] = oc_window(k0 + i, unique_idx, unique_rs_asso, rs, n_vert, n_splits, n_maxrs, rot_block);
-        total[i] = counts[(int64_t)n_chunks * n_unique + k0 + i];
-        cut = cut || total[i] > n_maxuq;
-        j[i] = 0;
-    }
-    if (__any(cut)) {
-#pragma unroll 1
-        for (int i = 0; i < VEC && mine; ++i) {
-            const OcWindow wi = oc_window(k0 + i, unique_idx, unique_rs_asso, rs, n_vert, n_splits, n_maxrs, rot_block);
-            oc_others_walk(wi, k0 + i, r0, r1, asso_idx, n_unique, n_chunks, counts, M_not);
-        }
-        return;
-    }
-    // the row from which on member q of object i lies behind: its walk position less the members before it
-    auto row_of = [&](int i, int32_t q) -> int32_t {
-        int32_t o = M[(int64_t)q * n_unique + k0 + i] - w[i].start - w[i].rot;
-        if (o < 0) o += w[i].len;
+    __shared__ int32_t steps[kOcTile][kOcBlock];
+    const int lane = threadIdx.x;
+    const int32_t k = blockIdx.x * kOcBlock + lane;
+    if (k >= n_unique) return;
+    const int32_t r0 = blockIdx.y * rows;
+    const int32_t r1 = r0 + rows < n_maxrs ? r0 + rows : n_maxrs;
+    const OcWindow w = oc_window(k, unique_idx, unique_rs_asso, rs, n_vert, n_splits, n_maxrs, rot_block);
+    const int32_t total = counts[(int64_t)n_chunks * n_unique + k];
+    const bool listed = total <= n_maxuq;          // M holds every member
+    // the row before which member q comes: its walk position less the members before it
+    auto row_of = [&](int32_t vertex, int32_t q) -> int32_t {
+        int32_t o = vertex - w.start - w.rot;
+        if (o < 0) o += w.len;
         return o - q;
     };
-    // moves every object past its members that lie before row r, then reads the next steps
-    auto seek = [&](int32_t r, bool far) {
-        if (far) {                                       // rows of the members ascend: halving
-            int32_t hi[VEC];
+    auto entry = [&](int32_t q) -> int32_t { return M[(int64_t)q * n_unique + k]; };
+    // q: members before row r0
+    int32_t q = 0;
+    if (listed) {
+        for (int32_t hi = total; q < hi;) {        // rows of the members ascend: halving
+            const int32_t mid = (q + hi) >> 1;
+            if (row_of(entry(mid), mid) < r0) q = mid + 1; else hi = mid;
+        }
+    } else {
+        // the last chunk with at most r0 non-members before it, then on to the place right after non-member r0 - 1
+        int32_t lo = 0, hi = n_chunks;
+        while (hi - lo > 1) {
+            const int32_t mid = (lo + hi) >> 1;
+            if (mid * kOcChunk - counts[(int64_t)mid * n_unique + k] <= r0) lo = mid; else hi = mid;
+        }
+        int32_t p = lo * kOcChunk;
+        q = counts[(int64_t)lo * n_unique + k];
+        while (p < w.len && p - q < r0) {
+            int32_t v[kOcBatch];
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) hi[i] = total[i];
-            for (;;) {
-                bool open = false;
+            for (int u = 0; u < kOcBatch; ++u) v[u] = p + u < w.len ? asso_idx[oc_vertex(w, p + u)] : w.uq;
 #pragma unroll
-                for (int i = 0; i < VEC; ++i) open = open || j[i] < hi[i];
-                if (!__any(open)) break;
+            for (int u = 0; u < kOcBatch; ++u) {
+                if (p < w.len && p - q < r0) { q += v[u] == w.uq; ++p; }
+            }
+        }
+    }
+    int32_t next[kOcAhead];
+    auto request = [&]() {
 #pragma unroll
-                for (int i = 0; i < VEC; ++i) {
-                    if (j[i] < hi[i]) {
-                        const int32_t mid = (j[i] + hi[i]) >> 1;
-                        if (row_of(i, mid) <= r) j[i] = mid + 1; else hi[i] = mid;
+        for (int u = 0; u < kOcAhead; ++u) next[u] = listed && q + u < total ? entry(q + u) : 0;
+    };
+    request();
+#pragma unroll
+    for (int i = 0; i < kOcTile; ++i) steps[i][lane] = 0;
+    int32_t before = q;
+    for (int32_t rb = r0; rb < r1; rb += kOcTile) {
+        const int32_t re = rb + kOcTile;
+        // false: the step (if there is one) belongs to a later row
+        auto step_at = [&](int32_t row) -> bool {
+            if (row >= re) return false;
+            atomicAdd(&steps[row - rb][lane], 1);      // the lane's own word: only so that nothing waits for a result
+            ++q;
+            return true;
+        };
+        if (listed) {
+            bool open = true;
+#pragma unroll
+            for (int u = 0; u < kOcAhead; ++u) open = open && q < total && step_at(row_of(next[u], q));
+            while (open) {
+                int32_t v[kOcBatch];
+#pragma unroll
+                for (int u = 0; u < kOcBatch; ++u) v[u] = q + u < total ? entry(q + u) : 0;
+#pragma unroll
+                for (int u = 0; u < kOcBatch; ++u) open = open && q < total && step_at(row_of(v[u], q));
+            }
+            request();
+        } else {
+            int32_t p = rb + q;
+            while (p < w.len && p - q < re) {
+                int32_t v[kOcBatch];
+#pragma unroll
+                for (int u = 0; u < kOcBatch; ++u) v[u] = p + u < w.len ? asso_idx[oc_vertex(w, p + u)] : w.uq;
+#pragma unroll
+                for (int u = 0; u < kOcBatch; ++u) {
+                    if (p < w.len && p - q < re) {
+                        if (v[u] == w.uq) step_at(p - q);
+                        ++p;
                     }
                 }
             }
         }
+        int32_t* at = M_not + (int64_t)rb * n_unique + k;
+        const int32_t some = re < r1 ? kOcTile : r1 - rb;
+        for (int32_t i0 = 0; i0 < some; i0 += kOcBatch) {
+            int32_t s[kOcBatch];
 #pragma unroll
-        for (int i = 0; i < VEC; ++i)
+            for (int u = 0; u < kOcBatch; ++u) { s[u] = steps[i0 + u][lane]; steps[i0 + u][lane] = 0; }
 #pragma unroll
-            for (int q = 0; q < kOcSteps; ++q) step[i][q] = j[i] + q < total[i] ? row_of(i, j[i] + q) : 0x7fffffff;
-    };
-    seek(r0, true);
-    for (int32_t r = r0; r < r1;) {
-        // the steps in registers hold up to the row where some object reaches its last one
-        int32_t stop = r1;
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) stop = step[i][kOcSteps - 1] < stop ? step[i][kOcSteps - 1] : stop;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int32_t other = __shfl_xor(stop, o, 64);
-            stop = other < stop ? other : stop;
-        }
-        stop = __builtin_amdgcn_readfirstlane(stop);
-        for (; r < stop; ++r) {
-            int32_t v[VEC];
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) {
-                int32_t p = r + j[i];
-#pragma unroll
-                for (int q = 0; q < kOcSteps - 1; ++q) p += r >= step[i][q];
-                v[i] = p < w[i].len ? oc_vertex(w[i], p) : -1;
+            for (int u = 0; u < kOcBatch; ++u) {
+                before += s[u];
+                const int32_t p = rb + i0 + u + before;
+                if (i0 + u < some) *at = p < w.len ? oc_vertex(w, p) : -1;
+                at += n_unique;
             }
-            if (!mine) continue;
-            int32_t* const at = M_not + (int64_t)r * n_unique + k0;
-            if constexpr (VEC == 4) *reinterpret_cast<int4*>(at) = make_int4(v[0], v[1], v[2], v[3]);
-            else at[0] = v[0];
-        }
-        if (r < r1) {
-            bool far = false;
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) {
-                int32_t passed = 0;
-#pragma unroll
-                for (int q = 0; q < kOcSteps; ++q) passed += step[i][q] <= r;
-                j[i] += passed;
-                far = far || passed == kOcSteps;         // a run of members: there may be any number more of them
-            }
-            seek(r, __any(far));
         }
     }
 }
@@ -407,13 +375,12 @@ hipError_t launch_oc_helper(const int32_t* asso_idx, const int32_t* unique_idx, 
     hipLaunchKernelGGL(k_oc_members, dim3(groups, n_chunks + (unsigned)pads), dim3(kOcBlock), 0, stream, asso_idx, unique_idx,
                        unique_rs_asso, rs, n_vert, n_unique, n_splits, n_maxuq, n_maxrs, rot_block, n_chunks, counts, M);
     if (calc_m_not) {
-        const unsigned rows = (unsigned)((n_maxrs + (int64_t)kOcRows - 1) / kOcRows);
-        if (n_unique % 4 == 0 && ((uintptr_t)M_not & 15) == 0)
-            hipLaunchKernelGGL(k_oc_others<4>, dim3((groups + 3) / 4, rows), dim3(kOcBlock), 0, stream, asso_idx, unique_idx, unique_rs_asso,
-                               rs, n_vert, n_unique, n_splits, n_maxuq, n_maxrs, rot_block, n_chunks, counts, M, M_not);
-        else
-            hipLaunchKernelGGL(k_oc_others<1>, dim3(groups, rows), dim3(kOcBlock), 0, stream, asso_idx, unique_idx, unique_rs_asso,
-                               rs, n_vert, n_unique, n_splits, n_maxuq, n_maxrs, rot_block, n_chunks, counts, M, M_not);
+        // rows per wavefront: its search for the first one is paid once, but the chip holds some 5000 of these wavefronts
+        int32_t rows = 4 * kOcTile;
+        while (rows > kOcTile && (int64_t)groups * ((n_maxrs + rows - 1) / rows) < kOcOthersWaves) rows >>= 1;
+        hipLaunchKernelGGL(k_oc_others, dim3(groups, (unsigned)((n_maxrs + (int64_t)rows - 1) / rows)), dim3(kOcBlock), 0, stream,
+                           asso_idx, unique_idx, unique_rs_asso, rs, n_vert, n_unique, n_splits, n_maxuq, n_maxrs, rot_block,
+                           n_chunks, rows, counts, M, M_not);
     }
     return hipGetLastError();
 }

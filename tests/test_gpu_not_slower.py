@@ -1,0 +1,79 @@
+"""Inputs on which the default choice of kernels was once much slower than another kernel of the library on the same call:
+both are timed in turn on the same inputs, the shortest of several runs each, and the bound lies between the ratio that
+was wrong and the one that is right."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_10442_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def shortest(calls, runs=7, reps=3):
+    """Microseconds of each call, in turn."""
+    best = [float("inf")] * len(calls)
+    for _ in range(runs + 1):                            # the first run warms up
+        for i, call in enumerate(calls):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(reps):
+                call()
+            b.record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], a.elapsed_time(b) / reps * 1e3)
+    print("us:", ["%.1f" % b for b in best])
+    return best
+
+
+def cloud(kind, n, d):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(17)
+    x = torch.rand(n, d, generator=gen, device=DEV)
+    pick = lambda m: torch.randint(0, m, (n,), generator=gen, device=DEV)
+    if kind == "lattice":
+        return torch.floor(x * 4)
+    if kind.startswith("clusters"):
+        count, width = {"clusters_fine": (5000, 0.01), "clusters_tight": (50, 0.001)}[kind]
+        return x[:count][pick(count)] + width * torch.randn(n, d, generator=gen, device=DEV)
+    if kind == "outliers":
+        x[torch.rand(n, generator=gen, device=DEV) < 0.001] *= 1000.0
+    return x
+
+
+# the object-condensation matrices: M and M_not together against M alone, and against the same call with rows of M for every
+# member
+def objects(splits, size, count, sort=False):
+    rng = np.random.Generator(np.random.PCG64(splits * 7 + count))
+    label, unique, unique_rs = [], [], []
+    for s in range(splits):
+        points = np.sort(rng.choice(size, count, replace=False)) + s * size
+        weight = rng.random(count) ** 3 + 1e-3
+        a = points[np.minimum(np.searchsorted(np.cumsum(weight / weight.sum()), rng.random(size)), count - 1)]
+        if sort:
+            a = np.sort(a)
+        a[rng.random(size) < 0.1] = -1
+        label.append(a)
+        unique.append(points)
+        unique_rs.append(np.full(count, s))
+    label, unique, unique_rs = (np.concatenate(v).astype(np.int32) for v in (label, unique, unique_rs))
+    members = np.bincount(label[label >= 0], minlength=splits * size)[unique]
+    rs = (np.arange(splits + 1) * size).astype(np.int32)
+    return [torch.from_numpy(v).to(DEV) for v in (label, unique, unique_rs, rs)], int(members.max()), int(np.median(members))
+
+
+@pytest.mark.parametrize("splits,size,count,sort,clip,bound", [
+    (64, 1500, 8, False, False, 4.0),                    # few objects a split: 55, now 1.5
+    (10, 100_000, 50, True, False, 15.0),                # members of an object one after the other: 81, now 6.4
+    (10, 100_000, 200, False, True, 2.5),                # half of the objects with more members than rows in M: 4.9, now 1.6
+])
+def test_rows_of_others(splits, size, count, sort, clip, bound):
+    arrays, most, median = objects(splits, size, count, sort)
+    u = arrays[1].numel()
+    M = torch.empty((most, u), dtype=torch.int32, device=DEV)
+    M_not = torch.empty((size, u), dtype=torch.int32, device=DEV)
+    ws = torch.empty(max(256, B.fg_oc_helper_workspace_size(u, size)), dtype=torch.uint8, device=DEV)
+    call = lambda rows, others: lambda: B.fg_oc_helper(*arrays, rows, size, others, 1, M[:rows], M_not, ws)
+    t = shortest([call(median if clip else most, True), call(most, clip)])
+    assert t[0] <= bound * t[1], "%.0f against %.0f us" % (t[0], t[1])
