@@ -4,7 +4,7 @@
 // what differs is how unsearched points are ruled out and how candidates are sifted:
 //   * the sorted points are cut into leaves of 32 consecutive points; every leaf, every 64 leaves and every 4096
 //     leaves have the bounding box of their points over ALL d coordinates (k_leaf_boxes, k_node_boxes).  A tile
-//     descends only where a box is near enough to one of its four groups of 16 queries to improve a list there, by
+//     descends only where a box is near enough to one of its four groups of queries to improve a list there, by
 //     the same lower bound that prunes bins elsewhere; 64 boxes are tested at a time, one per lane.  There are no
 //     shells and nothing is handed over: when the descent ends, every point not looked at is strictly farther than
 //     the k-th best of every query;
@@ -15,8 +15,8 @@
 //     float32 exactly as everywhere else, and sorted into the list in registers with the networks of fg_sortnet.hpp.
 // What bounds it: vector issue, about 220 instructions per 64 x 64 pairs (40 conversion, 64 signs, 60 queueing; the four
 // matrix instructions run beside other wavefronts' vector work) and some 1300 per merge of 16 survivors a lane at 64 keys,
-// at two wavefronts per SIMD, which the list in registers allows.  Whole forward call: 500k uniform points, d = 8, K = 64
-// 21.5 -> 11.7 ms; 60k, d = 10, K = 40 7.1 -> 1.27 ms.
+// at two wavefronts per SIMD, which the list in registers allows.  Whole forward call against the tile kernel: 500k uniform
+// points, d = 8, K = 64 21.5 -> 10.0 ms; 60k, d = 10, K = 40 7.0 -> 1.31 ms.
 #pragma once
 #include "fg_query_tile.hpp"
 
@@ -50,6 +50,13 @@ static inline LeafTree leaf_tree(void* area, int32_t n)
     t.has2 = t.n1 > 64;
     t.has3 = t.n2 > 64;
     return t;
+}
+
+// |x - the coordinate of the lane below|; 0 in lane 0
+__device__ __forceinline__ float leaf_step(float x)
+{
+    const int32_t v = __float_as_int(x);
+    return fabsf(x - __int_as_float(__builtin_amdgcn_update_dpp(v, v, 0x138, 0xf, 0xf, false)));    // wave_shr:1
 }
 
 template <int D>
@@ -166,25 +173,20 @@ __device__ __forceinline__ float half_norm(const float (&c)[D])
     return 0.5f * h;
 }
 
-// maximum / minimum over each row of 16 lanes, valid in the row's last lane
-__device__ __forceinline__ int32_t row16_max_to_last(int32_t v)
+// maximum over the lanes up to and with the own one
+__device__ __forceinline__ uint32_t wave_max_below(uint32_t v)
 {
-    const int32_t id = (int32_t)0x80000000;
-    v = max(v, __builtin_amdgcn_update_dpp(id, v, 0x111, 0xf, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(id, v, 0x112, 0xf, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(id, v, 0x114, 0xf, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(id, v, 0x118, 0xf, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, 0x111, 0xf, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, 0x112, 0xf, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, 0x114, 0xf, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, 0x118, 0xf, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, 0x142, 0xa, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, 0x143, 0xc, 0xf, false));
     return v;
 }
-__device__ __forceinline__ float row16_fmax_to_last(float v)
-{
-    const int32_t id = __float_as_int(-3.4028235e38f);
-    v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x111, 0xf, 0xf, false)));
-    v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x112, 0xf, 0xf, false)));
-    v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x114, 0xf, 0xf, false)));
-    v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x118, 0xf, 0xf, false)));
-    return v;
-}
+
+// a value that is the same in all lanes, kept in a scalar register (the vector registers are what a long list is short of)
+template <bool ON> __device__ __forceinline__ float uniform_value(float v) { return ON ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))) : v; }
 
 // swaps the upper 32 lanes of a with the lower 32 lanes of b
 __device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b)
@@ -197,7 +199,7 @@ __device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b)
 template <int KC> constexpr int leaf_waves() { return KC <= 16 ? 3 : 2; }
 template <int KC, int D> constexpr size_t leaf_lds_bytes()
 {
-    const size_t scan = (size_t)kLeafQueue * kQueryBlock * 4 + (size_t)(4 * 2 * D + 2 * D * kQueryBlock + D) * 4;
+    const size_t scan = (size_t)kLeafQueue * kQueryBlock * 4 + (size_t)(kQueryBlock * box_vecs<D>() * 4 + 4 * 2 * D + D + 2 * kQueryBlock) * 4;
     const size_t out = (size_t)kQueryBlock * 4 + (size_t)KC * kDumpStride * 4;
     return scan > out ? scan : out;
 }
@@ -210,9 +212,9 @@ k_query_leaf(QueryArgs a, LeafTree tree)
     constexpr int NV = rec_vecs(D);
     constexpr int NB = box_vecs<D>();
     uint32_t* const queue = reinterpret_cast<uint32_t*>(lds64);                   // [kLeafQueue][64] sorted positions
-    float* const gbox = reinterpret_cast<float*>(queue + kLeafQueue * kQueryBlock);   // [4 groups][D minima, D maxima]
-    float* const lbox = gbox + 4 * 2 * D;                                         // [D minima, D maxima][64 leaves]
-    float* const centre = lbox + 2 * D * kQueryBlock;                             // [D] of the tile's box
+    float4* const lbox = reinterpret_cast<float4*>(queue + kLeafQueue * kQueryBlock); // [64 nodes] boxes measured last
+    float* const gbox = reinterpret_cast<float*>(lbox + kQueryBlock * NB);        // [4 groups][D minima, D maxima]
+    float* const centre = gbox + 4 * 2 * D;                                       // [D] of the tile's box
     const int lane = threadIdx.x;
     // Neighbouring tiles read the same leaves: runs of 16 tiles go to one XCD (workgroups are dealt round robin to 8)
     // so that they meet in its L2 (runs of 4 to 256: the same within 3 %; heaviest tiles first, as the tile kernel
@@ -227,16 +229,19 @@ k_query_leaf(QueryArgs a, LeafTree tree)
     }
     const int32_t cap = a.k_list;
     const int32_t p = tile * kQueryBlock + lane;
-    const bool valid = p < a.n;
-    const int32_t pp = valid ? p : a.n - 1;
+    const int32_t pp = p < a.n ? p : a.n - 1;
     float x[D];
     int32_t my_row;
     load_rec<D>(a.rec, pp, x, my_row);
+    const bool asks = !(a.dir && !dir_is_query(a.dir[my_row]));
+    const bool valid = p < a.n;
     const int32_t seg = segment_of(a.row_splits, a.n_segments, pp);
+    int32_t* const ends = reinterpret_cast<int32_t*>(centre + D);                 // [2][64] of the query's row split
     const int32_t sa = a.row_splits[seg], sb = a.row_splits[seg + 1];
+    ends[lane] = sa;
+    ends[kQueryBlock + lane] = sb;
     const int32_t pa = __builtin_amdgcn_readlane(sa, 0), pb = __builtin_amdgcn_readlane(sb, kQueryBlock - 1);
     const bool several = pa != __builtin_amdgcn_readlane(sa, kQueryBlock - 1);    // the tile spans several row splits
-    const bool asks = !(a.dir && !dir_is_query(a.dir[my_row]));
     const bool active = valid && cap > 0 && asks;
     uint64_t lower = 0;
     if (LOWER && active) {
@@ -250,22 +255,66 @@ k_query_leaf(QueryArgs a, LeafTree tree)
     int32_t cnt = 0;
 
     if (__any(active)) {
+    // The queries form four groups of consecutive ones, and boxes of points are tested against the groups' boxes.  The sorted
+    // order runs along columns of bins and jumps at their ends; a group across a jump has a box that spans all
+    // between, so the groups end at the three longest jumps (uniform points: about the columns that the tile spans).  Where
+    // no jumps stand out, within a bin, they are 16 queries each.  (Always 16 each: 1M uniform points, d = 6, K = 8 7.8 ms, now 4.8;
+    // 5000 clusters of 200 points, K = 16 2.9, now 1.45, with the tests of single queries on the upper level below.)
+    int32_t g1 = 16, g2 = 32, g3 = 48;       // first queries of groups 1, 2, 3
+    {
+        float step = 0.0f;
+#pragma unroll
+        for (int c = 0; c < D && c < FG_MAX_D_BIN; ++c) step += leaf_step(x[c]);
+        int32_t key = (__float_as_int(step) & ~63) | lane;
+        const int32_t c0 = wave_max_i32(key);
+        key = key == c0 ? 0 : key;
+        const int32_t c1 = wave_max_i32(key);
+        key = key == c1 ? 0 : key;
+        const int32_t c2 = wave_max_i32(key);
+        const float third = __int_as_float(c2 & ~63);       // (0 where the tile has but one or two steps)
+        if (c0 >= kQueryBlock && __popcll(__ballot(step * 3.0f > third)) <= 16) {
+            const int32_t l0 = c0 & 63, l1 = c1 & 63, l2 = c2 & 63;
+            g1 = min(l0, min(l1, l2));
+            g3 = max(l0, max(l1, l2));
+            g2 = l0 + l1 + l2 - g1 - g3;
+        }
+    }
     // boxes of the four groups, and the tile's
     float hext = 0.0f;         // largest half extent of the tile
     float zmax = 0.0f;         // largest coordinate of its centre
+    {
+        // maximum from the lane's group's first query up to its own: what a step of the scan brings counts if it comes from there
+        const int32_t start = lane >= g3 ? g3 : (lane >= g2 ? g2 : (lane >= g1 ? g1 : 0));
+        const bool last = lane + 1 == g1 || lane + 1 == g2 || lane + 1 == g3 || lane == kQueryBlock - 1;
+        const int32_t group = (lane >= g1) + (lane >= g2) + (lane >= g3);
+        const bool in1 = lane - 1 >= start, in2 = lane - 2 >= start, in4 = lane - 4 >= start, in8 = lane - 8 >= start;
+        const bool in_row = start < (lane & ~15), in_half = start < 32;
+        auto group_max = [&](float v) __attribute__((always_inline)) -> float {
+            const int32_t id = __float_as_int(-3.4028235e38f);
+            auto from = [&](float t, bool in) __attribute__((always_inline)) { v = in ? fmaxf(v, t) : v; };
+            from(__int_as_float(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x111, 0xf, 0xf, false)), in1);
+            from(__int_as_float(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x112, 0xf, 0xf, false)), in2);
+            from(__int_as_float(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x114, 0xf, 0xf, false)), in4);
+            from(__int_as_float(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x118, 0xf, 0xf, false)), in8);
+            from(__int_as_float(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x142, 0xa, 0xf, false)), in_row);
+            from(__int_as_float(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x143, 0xc, 0xf, false)), in_half);
+            return v;
+        };
+        auto over_groups = [&](float v) __attribute__((always_inline)) -> float {
+            const int32_t w = __float_as_int(v);
+            return fmaxf(fmaxf(__int_as_float(__builtin_amdgcn_readlane(w, g1 - 1)), __int_as_float(__builtin_amdgcn_readlane(w, g2 - 1))),
+                         fmaxf(__int_as_float(__builtin_amdgcn_readlane(w, g3 - 1)), __int_as_float(__builtin_amdgcn_readlane(w, 63))));
+        };
 #pragma unroll
-    for (int c = 0; c < D; ++c) {
-        const float mx = row16_fmax_to_last(active ? x[c] : -3.4028235e38f);
-        const float mn = -row16_fmax_to_last(active ? -x[c] : -3.4028235e38f);
-        if ((lane & 15) == 15) { gbox[(lane >> 4) * 2 * D + c] = mn; gbox[(lane >> 4) * 2 * D + D + c] = mx; }
-        const float tmx = fmaxf(fmaxf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(mx), 15)), __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mx), 31))),
-                                fmaxf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(mx), 47)), __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mx), 63))));
-        const float tmn = fminf(fminf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(mn), 15)), __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mn), 31))),
-                                fminf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(mn), 47)), __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mn), 63))));
-        const float zc = tmn * 0.5f + tmx * 0.5f;
-        if (lane == 0) centre[c] = zc;
-        hext = fmaxf(hext, fmaxf(tmx - zc, zc - tmn));
-        zmax = fmaxf(zmax, fabsf(zc));
+        for (int c = 0; c < D; ++c) {
+            const float mx = group_max(active ? x[c] : -3.4028235e38f), mn = -group_max(active ? -x[c] : -3.4028235e38f);
+            if (last) { gbox[group * 2 * D + c] = mn; gbox[group * 2 * D + D + c] = mx; }
+            const float tmx = over_groups(mx), tmn = -over_groups(-mn);
+            const float zc = tmn * 0.5f + tmx * 0.5f;
+            if (lane == 0) centre[c] = zc;
+            hext = uniform_value<(KC > 48)>(fmaxf(hext, fmaxf(tmx - zc, zc - tmn)));
+            zmax = uniform_value<(KC > 48)>(fmaxf(zmax, fabsf(zc)));
+        }
     }
     __syncthreads();
 
@@ -289,16 +338,21 @@ k_query_leaf(QueryArgs a, LeafTree tree)
     auto refresh = [&]() __attribute__((always_inline)) {
         const bool full = tau_hi < 0x7f800000u;
         const float rho = sqrtf(fmaxf(__uint_as_float(tau_hi), 1e-30f)) * 1.000031f;
-        const int32_t gm = row16_max_to_last(active ? (int32_t)tau_hi : -1);
+        // with the group's number on top the maximum up to a group's last query is the group's (the two bits this takes are
+        // rounded up)
+        const uint32_t gm = wave_max_below((uint32_t)((lane >= g1) + (lane >= g2) + (lane >= g3)) << 29 | (active ? (tau_hi >> 2) + 1 : 0u));
 #pragma unroll
-        for (int g = 0; g < 4; ++g) gtau[g] = __builtin_amdgcn_readlane(gm, 16 * g + 15);
+        for (int g = 0; g < 4; ++g) {
+            const int32_t m = __builtin_amdgcn_readlane((int32_t)gm, g == 0 ? g1 - 1 : (g == 1 ? g2 - 1 : (g == 2 ? g3 - 1 : 63))) & 0x1fffffff;
+            gtau[g] = m > 0 ? m << 2 : -1;
+        }
         const int32_t rb = wave_max_i32(active && full ? __float_as_int(rho) : 0);
         // (not finer than the spacing of floats at the centre: a lone point has no extent, and a scale without bound would
         // overflow the scaled centre)
         const float reach = fmaxf(hext + __int_as_float(rb), zmax * 5.9604645e-8f);
         int32_t se = 258 - (int32_t)(__float_as_uint(reach) >> 23);     // reach < 2^(e - 126): scale * reach < 32
         se = se > 254 ? 254 : (se < 1 ? 1 : se);
-        scale = __int_as_float(se << 23);
+        scale = uniform_value<(KC > 48)>(__int_as_float(se << 23));
         float q[D];
         float n2 = 0.0f;
 #pragma unroll
@@ -400,14 +454,12 @@ k_query_leaf(QueryArgs a, LeafTree tree)
     const int32_t own_a = tile * 2 - around, own_b = tile * 2 + 1 + around;       // inclusive
     float b2[4];
     // squared lower bounds between this lane's box and the four groups' boxes
-    auto measure = [&](const float4* __restrict__ boxes, int32_t node, bool keep) __attribute__((always_inline)) {
+    auto measure = [&](const float4* __restrict__ boxes, int32_t node) __attribute__((always_inline)) {
         float w[NB * 4];
         load_box<D>(boxes, node, w);
         asm volatile("" ::: "memory");      // the groups' boxes are read here, not kept in 8 D registers across the search
-        if (keep) {
 #pragma unroll
-            for (int c = 0; c < 2 * D; ++c) lbox[c * kQueryBlock + lane] = w[c];
-        }
+        for (int v = 0; v < NB; ++v) lbox[lane * NB + v] = make_float4(w[4 * v], w[4 * v + 1], w[4 * v + 2], w[4 * v + 3]);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             float s = 0.0f;
@@ -439,15 +491,56 @@ k_query_leaf(QueryArgs a, LeafTree tree)
     const float4* const box3 = box2 + (int64_t)tree.n2 * NB;
     const int32_t l_last = lb - 1;
     // Sweep 0 takes the tile's own leaves; sweep 1 the boxes within an eighth of the distance the lists reach after
-    // that; sweep 2 the rest, with lists that have tightened by then (500k uniform points, d = 8, K = 64: 12.2 ms; within a
-    // quarter 12.6, a half 14.9, without sweep 1 21.1; two or three rings 12.5 to 13.1).  m3, m2, m1: nodes of the
+    // that; sweep 2 the rest, with lists that have tightened by then (500k uniform points, d = 8, K = 64,
+    // with groups of 16: 12.2 ms; within a quarter 12.6, a half 14.9, without sweep 1 21.1; two or three rings 12.5 to 13.1).  m3, m2, m1: nodes of the
     // current 64 of each level still to be taken.
     int32_t sweep = 0, t3 = (l_last >> 12) + 1, first3 = 0, first2 = 0, first1 = own_a;
     uint64_t m3 = 0, m2 = 0, m1 = 0;
     for (int32_t l = own_a; l <= own_b; ++l) if (l >= la && l <= l_last) m1 |= 1ull << (l - own_a);
 #pragma unroll
     for (int g = 0; g < 4; ++g) { b2[g] = 0.0f; near_limit[g] = 0.0f; }
-    int32_t seen = 0, dropped = 0;       // leaves tested query by query, and those ruled out
+    // A group's box is often much larger than the reach of its queries (a run of the sorted order that wraps from the end
+    // of one column of bins to the next, an isolated point among close ones): the nodes that the groups let through are
+    // tested once more against every query by itself, the leaves and the nodes above (on the leaves alone, a tile at the wrap
+    // of the first dimensions tested them all, and a handful of such tiles took the kernel's time: 200k points on a lattice of
+    // 4^6, K = 16 0.98 ms, now 0.19).
+    // Of the leaves under a node every eighth is tested first; where that drops less than a third (from d = 8 on nearly every
+    // box reaches), the others are left out, and so is the next node, then the next three, seven, and so on up to 63.
+    int32_t wait = 0, pause = 0;
+    constexpr uint64_t kProbe = 0x0101010101010101ull;
+    auto each_query = [&](uint64_t m, uint64_t which) __attribute__((always_inline)) -> uint64_t {
+        __syncthreads();
+        for (uint64_t mm = which; mm;) {             // two at a time: one alone is a chain of some 450 clocks
+            int j[2];
+            j[0] = __builtin_ctzll(mm);
+            mm &= mm - 1;
+            j[1] = mm ? __builtin_ctzll(mm) : j[0];
+            mm &= mm - 1;
+            float w[2][NB * 4], s[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int v = 0; v < NB; ++v) {
+                    const float4 f = lbox[j[i] * NB + v];
+                    w[i][4 * v] = f.x; w[i][4 * v + 1] = f.y; w[i][4 * v + 2] = f.z; w[i][4 * v + 3] = f.w;
+                }
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const float gap = fmaxf(fmaxf(w[i][c] - x[c], x[c] - w[i][D + c]), 0.0f);
+                    s[i] = c == 0 ? gap * gap : s[i] + gap * gap;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const bool out = !active || (tau_hi < 0x7f800000u && s[i] > 1e-30f && __uint_as_float(tau_hi) < s[i] * kBoundShrink);
+                if (!__any(!out)) m &= ~(1ull << j[i]);
+            }
+        }
+        __syncthreads();
+        return m;
+    };
     // fills m1 with leaves to visit; false: the sweep is over
     auto advance = [&]() __attribute__((always_inline)) -> bool {
         while (!m1) {
@@ -456,46 +549,41 @@ k_query_leaf(QueryArgs a, LeafTree tree)
                 m2 &= m2 - 1;
                 const int32_t n1 = first1 + lane;
                 const bool ok = n1 >= la && n1 <= l_last && (n1 < own_a || n1 > own_b);
-                measure(box1, ok ? n1 : l_last, true);
+                measure(box1, ok ? n1 : l_last);
                 m1 = __ballot(ok && near() == (sweep == 1) && reaches());
-                // A group's box is often much larger than the reach of its queries (a run of the sorted order that
-                // wraps from the end of one column of bins to the next, an isolated point among close ones): the
-                // leaves that the groups let through are tested once more against every query by itself.
-                // Where that drops less than a third (from d = 8 on nearly every box reaches), it is left out.
-                if (seen >= 128 && dropped * 3 < seen) continue;
-                seen += __popcll(m1);
-                dropped += __popcll(m1);
-                __syncthreads();
-                for (uint64_t mm = m1; mm; mm &= mm - 1) {
-                    const int j = __builtin_ctzll(mm);
-                    float s = 0.0f;
-#pragma unroll
-                    for (int c = 0; c < D; ++c) {
-                        const float gap = fmaxf(fmaxf(lbox[c * kQueryBlock + j] - x[c], x[c] - lbox[(D + c) * kQueryBlock + j]), 0.0f);
-                        s = c == 0 ? gap * gap : s + gap * gap;
+                if (wait > 0) {
+                    --wait;
+                } else if (m1) {
+                    uint64_t which = m1 & kProbe ? m1 & kProbe : m1;
+                    for (bool probe = true;; probe = false) {
+                        const int32_t tested = __popcll(which);
+                        m1 = each_query(m1, which);
+                        if (!probe) break;
+                        const bool pays = 3 * (tested - __popcll(m1 & which)) >= tested;
+                        pause = pays ? 0 : min(2 * pause + 1, 63);
+                        which = m1 & ~which;
+                        if (!pays || !which) break;
                     }
-                    const bool out = !active || (tau_hi < 0x7f800000u && s > 1e-30f && __uint_as_float(tau_hi) < s * kBoundShrink);
-                    if (!__any(!out)) m1 &= ~(1ull << j);
+                    wait = pause;
                 }
-                dropped -= __popcll(m1);
-                __syncthreads();
             } else if (m3) {
                 first2 = (first3 + __builtin_ctzll(m3)) << 6;
                 m3 &= m3 - 1;
                 const int32_t n2 = first2 + lane;
                 bool ok = n2 >= (la >> 6) && n2 <= (l_last >> 6);
                 if (tree.has2) {
-                    measure(box2, ok ? n2 : (l_last >> 6), false);
+                    measure(box2, ok ? n2 : (l_last >> 6));
                     ok = ok && (sweep > 1 || near()) && reaches();
                 }
                 m2 = __ballot(ok);
+                if (tree.has2) m2 = each_query(m2, m2);
             } else if (t3 <= (l_last >> 12)) {
                 first3 = t3;
                 const int32_t n3 = t3 + lane;
                 t3 += 64;
                 bool ok = n3 <= (l_last >> 12);
                 if (tree.has3) {
-                    measure(box3, ok ? n3 : (l_last >> 12), false);
+                    measure(box3, ok ? n3 : (l_last >> 12));
                     ok = ok && (sweep > 1 || near()) && reaches();
                 }
                 m3 = __ballot(ok);
@@ -561,7 +649,7 @@ k_query_leaf(QueryArgs a, LeafTree tree)
                 // Only the query's own row split: where the tile spans several, and at either end (there the filter has
                 // refused what lies outside already; this keeps a position beyond the last point out of the queue by itself)
                 if (several || base < pa || base + kLeafPts > pb) {
-                    const int32_t from = sa > base ? sa - base : 0, to = sb - base < 32 ? sb - base : 32;
+                    const int32_t from = max(ends[lane] - base, 0), to = min(ends[kQueryBlock + lane] - base, 32);
                     const uint64_t range = to > from ? ((1ull << to) - 1) & ~((1ull << from) - 1) : 0ull;
                     m &= (uint32_t)range;
                 }
@@ -587,7 +675,7 @@ k_query_leaf(QueryArgs a, LeafTree tree)
             if (sweep == 1) {
 #pragma unroll
                 for (int g = 0; g < 4; ++g)
-                    near_limit[g] = gtau[g] < 0 ? -1.0f : (gtau[g] < 0x7f800000 ? __int_as_float(gtau[g]) * 0.015625f : hext * hext);
+                    near_limit[g] = uniform_value<(KC > 48)>(gtau[g] < 0 ? -1.0f : (gtau[g] < 0x7f800000 ? __int_as_float(gtau[g]) * 0.015625f : hext * hext));
             }
             t3 = la >> 12;
         }

@@ -42,6 +42,21 @@ def cloud(kind, n, d):
     return x
 
 
+# the default from six dimensions on against the tile kernel (query stage alone)
+@pytest.mark.parametrize("kind,n,d,k,bound", [
+    ("lattice", 200_000, 6, 16, 2.0),                    # tiles that wrap: 5.5, now 1.1
+    ("clusters_fine", 1_000_000, 6, 16, 1.5),            # 2.3, now 1.1
+])
+def test_leaf_kernel_against_tile_kernel(kind, n, d, k, bound):
+    x = cloud(kind, n, d).contiguous()
+    rs = torch.tensor([0, n], dtype=torch.int32, device=DEV)
+    bn = B.fg_bin_points(x, rs, k)
+    out = [(torch.empty((n, k), dtype=torch.int32, device=DEV), torch.empty((n, k), device=DEV)) for _ in range(2)]
+    t = shortest([lambda: B.fg_query_binned(bn, rs, k, *out[0]), lambda: B.fg_query_binned(bn, rs, k, *out[1], algo=4)])
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert t[0] <= bound * t[1], "%s: %.0f against %.0f us" % (kind, t[0], t[1])
+
+
 # the object-condensation matrices: M and M_not together against M alone, and against the same call with rows of M for every
 # member
 def objects(splits, size, count, sort=False):
