@@ -25,6 +25,11 @@ namespace fg {
 constexpr int kLeafPts = 32;
 constexpr int kLeafTrig = 16;                       // queued survivors of a lane that start a merge
 constexpr int kLeafQueue = kLeafTrig + kLeafPts;    // most a lane can hold: one block of 32 candidates on top of kLeafTrig - 1
+// So many merges more than blocks, and blocks are compared exactly from then on; the second where every list holds nothing but
+// copies of its query.  (Ordinary tiles take two merges a block for their own leaves, 4 to 6 blocks, and soon fewer than
+// one for two.)
+constexpr int kLeafSiftFrom = 24;
+constexpr int kLeafSiftTies = 4;
 constexpr int kLeafBigH = 60000;                    // filter value of a candidate that must not pass / a query that takes none
 constexpr int kLeafAllT = -30000;                   // query term that lets every live candidate pass
 
@@ -426,6 +431,35 @@ k_query_leaf(QueryArgs a, LeafTree tree)
         refresh();
     };
 
+    // ---- candidates that the filter does not tell apart ----
+    // The filter's grain is a 2^-10 of the tile's extent.  Where it lets through more than that sorts out (equal points, two
+    // dense clusters in one tile, an outlier's tile, far from all of which the k-th best differ by less than the grain), the
+    // merges outnumber the blocks of 32 candidates: 746 merges against 40 in other tiles, 200k points in 50 clusters of width
+    // 0.001, d = 8, K = 64.  From then on a block's survivors are compared with the k-th best, exactly and for all queries at
+    // once, before they are queued: some 900 instructions for 32, less than one merge of 16.  Those points 3.5 -> 2.3 ms; 60k
+    // points of which one in a thousand lies a thousand times as far out, d = 10, K = 64 16.1 -> 8 ms.
+    int32_t excess = 0;                          // merges less blocks
+    bool exact = false;
+    auto sift = [&](int32_t base, uint32_t m) __attribute__((always_inline)) -> uint32_t {
+        uint32_t keep = 0;
+        float w[D];                              // the candidate of the lane's number
+        int32_t from;
+        load_rec<D>(a.rec, min(base + (lane & (kLeafPts - 1)), a.n - 1), w, from);
+#pragma unroll 2
+        for (int c = 0; c < kLeafPts; ++c) {
+            float diff = x[0] - __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w[0]), c));
+            float d2 = diff * diff;
+#pragma unroll
+            for (int i = 1; i < D; ++i) {
+                diff = x[i] - __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w[i]), c));
+                d2 = d2 + diff * diff;
+            }
+            const uint64_t key = ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)__builtin_amdgcn_readlane(from, c);
+            keep |= (key < best[KC - 1] ? 1u : 0u) << c;
+        }
+        return m & keep;
+    };
+
     // ---- 64 candidates against 64 queries ----
     // matrix row r of a block of 32 carries candidate 16 * (r >> 2 & 1) + 4 * (r >> 3) + (r & 3), so that the 16 signs of
     // a lane and the 16 of its partner half are the candidates in order
@@ -653,6 +687,8 @@ k_query_leaf(QueryArgs a, LeafTree tree)
                     const uint64_t range = to > from ? ((1ull << to) - 1) & ~((1ull << from) - 1) : 0ull;
                     m &= (uint32_t)range;
                 }
+                --excess;
+                if (__builtin_expect(exact, 0)) m = sift(base, m);
                 while (m) {
                     queue[cnt * kQueryBlock + lane] = (uint32_t)(base + __builtin_ctz(m));
                     m &= m - 1;
@@ -661,7 +697,11 @@ k_query_leaf(QueryArgs a, LeafTree tree)
                 // at the end of a sweep everything queued is merged
                 const int32_t trig = last && !have ? 1 : kLeafTrig;
                 if (__any(cnt >= trig)) {
-                    do absorb(); while (__any(cnt >= trig));
+                    do {
+                        absorb();
+                        ++excess;
+                    } while (__any(cnt >= trig));
+                    exact = exact || excess > kLeafSiftFrom || (excess > kLeafSiftTies && !__any(active && tau_hi != 0));
                     m1 &= __ballot(reaches());
                 }
                 if (last) break;

@@ -46,6 +46,8 @@ def cloud(kind, n, d):
 @pytest.mark.parametrize("kind,n,d,k,bound", [
     ("lattice", 200_000, 6, 16, 2.0),                    # tiles that wrap: 5.5, now 1.1
     ("clusters_fine", 1_000_000, 6, 16, 1.5),            # 2.3, now 1.1
+    ("clusters_tight", 200_000, 8, 64, 1.6),             # tiles over two clusters: 2.0, now 1.3
+    ("outliers", 60_000, 10, 64, 0.65),                  # 0.8, now 0.48
 ])
 def test_leaf_kernel_against_tile_kernel(kind, n, d, k, bound):
     x = cloud(kind, n, d).contiguous()
