@@ -38,6 +38,7 @@ struct QueryArgs {
     int32_t defer_lanes;       // tile kernel: go on past shell 1 only while more lanes than this are unfinished
     // of some kernels only, and last: the fields above keep their places in the other kernels' arguments
     int32_t dense_class;       // > 0: tiles of this work class and above are the leaf kernel's, the others the tile kernel's
+    int32_t few_ask;           // leaf kernel: tiles of which no more queries than this ask (direction flags) are handed over
     const float* coords;       // [n][d] the points in their original order: given (and rec not) where nothing was binned, else nullptr
 };
 

@@ -233,6 +233,18 @@ static void allow_lds(K kernel, size_t bytes)
 constexpr int32_t kDenseClass = 18;
 constexpr int32_t kDenseMinN = 1 << 22;
 
+// The queries handed over by the tile (or leaf) kernel: their work list, then the list kernel.
+template <int D, int DB, bool COUNT>
+static void launch_handed(const QueryArgs& a, hipStream_t stream)
+{
+    const int grid = (a.n + kQueryBlock - 1) / kQueryBlock;
+    hipLaunchKernelGGL(k_list_compact, dim3((grid + 1023) / 1024), dim3(1024), 0, stream, a.handed, grid, a.work_list, a.work_count);
+    // one query per wavefront; four times the wave slots of the chip: the queries differ widely in cost, and with
+    // more, shorter workgroups the hardware dispatcher evens them out (cursors in memory cost more than they gained)
+    const int list_grid = a.n < 32768 ? a.n : 32768;
+    hipLaunchKernelGGL((k_query_list_wave<D, DB, COUNT>), dim3(list_grid), dim3(kQueryBlock), 0, stream, a);
+}
+
 // One pass of the fast path: tile kernel + list kernel for a.k_list <= 64 neighbours per query.
 template <int D, int DB, bool COUNT, bool LOWER>
 static void launch_query_pass(const QueryArgs& a_in, hipStream_t stream)
@@ -268,13 +280,8 @@ static void launch_query_pass(const QueryArgs& a_in, hipStream_t stream)
         const size_t lds = tile_sorted_lds_bytes<64, D>();
         hipLaunchKernelGGL((k_query_tile_sorted<D, DB, 64, COUNT, LOWER>), dim3(grid), dim3(kQueryBlock), lds, stream, a);
     }
-    hipLaunchKernelGGL(k_list_compact, dim3((grid + 1023) / 1024), dim3(1024), 0, stream, a.handed, grid, a.work_list, a.work_count);
-    // one query per wavefront; four times the wave slots of the chip: the queries differ widely in cost, and with
-    // more, shorter workgroups the hardware dispatcher evens them out (cursors in memory cost more than they gained)
-    const int list_grid = a.n < 32768 ? a.n : 32768;
-    hipLaunchKernelGGL((k_query_list_wave<D, DB, COUNT>), dim3(list_grid), dim3(kQueryBlock), 0, stream, a);
+    launch_handed<D, DB, COUNT>(a, stream);
 }
-
 // From this many dimensions on the leaf kernel is the default.  Query stage, tile + list kernel against leaf kernel:
 //   200k uniform points, d = 6, K = 40      3.69 against  2.32 ms     1M the same                     13.0 against 11.5 ms
 //   400k, d = 6, K = 10                     3.68 against  2.92 ms     400k, d = 7, K = 16              6.2 against  6.1 ms
@@ -313,10 +320,12 @@ static hipError_t launch_query_impl(const QueryArgs& a_in, hipStream_t stream)
         }
         if (a.algo == 3 || (a.algo == 0 && D >= kLeafMinD)) {
             launch_leaf_pass<D, false>(a, stream);
+            if (a.dir) launch_handed<D, DB, false>(a, stream);
             if (cap > 64) {
                 a.slot0 = 64;
                 a.k_list = cap - 64;
                 launch_leaf_pass<D, true>(a, stream);
+                if (a.dir) launch_handed<D, DB, false>(a, stream);
             }
             return hipGetLastError();
         }

@@ -247,7 +247,23 @@ k_query_leaf(QueryArgs a, LeafTree tree)
     ends[kQueryBlock + lane] = sb;
     const int32_t pa = __builtin_amdgcn_readlane(sa, 0), pb = __builtin_amdgcn_readlane(sb, kQueryBlock - 1);
     const bool several = pa != __builtin_amdgcn_readlane(sa, kQueryBlock - 1);    // the tile spans several row splits
-    const bool active = valid && cap > 0 && asks;
+    // Where few queries ask they are handed to the list kernel, which gives each a wavefront, before any search.  Eight
+    // neighbouring tiles decide together: one tile of many may have few by chance, or be the last, and would have the call wait
+    // for its queries alone (d = 10: 0.17 ms).
+    uint64_t few = 0;
+    if (a.dir && a.dense_class == 0) {
+        int32_t points = 0, ask = 0;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const int64_t pos = (int64_t)((tile & ~7) + b) * kQueryBlock + lane;
+            const bool in = pos < a.n;
+            points += __popcll(__ballot(in));
+            ask += __popcll(__ballot(in && dir_is_query(a.dir[rec_row<D>(a.rec, in ? pos : 0)])));
+        }
+        if (cap > 0 && ask * kQueryBlock <= a.few_ask * points) few = __ballot(valid && asks);
+        if (lane == 0) a.handed[tile] = few;
+    }
+    const bool active = valid && cap > 0 && asks && few == 0;
     uint64_t lower = 0;
     if (LOWER && active) {
         const int32_t li = a.out_idx[(int64_t)my_row * a.k + a.slot0];
@@ -722,15 +738,30 @@ k_query_leaf(QueryArgs a, LeafTree tree)
     }
     }   // any query searches
 
-    write_tile_rows<KC>(a, best, lds64, my_row, valid, asks, cap, 0ull, 0u);
+    write_tile_rows<KC>(a, best, lds64, my_row, valid, asks, cap, few, 0u);
+}
+
+// With direction flags: tiles of which no more queries than this ask hand them to the list kernel.  A tile costs nearly the same
+// however few of its queries ask; the list kernel costs so much a query, which grows with the points around it from d = 8
+// on.  One uniform split, a tile's cost over a query's: d = 6, 50k to 1M points 30 to 38; d = 8, 50k 35 to 41, 200k 16
+// (K = 64) and 20 (K = 16), 1M 6 to 9; d = 10, 50k 20 to 28.  One in ten asking: 200k points, d = 6, K = 64 2.05 -> 0.42 ms
+// (tile kernel 1.15); 1M, d = 6, K = 16 8.3 -> 1.5 (2.5); 50k, d = 10, K = 40 1.15 -> 0.62 (2.0).  Half of them asking, d = 6,
+// the tile kernel would be the faster one (1M, K = 16 5.4 against 7.6 ms; d = 8 45 against 17), but the share is
+// known on the device only.
+static inline int32_t leaf_few_ask(int32_t d, int32_t n, int32_t n_segments, int32_t k_list)
+{
+    const int32_t split = n / n_segments;
+    if (d <= 7) return 32;
+    return split <= 1 << 16 ? 24 : (split <= 1 << 18 ? (k_list > 32 ? 12 : 16) : 6);
 }
 
 template <int D, bool LOWER>
-static void launch_leaf_pass(const QueryArgs& a, hipStream_t stream)
+static void launch_leaf_pass(const QueryArgs& a_in, hipStream_t stream)
 {
+    QueryArgs a = a_in;
     const LeafTree t = leaf_tree(a.work_list, a.n);
     const int grid = (a.n + kQueryBlock - 1) / kQueryBlock;
-    if (!LOWER || a.dense_class > 0) {       // the second pass of a long list finds the boxes of the first
+    if (!LOWER || a.dense_class > 0 || a.dir) {       // the second pass of a long list finds the boxes of the first, unless the work list took their place
         constexpr int NB = box_vecs<D>();
         hipLaunchKernelGGL(k_leaf_boxes<D>, dim3((a.n + 255) / 256), dim3(256), 0, stream, a, t.boxes);
         float4* const box2 = t.boxes + (int64_t)t.n1 * NB;
@@ -738,6 +769,7 @@ static void launch_leaf_pass(const QueryArgs& a, hipStream_t stream)
         if (t.has3) hipLaunchKernelGGL(k_node_boxes<D>, dim3((t.n3 + 3) / 4), dim3(256), 0, stream, box2, t.n2, box2 + (int64_t)t.n2 * NB, t.n3);
     }
     const int32_t cap = a.k_list;
+    a.few_ask = leaf_few_ask(D, a.n, a.n_segments, a.k_list);
 #define FG_LEAF(KC) hipLaunchKernelGGL((k_query_leaf<D, KC, LOWER>), dim3(grid), dim3(kQueryBlock), (leaf_lds_bytes<KC, D>()), stream, a, t)
     if (cap <= 16) FG_LEAF(16);
     else if (cap <= 32) FG_LEAF(32);
