@@ -59,9 +59,10 @@ __device__ __forceinline__ float wave_max(float v)
 // One block per chunk of kBboxChunk consecutive points.  A chunk that lies inside one row split
 // (the common case) is reduced in registers, then across the wave, then across the block, and
 // issues one atomic pair per dimension; a chunk straddling a split boundary falls back to
-// one pair per wavefront, split and dimension.  Same-address atomics serialise, so their number matters.
+// one pair per wavefront, split and dimension, or per lane.  Same-address atomics serialise, so their number matters.
 constexpr int kBboxItems = 4;     // few points per thread: the launch needs well over 256 blocks to keep loads in flight
 constexpr int kBboxChunk = kBlock * kBboxItems;
+constexpr int kBboxSplits = 24;   // more row splits than this in a wavefront's 64 points: atomics per lane
 
 template <int DB>
 __global__ void __launch_bounds__(kBlock)
@@ -116,8 +117,21 @@ k_bbox(const float* __restrict__ coords, const int32_t* __restrict__ row_splits,
         float x[DB];
 #pragma unroll
         for (int c = 0; c < DB; ++c) x[c] = p[c];
-        // One reduction and one atomic pair per row split and dimension the wavefront meets.  (One pair per lane, where
-        // it meets more than one: 20k points in 48 splits 29 us, the atomics of a split queueing in its lines; now 15 us.)
+        // Many row splits in the wavefront: their atomics hardly meet, and one pair per lane is the faster way (fg_bin_points of
+        // 500k splits of one point, d = 3: 425 us reduced, 255 this way; of two points the same; of five, 13 splits a
+        // wavefront, 210 against 335).
+        const int32_t below = __shfl_up(s, 1, 64);
+        if (__popcll(__ballot((threadIdx.x & 63) > 0 && s != below)) > kBboxSplits) {
+            if (!live) continue;
+#pragma unroll
+            for (int c = 0; c < DB; ++c) {
+                atomicMin(&kmin[(s * DB + c) * kKeyStride], float_to_key(x[c]));
+                atomicMax(&kmax[(s * DB + c) * kKeyStride], float_to_key(x[c]));
+            }
+            continue;
+        }
+        // else one reduction and one atomic pair per row split and dimension the wavefront meets.  (One pair per lane: 20k
+        // points in 48 splits 29 us, the atomics of a split queueing in its lines; now 15 us.)
         for (uint64_t left = ~0ull; left;) {
             const int32_t cur = __shfl(s, __ffsll((unsigned long long)left) - 1, 64);
             const bool in = s == cur;

@@ -108,3 +108,13 @@ def test_rows_of_others(splits, size, count, sort, clip, bound):
     call = lambda rows, others: lambda: B.fg_oc_helper(*arrays, rows, size, others, 1, M[:rows], M_not, ws)
     t = shortest([call(median if clip else most, True), call(most, clip)])
     assert t[0] <= bound * t[1], "%.0f against %.0f us" % (t[0], t[1])
+
+
+# row splits of one point, as many bounding boxes as points, against splits of five (2.9 times as long, now 1.7)
+def test_bounding_boxes_of_tiny_splits():
+    x = cloud("uniform", 500_000, 3)
+    one = torch.arange(500_001, dtype=torch.int32, device=DEV)
+    five = torch.arange(0, 500_001, 5, dtype=torch.int32, device=DEV)
+    ws = torch.empty(max(B.fg_workspace_size(500_000, 3, s, 8) for s in (500_000, 100_000)), dtype=torch.uint8, device=DEV)
+    t = shortest([lambda: B.fg_bin_points(x, one, 8, workspace=ws), lambda: B.fg_bin_points(x, five, 8, workspace=ws)])
+    assert t[0] <= 2.3 * t[1], "%.0f against %.0f us" % (t[0], t[1])
