@@ -99,9 +99,9 @@ typedef struct {
                                   depend on it) */
     int32_t record_floats;     /* floats per record of sorted_points: d + 1 rounded up to a multiple of 4 */
     void* scratch;             /* opaque: scratch of the query stage inside the workspace.  Its first int32 holds, after
-                                  fg_query_binned, the number of queries the tile kernel handed to the list kernel, 0 where
-                                  another kernel served the call (a diagnostic; nothing else in it is meant
-                                  to be read) */
+                                  fg_query_binned, the number of queries handed to the list kernel: by the tile kernel,
+                                  or, with direction flags, by the leaf kernel where few points ask (a diagnostic; nothing
+                                  else in it is meant to be read) */
 } fg_binning;
 
 /* Options of the query stage; none changes the result.  A NULL pointer means all defaults. */
@@ -116,8 +116,8 @@ typedef struct {
                                   kernel + list kernel.  Calls that count candidates take 3 as 4 */
     int32_t defer_lanes;       /* after shell 1 a wavefront of the tile kernel goes on to the next shell only while
                                   more than this many of its 64 queries are unfinished, the rest go to the list
-                                  kernel; 0..64, negative: the default (64 for d <= 5, 6 beyond).  With algo 0 a value
-                                  that is not negative asks for the tile kernel */
+                                  kernel; 0..64, negative: the default (64 for d <= 5, 6 beyond).  Without effect where
+                                  another kernel serves the call */
 } fg_query_options;
 
 /* Spatial partition + counting sort (Section 3, second paragraph: bins per row split, points ordered by bin,

@@ -325,7 +325,6 @@ fg_status fg_query_binned(const fg_binning* view, const int32_t* row_splits, int
     a.bin_idx = view->bin_idx; a.tile_order = (int32_t*)(sc + S.tile_order);
     a.algo = (options && (options->algo >= 1 && options->algo <= 4)) ? options->algo : 0;
     a.defer_lanes = defer > 64 ? 64 : defer;
-    if (a.algo == 0 && options && options->defer_lanes >= 0) a.algo = 4;      // a hand-over rule is one of the tile kernel
     hipError_t e = launch_query(a, d, view->d_bin, (hipStream_t)stream);
     return e == hipSuccess ? FG_OK : FG_ERR_LAUNCH;
 }

@@ -93,3 +93,20 @@ def test_dense_tiles_of_two_dimensions(k):
     rows = np.unique(np.concatenate([near, rng.choice(n, size=40, replace=False)])).astype(np.int64)
     oi, od = oracle.knn_rows(x, rs, k, rows)
     assert np.array_equal(a[0][rows], oi) and np.array_equal(a[1][rows], od.view(np.uint32))
+
+
+# options filled with zeros, or with a hand-over rule alone, choose no kernel: the default serves the call and the tile
+# kernel's rule has no effect (the scratch block counts the queries that the tile kernel hands over)
+@pytest.mark.parametrize("n,d", [(2000, 3), (5000, 6)])
+@pytest.mark.parametrize("defer_lanes", [0, 64])
+def test_a_hand_over_rule_chooses_no_kernel(n, d, defer_lanes):
+    x, rs = W.uniform(n, d, seed=5)
+    xt, rt = torch.from_numpy(x).to(DEV), torch.from_numpy(rs).to(DEV)
+    bn = B.fg_bin_points(xt, rt, 10)
+    B.fg_query_binned(bn, rt, 10, algo=4, defer_lanes=64)
+    handed = int(bn.work_count.item())
+    idx, d2 = B.fg_query_binned(bn, rt, 10, defer_lanes=defer_lanes)
+    torch.cuda.synchronize()
+    assert handed > 0 and int(bn.work_count.item()) == 0
+    oi, od = oracle.knn(x, rs, 10)
+    assert np.array_equal(idx.cpu().numpy(), oi) and np.array_equal(d2.cpu().numpy().view(np.uint32), od.view(np.uint32))
