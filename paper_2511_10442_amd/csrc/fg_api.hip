@@ -77,7 +77,7 @@ ScratchLayout scratch_layout(int64_t n)
 {
     ScratchLayout S;
     size_t off = 0;
-    S.work_count = off; off = align_up(off + sizeof(int32_t));
+    S.work_count = off; off = align_up(off + 2 * sizeof(int32_t));
     S.work_list = off;  off = align_up(off + sizeof(int32_t) * (size_t)n);
     S.tile_order = off; off = align_up(off + sizeof(int32_t) * (size_t)(2 * ((n + 63) / 64) + 128));
     S.rank = off;       off = align_up(off + sizeof(int32_t) * (size_t)n);

@@ -21,7 +21,7 @@ struct QueryArgs {
     float* out_d2;             // [n][k]
     int32_t* out_cand;         // [n] or nullptr
     int32_t* work_list;        // [n] sorted positions of queries deferred by the tile kernel, in bin order
-    int32_t* work_count;       // [1]
+    int32_t* work_count;       // [2] queries on the work list; dense tiles (see dense_class)
     uint64_t* handed;          // [ceil(n/64)] per tile: which of its 64 queries the tile kernel hands over
     const int32_t* bin_idx;    // [n] flat bin of each point, original row order
     int32_t* tile_order;       // [2*ceil(n/64) + 128]: tile order, tile classes, class histogram, class cursors

@@ -192,7 +192,8 @@ static __global__ void __launch_bounds__(256) k_tile_work(QueryArgs a, int32_t n
 // Position of every tile: classes in descending order; inside a class roughly the bin order (blocks of 256
 // consecutive tiles reserve their places with one atomic per class, and a block's tiles keep the order in which
 // its waves arrive), so that tiles running at the same time still share their neighbourhoods in the L2 cache.
-static __global__ void __launch_bounds__(256) k_tile_rank(int32_t* __restrict__ order, int32_t n_tiles)
+static __global__ void __launch_bounds__(256) k_tile_rank(int32_t* __restrict__ order, int32_t n_tiles, int32_t dense_class,
+                                                          int32_t* __restrict__ n_dense /* tiles of that class and above, nullptr: not asked */)
 {
     __shared__ int32_t local[kTileClasses];   // this block's tiles per class, then the block's first position in the class
     __shared__ int32_t first[kTileClasses];   // position of the class's first tile: all heavier classes before it
@@ -201,6 +202,7 @@ static __global__ void __launch_bounds__(256) k_tile_rank(int32_t* __restrict__ 
         int32_t s = 0;
         for (int c = threadIdx.x + 1; c < kTileClasses; ++c) s += order[2 * n_tiles + c];
         first[threadIdx.x] = s;
+        if (n_dense && blockIdx.x == 0 && (int32_t)threadIdx.x == dense_class) *n_dense = s + order[2 * n_tiles + dense_class];
     }
     __syncthreads();
     const int32_t t = blockIdx.x * 256 + threadIdx.x;
@@ -225,13 +227,21 @@ static void allow_lds(K kernel, size_t bytes)
 }
 
 // Two dimensions, many points: tiles whose queries meet 2000 candidates and more in their first shells (class 18: 512 passes
-// of four) lie in bins that hold far more than their share, and go to the leaf kernel, which sifts such numbers four to
-// five times faster than the tile kernel scans them; its boxes prune little there (inside a bin the points are in no
-// order).  5M points of strongly skewed density, K = 16: query stage 15.8 -> 11.1 ms (classes 16 to 22: 11.1 to 11.5).
-// On uniform points no tile qualifies and the extra launches cost some 14 us: 2M points 282 against 296 us, 5M points
-// the same, so the line lies where that is below a hundredth.
+// of four) lie in bins that hold far more than their share, and go to the leaf kernel, which sifts such numbers several
+// times faster than the tile kernel scans them; its boxes prune little there (inside a bin the points are in no
+// order).  Bins are made for K points, so the class rises with K (two classes are a factor of two).  Query stage, skewed
+// density, tile kernel against both, in ms: 5M points, K = 16 15.8 against 11.1 (classes 16 to 22: 11.1 to 11.5); 1M, K = 8 6.3
+// against 3.4, K = 16 10.7 against 4.5; 2M, K = 16 11.5 against 9.3; 200k, K = 16 2.5 against 1.1.
+// Where no tile qualifies the four launches cost some 10 us from 1M points on (6 at 200k): of a whole call on uniform
+// points 3 % at 1M and 1 % at 4M, so the line lies at 2^20.
 constexpr int32_t kDenseClass = 18;
-constexpr int32_t kDenseMinN = 1 << 22;
+constexpr int32_t kDenseMinN = 1 << 20;
+static inline int32_t dense_class_for(int32_t k_list)
+{
+    int32_t c = kDenseClass;
+    for (float k = 19.0f; k < (float)(k_list + 1); k *= 1.4142136f) ++c;       // 16 neighbours and what rounds to them: class 18
+    return c;
+}
 
 // The queries handed over by the tile (or leaf) kernel: their work list, then the list kernel.
 template <int D, int DB, bool COUNT>
@@ -256,15 +266,14 @@ static void launch_query_pass(const QueryArgs& a_in, hipStream_t stream)
                        ordered ? a.tile_order + 2 * grid : nullptr);
     if (ordered) {
         hipLaunchKernelGGL(k_tile_work<DB>, dim3((grid + 4 * kTilesPerWave - 1) / (4 * kTilesPerWave)), dim3(256), 0, stream, a, grid);
-        hipLaunchKernelGGL(k_tile_rank, dim3((grid + 255) / 256), dim3(256), 0, stream, a.tile_order, grid);
+        if (D == 2 && !COUNT && a.algo == 0 && a.n > kDenseMinN) a.dense_class = dense_class_for(a.k_list);
+        hipLaunchKernelGGL(k_tile_rank, dim3((grid + 255) / 256), dim3(256), 0, stream, a.tile_order, grid, a.dense_class,
+                           a.dense_class > 0 ? a.work_count + 1 : nullptr);
     } else {
         a.tile_order = nullptr;
     }
     if constexpr (D == 2 && !COUNT) {
-        if (ordered && a.algo == 0 && a.n > kDenseMinN) {
-            a.dense_class = kDenseClass;
-            launch_leaf_pass<D, LOWER>(a, stream);
-        }
+        if (a.dense_class > 0) launch_leaf_pass<D, LOWER>(a, stream);
     }
     const int32_t cap = a.k_list;
     if (cap <= 16) {
@@ -282,6 +291,7 @@ static void launch_query_pass(const QueryArgs& a_in, hipStream_t stream)
     }
     launch_handed<D, DB, COUNT>(a, stream);
 }
+
 // From this many dimensions on the leaf kernel is the default.  Query stage, tile + list kernel against leaf kernel:
 //   200k uniform points, d = 6, K = 40      3.69 against  2.32 ms     1M the same                     13.0 against 11.5 ms
 //   400k, d = 6, K = 10                     3.68 against  2.92 ms     400k, d = 7, K = 16              6.2 against  6.1 ms

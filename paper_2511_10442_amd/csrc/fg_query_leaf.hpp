@@ -23,6 +23,8 @@
 namespace fg {
 
 constexpr int kLeafPts = 32;
+constexpr int kDenseGrid = 16384;                   // most workgroups where only dense tiles are searched: there may be none (5M skewed
+                                                    // points 13.5 ms with 8192, 13.3 with 32768; no dense tile among 4M: 8 and 16 us)
 constexpr int kLeafTrig = 16;                       // queued survivors of a lane that start a merge
 constexpr int kLeafQueue = kLeafTrig + kLeafPts;    // most a lane can hold: one block of 32 candidates on top of kLeafTrig - 1
 // So many merges more than blocks, and blocks are compared exactly from then on; the second where every list holds nothing but
@@ -71,7 +73,8 @@ static __global__ void __launch_bounds__(256) k_leaf_boxes(QueryArgs a, float4* 
     const int32_t n = a.n;
     if (a.dense_class > 0 && dense_tiles(a) == 0) return;
     if (a.dense_class == 0 && blockIdx.x == 0 && threadIdx.x == 0) *a.work_count = 0;        // nothing is handed over on this path
-    const int32_t p = blockIdx.x * 256 + threadIdx.x;
+    for (int64_t p0 = (int64_t)blockIdx.x * 256; p0 < n; p0 += (int64_t)gridDim.x * 256) {
+    const int32_t p = (int32_t)p0 + threadIdx.x;
     float x[D];
     int32_t row;
     load_rec<D>(rec, p < n ? p : n - 1, x, row);                     // past the end: the last point once more
@@ -93,6 +96,7 @@ static __global__ void __launch_bounds__(256) k_leaf_boxes(QueryArgs a, float4* 
         for (int v = 0; v < box_vecs<D>(); ++v)
             boxes[(int64_t)(p / kLeafPts) * box_vecs<D>() + v] = make_float4(w[4 * v], w[4 * v + 1], w[4 * v + 2], w[4 * v + 3]);
     }
+    }
 }
 
 template <int D>
@@ -107,9 +111,10 @@ __device__ __forceinline__ void load_box(const float4* __restrict__ boxes, int32
 
 // box of 64 nodes of the level below, one wavefront each
 template <int D>
-static __global__ void __launch_bounds__(256) k_node_boxes(const float4* __restrict__ below, int32_t n_below, float4* __restrict__ boxes,
+static __global__ void __launch_bounds__(256) k_node_boxes(QueryArgs a, const float4* __restrict__ below, int32_t n_below, float4* __restrict__ boxes,
                                                            int32_t n_nodes)
 {
+    if (a.dense_class > 0 && dense_tiles(a) == 0) return;
     const int32_t node = blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (node >= n_nodes) return;
@@ -210,10 +215,8 @@ template <int KC, int D> constexpr size_t leaf_lds_bytes()
 }
 
 template <int D, int KC, bool LOWER>
-__global__ void __launch_bounds__(kQueryBlock) __attribute__((amdgpu_waves_per_eu(leaf_waves<KC>(), leaf_waves<KC>())))
-k_query_leaf(QueryArgs a, LeafTree tree)
+__device__ __forceinline__ void leaf_tile(const QueryArgs& a, const LeafTree& tree, const int32_t tile, uint64_t* lds64)
 {
-    extern __shared__ uint64_t lds64[];
     constexpr int NV = rec_vecs(D);
     constexpr int NB = box_vecs<D>();
     uint32_t* const queue = reinterpret_cast<uint32_t*>(lds64);                   // [kLeafQueue][64] sorted positions
@@ -221,17 +224,6 @@ k_query_leaf(QueryArgs a, LeafTree tree)
     float* const gbox = reinterpret_cast<float*>(lbox + kQueryBlock * NB);        // [4 groups][D minima, D maxima]
     float* const centre = gbox + 4 * 2 * D;                                       // [D] of the tile's box
     const int lane = threadIdx.x;
-    // Neighbouring tiles read the same leaves: runs of 16 tiles go to one XCD (workgroups are dealt round robin to 8)
-    // so that they meet in its L2 (runs of 4 to 256: the same within 3 %; heaviest tiles first, as the tile kernel
-    // takes them: 500k uniform points, d = 8, K = 64 17.4 against 15.3 ms).
-    int32_t tile = blockIdx.x;
-    if (a.dense_class > 0) {                 // only the heaviest tiles, in the order of the ranking kernels
-        if (tile >= dense_tiles(a)) return;
-        tile = a.tile_order[tile] & ((1 << kOrderFlagBit) - 1);
-    } else if (tile < (int32_t)(gridDim.x & ~127u)) {
-        const int32_t xcd = tile & 7, j = tile >> 3;
-        tile = ((j >> 4) * 8 + xcd) * 16 + (j & 15);
-    }
     const int32_t cap = a.k_list;
     const int32_t p = tile * kQueryBlock + lane;
     const int32_t pp = p < a.n ? p : a.n - 1;
@@ -741,6 +733,33 @@ k_query_leaf(QueryArgs a, LeafTree tree)
     write_tile_rows<KC>(a, best, lds64, my_row, valid, asks, cap, few, 0u);
 }
 
+template <int D, int KC, bool LOWER>
+__global__ void __launch_bounds__(kQueryBlock) __attribute__((amdgpu_waves_per_eu(leaf_waves<KC>(), leaf_waves<KC>())))
+k_query_leaf(QueryArgs a, LeafTree tree)
+{
+    extern __shared__ uint64_t lds64[];
+    const bool dense = D == 2 && a.dense_class > 0;      // only the heaviest tiles, in the order of the ranking kernels
+    const int32_t count = dense ? dense_tiles(a) : 0;
+    int32_t i = blockIdx.x;
+    if (dense && i >= count) return;
+    do {
+        int32_t tile = i;
+        if (dense) {
+            tile = a.tile_order[i] & ((1 << kOrderFlagBit) - 1);
+        } else if (tile < (int32_t)(gridDim.x & ~127u)) {
+            // Neighbouring tiles read the same leaves: runs of 16 tiles go to one XCD (workgroups are dealt round robin to 8)
+            // so that they meet in its L2 (runs of 4 to 256: the same within 3 %; heaviest tiles first, as the tile
+            // kernel takes them: 500k uniform points, d = 8, K = 64 17.4 against 15.3 ms).
+            const int32_t xcd = tile & 7, j = tile >> 3;
+            tile = ((j >> 4) * 8 + xcd) * 16 + (j & 15);
+        }
+        leaf_tile<D, KC, LOWER>(a, tree, tile, lds64);
+        if (!dense) break;
+        __syncthreads();
+        i += gridDim.x;
+    } while (i < count);
+}
+
 // With direction flags: tiles of which no more queries than this ask hand them to the list kernel.  A tile costs nearly the same
 // however few of its queries ask; the list kernel costs so much a query, which grows with the points around it from d = 8
 // on.  One uniform split, a tile's cost over a query's: d = 6, 50k to 1M points 30 to 38; d = 8, 50k 35 to 41, 200k 16
@@ -760,13 +779,15 @@ static void launch_leaf_pass(const QueryArgs& a_in, hipStream_t stream)
 {
     QueryArgs a = a_in;
     const LeafTree t = leaf_tree(a.work_list, a.n);
-    const int grid = (a.n + kQueryBlock - 1) / kQueryBlock;
+    int grid = (a.n + kQueryBlock - 1) / kQueryBlock;
+    if (a.dense_class > 0 && grid > kDenseGrid) grid = kDenseGrid;      // its workgroups take further tiles
     if (!LOWER || a.dense_class > 0 || a.dir) {       // the second pass of a long list finds the boxes of the first, unless the work list took their place
         constexpr int NB = box_vecs<D>();
-        hipLaunchKernelGGL(k_leaf_boxes<D>, dim3((a.n + 255) / 256), dim3(256), 0, stream, a, t.boxes);
+        const int box_grid = (a.n + 255) / 256;
+        hipLaunchKernelGGL(k_leaf_boxes<D>, dim3(a.dense_class > 0 && box_grid > kDenseGrid ? kDenseGrid : box_grid), dim3(256), 0, stream, a, t.boxes);
         float4* const box2 = t.boxes + (int64_t)t.n1 * NB;
-        if (t.has2) hipLaunchKernelGGL(k_node_boxes<D>, dim3((t.n2 + 3) / 4), dim3(256), 0, stream, t.boxes, t.n1, box2, t.n2);
-        if (t.has3) hipLaunchKernelGGL(k_node_boxes<D>, dim3((t.n3 + 3) / 4), dim3(256), 0, stream, box2, t.n2, box2 + (int64_t)t.n2 * NB, t.n3);
+        if (t.has2) hipLaunchKernelGGL(k_node_boxes<D>, dim3((t.n2 + 3) / 4), dim3(256), 0, stream, a, t.boxes, t.n1, box2, t.n2);
+        if (t.has3) hipLaunchKernelGGL(k_node_boxes<D>, dim3((t.n3 + 3) / 4), dim3(256), 0, stream, a, box2, t.n2, box2 + (int64_t)t.n2 * NB, t.n3);
     }
     const int32_t cap = a.k_list;
     a.few_ask = leaf_few_ask(D, a.n, a.n_segments, a.k_list);

@@ -581,13 +581,9 @@ __device__ __forceinline__ void tile_body(const QueryArgs& a, const int32_t tile
     write_tile_rows<KC>(a, best, lds64, my_row, valid, asks, cap, mask, (uint32_t)(R + 1));
 }
 
-// Tiles of class a.dense_class and above, which are the first of the order: summed from the classes' histogram.
-__device__ __forceinline__ int32_t dense_tiles(const QueryArgs& a)
-{
-    const int32_t* const hist = a.tile_order + 2 * ((a.n + kQueryBlock - 1) / kQueryBlock);
-    const int lane = threadIdx.x & (kQueryBlock - 1);
-    return wave_sum_i32(lane >= a.dense_class ? hist[lane] : 0);      // one lane per class
-}
+// Tiles of class a.dense_class and above, which are the first of the order: counted by k_tile_rank, in the word after the
+// hand-over counter.
+__device__ __forceinline__ int32_t dense_tiles(const QueryArgs& a) { return a.work_count[1]; }
 
 // The kernel: one workgroup of one wavefront per tile.  Tiles the ordering kernels marked as uneven take the
 // flattened scan, all others, and every tile of an unordered launch, the direct one.  One kernel with a branch,

@@ -59,6 +59,25 @@ def test_leaf_kernel_against_tile_kernel(kind, n, d, k, bound):
     assert t[0] <= bound * t[1], "%s: %.0f against %.0f us" % (kind, t[0], t[1])
 
 
+# two dimensions, a million points of strongly varying density: dense tiles by the leaf kernel against the tile kernel alone
+# (1.0 while the choice began at four million points, now 0.5)
+def test_dense_tiles_below_four_million_points():
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(17)
+    n, k = 1_200_000, 16
+    rand = lambda *shape: torch.rand(*shape, generator=gen, device=DEV, dtype=torch.float64)
+    r, phi = rand(n) ** 3, rand(n) * 6.283185307179586
+    hot = (rand(1000, 2) * 2.0 - 1.0)[torch.randint(0, 1000, (n,), generator=gen, device=DEV)]
+    hot = hot + 1e-3 * torch.randn(n, 2, generator=gen, device=DEV, dtype=torch.float64)
+    x = torch.where(rand(n, 1) < 0.4, hot, torch.stack([r * torch.cos(phi), r * torch.sin(phi)], dim=1)).float().contiguous()
+    rs = torch.tensor([0, n], dtype=torch.int32, device=DEV)
+    bn = B.fg_bin_points(x, rs, k)
+    out = [(torch.empty((n, k), dtype=torch.int32, device=DEV), torch.empty((n, k), device=DEV)) for _ in range(2)]
+    t = shortest([lambda: B.fg_query_binned(bn, rs, k, *out[0]), lambda: B.fg_query_binned(bn, rs, k, *out[1], algo=4)])
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert t[0] <= 0.85 * t[1], "%.0f against %.0f us" % (t[0], t[1])
+
+
 # with direction flags and one point in ten asking, the same
 @pytest.mark.parametrize("n,d,k", [(200_000, 6, 64), (200_000, 8, 16)])
 def test_few_points_ask(n, d, k):
