@@ -10,7 +10,7 @@ from hypothesis import given, settings, HealthCheck, strategies as st
 import oracle
 from paper_2511_10442_amd import binding as B
 from paper_2511_10442_amd import workloads as W
-from test_gpu_parity import assert_exact, grad_close, gpu_knn
+from test_gpu_parity import assert_exact, grad_close, gpu_knn, gpu_knn_kernel
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -38,15 +38,16 @@ def points(kind, n, d, seed, sizes):
 @given(d=st.integers(2, 10), k=st.one_of(st.integers(1, 70), st.sampled_from([16, 32, 48, 64, 65, 128])),
        sizes=sizes_st, kind=st.sampled_from(["uniform", "shifted", "quantised", "duplicates", "flat"]),
        grid=st.sampled_from([(0, 0), (0, 2), (1, 2), (3, 2), (5, 3), (9, 4), (12, 5), (40, 2)]),
-       seed=st.integers(0, 2 ** 16))
-def test_forward_generated(d, k, sizes, kind, grid, seed):
+       algo=st.sampled_from([0, 3, 4]), seed=st.integers(0, 2 ** 16))
+def test_forward_generated(d, k, sizes, kind, grid, algo, seed):
     n = sum(sizes)
     x, rs = points(kind, n, d, seed, sizes)
     nb, db = grid
     db = min(db, d, 5) if db else 0
-    gi, gd = gpu_knn(x, rs, k, nb, db)
+    # algo: the default (which compares every pair in most of these), the leaf kernel, tile + list kernel
+    gi, gd = gpu_knn(x, rs, k, nb, db) if algo == 0 else gpu_knn_kernel(x, rs, k, nb, db, algo)
     oi, od = oracle.knn(x, rs, k)
-    assert_exact(gi, gd, oi, od, "d=%d k=%d sizes=%s %s grid=%s seed=%d" % (d, k, sizes, kind, grid, seed))
+    assert_exact(gi, gd, oi, od, "d=%d k=%d sizes=%s %s grid=%s algo=%d seed=%d" % (d, k, sizes, kind, grid, algo, seed))
 
 
 @settings(max_examples=80, deadline=None, derandomize=True, suppress_health_check=list(HealthCheck))

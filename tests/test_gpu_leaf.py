@@ -110,3 +110,34 @@ def test_a_hand_over_rule_chooses_no_kernel(n, d, defer_lanes):
     assert handed > 0 and int(bn.work_count.item()) == 0
     oi, od = oracle.knn(x, rs, 10)
     assert np.array_equal(idx.cpu().numpy(), oi) and np.array_equal(d2.cpu().numpy().view(np.uint32), od.view(np.uint32))
+
+
+# few points ask: whole groups of eight tiles handed to the list kernel, groups that are not, the last group short, and both
+# passes of a long list
+@pytest.mark.parametrize("d,k", [(3, 20), (6, 64), (6, 100), (8, 17), (10, 33)])
+@pytest.mark.parametrize("share", [0.0, 0.02, 0.3, 0.5, 1.0])
+def test_few_points_ask(d, k, share):
+    sizes = [3000, 0, 1, 700, 1333]
+    n = sum(sizes)
+    x, rs = W.uniform(n, d, seed=d + k, sizes=sizes)
+    rng = np.random.Generator(np.random.PCG64(k + d))
+    direction = np.where(rng.random(n) < share, 3, 0).astype(np.int32)
+    direction[n // 2:][rng.random(n - n // 2) < 0.8] = 1      # the second half of the rows mostly asks
+    check(x, rs, k, direction)
+
+
+# what sends blocks to the exact comparison: copies of few points, two tight clusters in a tile, far outliers; and tiles in
+# which no, one or many steps of the sorted order stand out
+@pytest.mark.parametrize("d", [2, 6, 8, 10])
+@pytest.mark.parametrize("kind", ["copies", "two_clusters", "far", "one_step", "steps"])
+@pytest.mark.parametrize("k", [12, 66])
+def test_grain_and_groups(d, kind, k):
+    rng = np.random.Generator(np.random.PCG64(d + k))
+    n = 3000
+    x = rng.random((n, d))
+    if kind == "copies": x = x[rng.integers(0, 7, size=n)]
+    if kind == "two_clusters": x = np.where(np.arange(n)[:, None] % 2, 0.1, 0.9) + 1e-5 * rng.standard_normal((n, d))
+    if kind == "far": x[rng.random(n) < 0.01] *= 1e4
+    if kind == "one_step": x[:, :min(d, 5)] = np.where(np.arange(n)[:, None] < n // 3, 0.25, 0.75)
+    if kind == "steps": x = np.floor(x * 3) / 3 + 1e-4 * rng.random((n, d))
+    check(np.ascontiguousarray(x.astype(np.float32)), np.array([0, 2100, n], dtype=np.int32), k)

@@ -71,3 +71,28 @@ def test_rows_from_member_lists(objs, kind):
         oM, oMn = oracle.oc_helper(asso, unique, unique_rs, rs, n_maxuq, n_maxrs, True, rot)
         M, Mn = run_gpu(asso, unique, unique_rs, rs, n_maxuq, n_maxrs, True, rot)
         assert np.array_equal(M, oM) and np.array_equal(Mn, oMn)
+
+
+# the row writer at its edges: rows per wavefront and rows per pass (32, 64, 128), one object that owns nearly all of a long
+# window (steps of thousands at one row), clipped and whole lists in one wavefront
+@pytest.mark.parametrize("n_maxrs", [1, 31, 32, 33, 127, 128, 129, 5000, 9000])
+@pytest.mark.parametrize("objs", [1, 63, 64, 65, 400])
+def test_row_writer_edges(n_maxrs, objs):
+    rng = np.random.Generator(np.random.PCG64(objs + n_maxrs))
+    rs = np.array([0, 5000, 5000, 9000], dtype=np.int32)
+    asso = np.empty(9000, dtype=np.int32)
+    unique, unique_rs = [], []
+    for s in (0, 2):
+        m = rs[s + 1] - rs[s]
+        labels = (rs[s] + np.sort(rng.choice(m, size=objs, replace=False))).astype(np.int32)
+        a = labels[rng.integers(0, objs, size=m)]
+        a[rng.random(m) < 0.9] = labels[objs // 2]           # most of the window is one object's
+        a[m // 2:m // 2 + 40] = -1
+        asso[rs[s]:rs[s + 1]] = a
+        unique.append(labels)
+        unique_rs.append(np.full(objs, s, dtype=np.int32))
+    unique, unique_rs = np.concatenate(unique), np.concatenate(unique_rs)
+    for n_maxuq, rot in [(5000, 1), (30, 1), (5000, 70), (2, 256)]:
+        oM, oMn = oracle.oc_helper(asso, unique, unique_rs, rs, n_maxuq, n_maxrs, True, rot)
+        M, Mn = run_gpu(asso, unique, unique_rs, rs, n_maxuq, n_maxrs, True, rot)
+        assert np.array_equal(M, oM) and np.array_equal(Mn, oMn)

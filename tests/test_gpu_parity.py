@@ -34,10 +34,22 @@ def assert_exact(gi, gd, oi, od, what=""):
         what, bad_d[0].size, bad_d[0][0], bad_d[1][0], gd[bad_d][0], od[bad_d][0])
 
 
+def gpu_knn_kernel(x, rs, k, n_bins, d_bin, algo, direction=None):
+    """One kernel of the query stage whatever the default is at this size: 3 leaf kernel, 4 tile + list kernel."""
+    xt, rt = torch.from_numpy(np.ascontiguousarray(x)).to(DEV), torch.from_numpy(np.ascontiguousarray(rs)).to(DEV)
+    dt = None if direction is None else torch.from_numpy(direction).to(DEV)
+    idx, d2 = B.fg_query_binned(B.fg_bin_points(xt, rt, k, n_bins, d_bin), rt, k, direction=dt, algo=algo)
+    torch.cuda.synchronize()
+    return idx.cpu().numpy(), d2.cpu().numpy()
+
+
 def check_against_oracle(x, rs, k, n_bins=0, d_bin=0, what=""):
+    """The default, which compares every pair in small problems, and both kernels that search the bins."""
     gi, gd = gpu_knn(x, rs, k, n_bins, d_bin)
     oi, od = oracle.knn(x, rs, k)
     assert_exact(gi, gd, oi, od, what)
+    for algo in (3, 4):
+        assert_exact(*gpu_knn_kernel(x, rs, k, n_bins, d_bin, algo), oi, od, "%s algo=%d" % (what, algo))
     return gi, gd
 
 
@@ -87,9 +99,10 @@ def test_k_range(k):
     check_against_oracle(x, rs, k, 9, 3, "k=%d nb=9" % k)
 
 
+@pytest.mark.parametrize("algo", [0, 3, 4])
 @pytest.mark.parametrize("k", [16, 32, 48, 64])
-def test_rows_written_from_registers_and_through_the_transposition(k):
-    """Rows of exactly the list size leave the tile kernel as 16-byte stores when the output is
+def test_rows_written_from_registers_and_through_the_transposition(k, algo):
+    """Rows of exactly the list size leave the tile and leaf kernels (algo 4, 3) as 16-byte stores when the output is
     16-byte aligned, through LDS otherwise: same result, nothing written outside the rows."""
     x, rs = W.uniform(2100, 3, seed=900 + k, sizes=[1500, 7, 593])          # a short split: padded rows
     n = x.shape[0]
@@ -100,7 +113,10 @@ def test_rows_written_from_registers_and_through_the_transposition(k):
         base_d = torch.full((n * k + 8,), -7.0, dtype=torch.float32, device=DEV)
         out_i = base_i[4 + shift:4 + shift + n * k].view(n, k)
         out_d = base_d[4 + shift:4 + shift + n * k].view(n, k)
-        B.fg_binned_select_knn(xt, rt, k, 0, 0, None, out_i, out_d)
+        if algo == 0:
+            B.fg_binned_select_knn(xt, rt, k, 0, 0, None, out_i, out_d)
+        else:
+            B.fg_query_binned(B.fg_bin_points(xt, rt, k), rt, k, out_i, out_d, algo=algo)
         torch.cuda.synchronize()
         assert_exact(out_i.cpu().numpy(), out_d.cpu().numpy(), oi, od, "k=%d shift=%d" % (k, shift))
         guard_i, guard_d = base_i.cpu().numpy(), base_d.cpu().numpy()
@@ -114,6 +130,8 @@ def test_n_bins_invariance():
     for nb, db in [(1, 2), (2, 3), (5, 3), (30, 3), (0, 0), (64, 3), (200, 2), (13, 2)]:
         gi, gd = gpu_knn(x, rs, 12, nb, db)
         assert_exact(gi, gd, oi, od, "nb=%d db=%d" % (nb, db))
+        for algo in (3, 4):                    # the default does not look at the bins at this size
+            assert_exact(*gpu_knn_kernel(x, rs, 12, nb, db, algo), oi, od, "nb=%d db=%d algo=%d" % (nb, db, algo))
 
 
 def test_short_and_empty_segments_padding():
@@ -292,6 +310,8 @@ def test_direction_flags(d, k):
         for nb, db in [(0, 0), (6, min(d, 3)), (1, 2)]:
             gi, gd = gpu_knn_dir(x, rs, direction, k, nb, db)
             assert_exact(gi, gd, oi, od, "dir d=%d k=%d nb=%d" % (d, k, nb))
+            for algo in (3, 4):
+                assert_exact(*gpu_knn_kernel(x, rs, k, nb, db, algo, direction), oi, od, "dir d=%d k=%d nb=%d algo=%d" % (d, k, nb, algo))
     # plain walk kernel with flags
     direction = patterns[0].astype(np.int32)
     oi, od = oracle.knn(x, rs, k, direction=direction)
@@ -435,20 +455,21 @@ def test_backward_overwrites_and_ignores_padding():
     assert np.all(out.cpu().numpy() == 0.0)
 
 
-def test_forward_and_backward_replay_in_a_hip_graph():
+@pytest.mark.parametrize("d", [3, 7])
+def test_forward_and_backward_replay_in_a_hip_graph(d):
     """The library enqueues only kernels (counters are cleared by fill kernels, not memset nodes) and never
     synchronises or allocates, so a whole step can be captured once and replayed.  Every replay is checked
     against the oracle, with eager work and synchronisations in between."""
-    x, rs = W.uniform(20000, 3, seed=91, sizes=[12000, 8000])
+    x, rs = W.uniform(20000, d, seed=91, sizes=[12000, 8000])
     k = 16
     g = W.upstream_grad(20000, k, seed=92)
     oi, od = oracle.knn(x, rs, k)
     ref, asum = oracle.knn_backward(g, oi, x)
     xt, rt, gt = torch.from_numpy(x).to(DEV), torch.from_numpy(rs).to(DEV), torch.from_numpy(g).to(DEV)
-    ws = B.alloc_workspace(20000, 3, 2, k, 0, 0, DEV)
+    ws = B.alloc_workspace(20000, d, 2, k, 0, 0, DEV)
     out_i = torch.empty((20000, k), dtype=torch.int32, device=DEV)
     out_d = torch.empty((20000, k), dtype=torch.float32, device=DEV)
-    grad = torch.empty((20000, 3), dtype=torch.float32, device=DEV)
+    grad = torch.empty((20000, d), dtype=torch.float32, device=DEV)
 
     def step():
         B.fg_binned_select_knn(xt, rt, k, 0, 0, ws, out_i, out_d)
