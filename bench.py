@@ -18,7 +18,9 @@ training step bins its points once).  The headline workload is configuration 3: 
   roofline_alu  the same stage against the float32 issue rate (what actually bounds it)
   cpu_baseline  the CPU oracle as it stands, timed on this machine's host cores on a bounded sample of the same
                 workload, all cores and one core (a reported baseline, not a target)
-  stages        mean milliseconds of binning / query / backward and candidate evaluations/s
+  stages        mean milliseconds of binning / query / backward, the kernel that serves the query stage, and the
+                candidate counts and evaluations/s of tile + list kernel (timed by themselves, tile_list_ms, where
+                another kernel is the default: the counts are theirs)
   configs       with --all-configs: the same stage figures for all five configurations
 
 --sweep uniform: the paper's own benchmark shape (Section 4: uniformly distributed random vectors, 1e3 .. 5e6
@@ -79,6 +81,15 @@ def _copy_bandwidth(torch, dev):
     return 2.0 * a.numel() * 4 / (ms * 1e-3) / 1e9
 
 
+def _default_kernel(n, d, k):
+    """What serves the query stage by default (fg_query_options::algo = 0)."""
+    if n <= 4096 and k <= 65:
+        return "all pairs"
+    if d >= 6:
+        return "leaf"
+    return "tile + list, dense tiles leaf" if d == 2 and n > 1 << 20 else "tile + list"
+
+
 class _Workload:
     """A configuration resident in HBM with its outputs and workspace."""
 
@@ -111,8 +122,11 @@ class _Workload:
         n, d, k = w.n, w.d, w.k
         ms_bin = _timed(torch, self.bin, reps)
         binning = self.bin()
-        ms_query = _timed(torch, lambda: B.fg_query_binned(binning, self.rs, k, self.out_idx, self.out_d2), reps)
-        deferred = int(binning.work_count.item())                     # of the timed query launches
+        ms_query = ms_tile = _timed(torch, lambda: B.fg_query_binned(binning, self.rs, k, self.out_idx, self.out_d2), reps)
+        kernel = _default_kernel(n, d, k)
+        if kernel != "tile + list":                                   # candidates are counted by these kernels only
+            ms_tile = _timed(torch, lambda: B.fg_query_binned(binning, self.rs, k, self.out_idx, self.out_d2, algo=4), reps)
+        deferred = int(binning.work_count.item())                     # of the timed launches of tile + list kernel
         B.fg_query_binned(binning, self.rs, k, self.out_idx, self.out_d2, self.cand)      # counting instantiation, never timed
         torch.cuda.synchronize()
         total_cand = int(self.cand.to(torch.int64).sum().item())
@@ -125,7 +139,7 @@ class _Workload:
         algo_bytes = n * (k * 8 + d * 4 + 4) + (total_bins + 1) * 4
         bwd_bytes = 2 * n * k * 4 + 2 * n * d * 4
         return {"n_bins": binning.n_bins, "d_bin": binning.d_bin, "total_bins": total_bins,
-                "binning_ms": ms_bin, "query_ms": ms_query, "backward_ms": ms_bwd, "backward_standalone_ms": ms_bwd_alone,
+                "binning_ms": ms_bin, "query_ms": ms_query, "kernel": kernel, "tile_list_ms": ms_tile, "backward_ms": ms_bwd, "backward_standalone_ms": ms_bwd_alone,
                 "candidates": total_cand, "deferred": deferred, "query_bytes": algo_bytes, "backward_bytes": bwd_bytes}
 
 
@@ -138,9 +152,10 @@ def _stage_record(w, st):
            "backward_ms": None if st["backward_ms"] is None else round(st["backward_ms"], 4),
            "backward_standalone_ms": None if st["backward_standalone_ms"] is None else round(st["backward_standalone_ms"], 4),
            "query_only_queries_per_s": round(n / q, 1),
+           "query_kernel": st["kernel"], "tile_list_ms": round(st["tile_list_ms"], 4),
            "candidates_per_query": round(st["candidates"] / n, 2),
            "queries_handed_to_list_kernel": st["deferred"],
-           "candidate_evals_per_s": round(st["candidates"] / q, 1),
+           "candidate_evals_per_s": round(st["candidates"] / (st["tile_list_ms"] * 1e-3), 1),
            "query_algorithmic_gbs": round(st["query_bytes"] / q / 1e9, 2),
            "hbm_frac_of_peak_query": round(st["query_bytes"] / q / 1e9 / HBM_PEAK_GBS, 5)}
     if st["backward_ms"] is not None:
@@ -179,7 +194,8 @@ def run_headline(args) -> int:
     copy_gbs = _copy_bandwidth(torch, dev)
     ms_query = st["query_ms"]
     achieved = st["query_bytes"] / (ms_query * 1e-3) / 1e9
-    roofline = {"bound": "hbm", "kernel": "query stage = k_query_tile_sorted (dominant) + k_query_list_wave + the tile-order kernels",
+    roofline = {"bound": "hbm", "kernel": "query stage = k_query_tile_sorted (dominant) + k_query_list_wave + the tile-order kernels"
+                if st["kernel"] == "tile + list" else "query stage: " + st["kernel"],
                 "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 5),
                 "traffic": _traffic_from_profiles("query_kernel_%s_traffic.txt" % w.name.split("_")[0]),
@@ -189,7 +205,7 @@ def run_headline(args) -> int:
     # the same stage against what actually bounds it: one float32 operation per lane and clock (no FMA by the
     # definition of the distance, packed float32 off): 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
     alu_peak = 256 * 4 * 16 * 2.4e9 / 1e12
-    alu_achieved = st["candidates"] * (3 * d - 1) / (ms_query * 1e-3) / 1e12
+    alu_achieved = st["candidates"] * (3 * d - 1) / (st["tile_list_ms"] * 1e-3) / 1e12
     roofline_alu = {"bound": "alu", "achieved": round(alu_achieved, 3), "peak": round(alu_peak, 1), "unit": "TFLOP/s",
                     "frac": round(alu_achieved / alu_peak, 5),
                     "note": "distance arithmetic only (3d-1 float32 operations per candidate); selection work not counted"}
@@ -246,11 +262,11 @@ def run_headline(args) -> int:
         if args.out:
             with open(args.out, "w") as f:
                 f.write("Stage times of the five configurations, one MI355X, automatic bins; command: python bench.py --all-configs --out %s\n\n" % args.out)
-                f.write("| config | N | d | K | splits | n_bins x d_bin | binning ms | query ms | backward ms | backward alone ms | candidates/query | handed to list kernel | query GB/s (algorithmic) | % of HBM peak |\n")
-                f.write("|---|---|---|---|---|---|---|---|---|---|---|---|---|---|\n")
+                f.write("| config | N | d | K | splits | n_bins x d_bin | binning ms | query kernel | query ms | tile + list ms | backward ms | backward alone ms | candidates/query (tile + list) | handed to list kernel (tile + list) | query GB/s (algorithmic) | % of HBM peak |\n")
+                f.write("|---|---|---|---|---|---|---|---|---|---|---|---|---|---|---|---|\n")
                 for name, r in table.items():
-                    f.write("| %s | %d | %d | %d | %d | %d x %d | %.3f | %.3f | %s | %s | %.1f | %d | %.1f | %.2f |\n" % (
-                        name, r["n"], r["d"], r["k"], r["segments"], r["n_bins"], r["d_bin"], r["binning_ms"], r["query_ms"],
+                    f.write("| %s | %d | %d | %d | %d | %d x %d | %.3f | %s | %.3f | %.3f | %s | %s | %.1f | %d | %.1f | %.2f |\n" % (
+                        name, r["n"], r["d"], r["k"], r["segments"], r["n_bins"], r["d_bin"], r["binning_ms"], r["query_kernel"], r["query_ms"], r["tile_list_ms"],
                         "" if r["backward_ms"] is None else "%.3f" % r["backward_ms"],
                         "" if r["backward_standalone_ms"] is None else "%.3f" % r["backward_standalone_ms"],
                         r["candidates_per_query"], r["queries_handed_to_list_kernel"], r["query_algorithmic_gbs"],
@@ -278,7 +294,7 @@ def run_sweep(args) -> int:
         for n in sizes:
             points.append(("k=%d" % k, n, 3, k))
 
-    lines = ["| sweep | N | d | K | n_bins x d_bin | forward ms | queries/s | candidates/query | brute force ms (n_bins=1) | speed-up | checked rows |",
+    lines = ["| sweep | N | d | K | n_bins x d_bin | forward ms | queries/s | candidates/query (tile + list) | brute force ms (n_bins=1) | speed-up | checked rows |",
              "|---|---|---|---|---|---|---|---|---|---|---|"]
     for name, n, d, k in points:
         x_np, rs_np = W.uniform(n, d, seed=4000 + d)

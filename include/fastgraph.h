@@ -108,7 +108,7 @@ typedef struct {
 typedef struct {
     const int32_t* dir;        /* [n] direction flags in ORIGINAL row order (see fg_binned_select_knn_dir), or NULL */
     int32_t algo;              /* 0: the default: every pair compared up to 4096 points and K <= 65, else the
-                                  leaf kernel from six dimensions on (and for the densest tiles of more than 2^22
+                                  leaf kernel from six dimensions on (and for the densest tiles of more than 2^20
                                   points in two), else tile kernel + list kernel;
                                   1: the one-lane-per-query shell walk for every query (slower; kept for
                                   cross-checking); 2: tile kernel + list kernel with the tile kernel's flattened scan on

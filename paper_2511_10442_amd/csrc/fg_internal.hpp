@@ -20,21 +20,21 @@ struct QueryArgs {
     int32_t* out_idx;          // [n][k]
     float* out_d2;             // [n][k]
     int32_t* out_cand;         // [n] or nullptr
-    int32_t* work_list;        // [n] sorted positions of queries deferred by the tile kernel, in bin order
+    int32_t* work_list;        // [n] sorted positions of handed-over queries, in bin order; before that the leaf kernel's boxes
     int32_t* work_count;       // [2] queries on the work list; dense tiles (see dense_class)
-    uint64_t* handed;          // [ceil(n/64)] per tile: which of its 64 queries the tile kernel hands over
+    uint64_t* handed;          // [ceil(n/64)] per tile: which of its 64 queries the tile (or leaf) kernel hands over
     const int32_t* bin_idx;    // [n] flat bin of each point, original row order
     int32_t* tile_order;       // [2*ceil(n/64) + 128]: tile order, tile classes, class histogram, class cursors
     int32_t n;
     int32_t d;                 // coordinates per point (the record length follows from it)
     int32_t n_segments;
     int32_t k;                 // slots per output row
-    int32_t slot0;             // tile + list kernels: neighbours already placed by an earlier pass (0 or 64); this pass keeps only keys above the one in row slot `slot0`
-    int32_t k_list;            // tile + list kernels: neighbours this pass finds (1..64, or 0 for K = 1); they go to row slots slot0+1 .. slot0+k_list
+    int32_t slot0;             // tile, list and leaf kernels: neighbours already placed by an earlier pass (0 or 64); this pass keeps only keys above the one in row slot `slot0`
+    int32_t k_list;            // tile, list and leaf kernels: neighbours this pass finds (1..64, or 0 for K = 1); they go to row slots slot0+1 .. slot0+k_list
     int32_t n_bins;
     int32_t cells_per_segment; // T: bins of a row split times the slices per bin
     int32_t sub_shift;         // log2 of the slices every bin is cut into along the last binning dimension
-    int32_t algo;              // 0: tile kernel + list kernel, 1: one lane per query for everything, 2: as 0 with the flattened scan on every tile
+    int32_t algo;              // 0: the default of the sizes, 1: one lane per query for everything, 2: tile + list kernel with the flattened scan on every tile, 3: leaf kernel, 4: tile + list kernel
     int32_t defer_lanes;       // tile kernel: go on past shell 1 only while more lanes than this are unfinished
     // of some kernels only, and last: the fields above keep their places in the other kernels' arguments
     int32_t dense_class;       // > 0: tiles of this work class and above are the leaf kernel's, the others the tile kernel's

@@ -11,14 +11,14 @@
 //   count    members of object k inside walk chunk c                    -> counts[c][k]
 //   scan     exclusive prefix over the chunks of every object           -> members before chunk c, total
 //   members  walk chunk c again and write the members at their final row of M; pad M with -1
-//   others   for a block of kOcRows OUTPUT rows of M_not: row r of an object holds the vertex at walk position r + m(r),
+//   others   for a block of OUTPUT rows of M_not: row r of an object holds the vertex at walk position r + m(r),
 //            m(r) = members met before the r-th non-member, a step function that M itself tells (member j at walk
-//            position w_j comes before row r iff w_j - j <= r).  So nothing is walked: a lane keeps the next four steps
-//            of each of its objects in registers and the rows are written with arithmetic alone.
+//            position w_j comes before row r iff w_j - j <= r).  So nothing is walked, but for objects with more members
+//            than M has rows: the steps of 32 rows go through LDS and the rows are written with a running sum.
 // Lanes are objects throughout, so objects of one row split read neighbouring vertices; all objects of a wavefront that
 // share a window read it through scalar loads (count, members).
 // Integer-only; bound by the M_not write stream (n_unique x n_maxrs words).  10 x 100,000 vertices, 2,000 objects,
-// 0.82 GB: 815 -> 395 us (count 100 -> 34, scan 56 -> 11, members 171 -> 50, others 509 -> 302, of which the stores
+// 0.82 GB: 800 -> 395 us (count 100 -> 34, scan 56 -> 11, members 171 -> 49, others 509 -> 294, of which the stores
 // alone would take some 160).
 // Without a workspace the single-kernel form of the paper is used.
 #include "fg_internal.hpp"

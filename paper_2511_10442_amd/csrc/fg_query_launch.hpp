@@ -292,15 +292,17 @@ static void launch_query_pass(const QueryArgs& a_in, hipStream_t stream)
     launch_handed<D, DB, COUNT>(a, stream);
 }
 
-// From this many dimensions on the leaf kernel is the default.  Query stage, tile + list kernel against leaf kernel:
-//   200k uniform points, d = 6, K = 40      3.69 against  2.32 ms     1M the same                     13.0 against 11.5 ms
-//   400k, d = 6, K = 10                     3.68 against  2.92 ms     400k, d = 7, K = 16              6.2 against  6.1 ms
-//   500k, d = 8, K = 64                    21.6  against 11.5 ms      60k, d = 10, K = 40              7.4 against  1.25 ms
-//   2k, d = 6, K = 10                       0.28 against  0.09 ms     2k, d = 10, K = 40               1.31 against 0.19 ms
-//   100k Gaussian mixture, d = 6, K = 60    5.3  against  2.9 ms
-//   below: 1M uniform points, d = 5, K = 40 3.2  against  9.0 ms      100k mixture, d = 4, K = 40      0.65 against 1.27 ms
-// Below, bins of one shell leave a query few hundred candidates and the tile kernel's scan is cheap next to the leaf
-// kernel's fixed cost per tile.
+// From this many dimensions on the leaf kernel is the default.  Query stage, tile + list kernel against leaf kernel, in ms:
+//   uniform points, one split                                    50 Gaussian clusters, width 0.03
+//   200k, d = 6, K = 40    3.62 against 1.85     5k, d = 6, K = 10    0.28 against 0.14     100k, d = 6, K = 60  1.03 against 0.81
+//   400k, d = 6, K = 10    3.80 against 1.68     1M, d = 6, K = 40   13.0  against 8.5      4M, d = 6, K = 16   32.3  against 30.9
+//   400k, d = 7, K = 16    6.2  against 4.2      500k, d = 8, K = 64 21.4  against 10.0     60k, d = 10, K = 40  7.4  against 1.3
+// Below, on uniform points, bins of one shell leave a query few hundred candidates and the tile kernel's scan is cheap next to
+// the leaf kernel's fixed cost per tile:
+//   1M, d = 5, K = 40      3.3  against 4.8      100k, d = 5, K = 40  0.55 against 0.76     1M, d = 4, K = 40    1.4  against 2.8
+//   20k, d = 4, K = 24     0.14 against 0.21     1M, d = 3, K = 32    0.39 against 1.22
+// There the leaf kernel is ahead on clusters and on few points (100k in clusters, d = 4, K = 40 1.13 against 0.62, d = 5
+// 1.16 against 0.70; 5k uniform, d = 5, K = 16 0.35 against 0.14), which no size tells from the others.
 constexpr int kLeafMinD = 6;
 
 // Lists of more than 64 neighbours (K - 1 up to 127) take two passes: the first finds the 64 nearest, the second
