@@ -108,12 +108,14 @@ typedef struct {
 typedef struct {
     const int32_t* dir;        /* [n] direction flags in ORIGINAL row order (see fg_binned_select_knn_dir), or NULL */
     int32_t algo;              /* 0: the default: every pair compared up to 4096 points and K <= 65, else the
-                                  leaf kernel from six dimensions on (and for the densest tiles of more than 2^20
+                                  group kernel up to some ten thousand points, else the leaf kernel from six
+                                  dimensions on (and for the densest tiles of more than 2^20
                                   points in two), else tile kernel + list kernel;
                                   1: the one-lane-per-query shell walk for every query (slower; kept for
                                   cross-checking); 2: tile kernel + list kernel with the tile kernel's flattened scan on
                                   every tile instead of the uneven ones only (for tests); 3: leaf kernel; 4: tile
-                                  kernel + list kernel.  Calls that count candidates take 3 as 4 */
+                                  kernel + list kernel; 5: group kernel.  Calls that count candidates take 3
+                                  and 5 as 4 */
     int32_t defer_lanes;       /* after shell 1 a wavefront of the tile kernel goes on to the next shell only while
                                   more than this many of its 64 queries are unfinished, the rest go to the list
                                   kernel; 0..64, negative: the default (64 for d <= 5, 6 beyond).  Without effect where

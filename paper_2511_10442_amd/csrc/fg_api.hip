@@ -21,6 +21,8 @@ hipError_t launch_query_d10(const QueryArgs&, int32_t, hipStream_t);
 
 hipError_t launch_query(const QueryArgs& a, int32_t d, int32_t d_bin, hipStream_t stream)
 {
+    if (!a.out_cand && (a.algo == 5 || (a.algo == 0 && !takes_small_path(a.n, a.k) && takes_group_kernel(a.n, d, a.n_segments, a.k))))
+        return launch_query_group(a, stream);
     switch (d) {
         case 2: return launch_query_d2(a, d_bin, stream);
         case 3: return launch_query_d3(a, d_bin, stream);
@@ -323,7 +325,7 @@ fg_status fg_query_binned(const fg_binning* view, const int32_t* row_splits, int
     a.work_list = (int32_t*)(sc + S.work_list); a.work_count = (int32_t*)(sc + S.work_count);
     a.handed = (uint64_t*)(sc + S.rank);       // the counting sort is done with its ranks
     a.bin_idx = view->bin_idx; a.tile_order = (int32_t*)(sc + S.tile_order);
-    a.algo = (options && (options->algo >= 1 && options->algo <= 4)) ? options->algo : 0;
+    a.algo = (options && (options->algo >= 1 && options->algo <= 5)) ? options->algo : 0;
     a.defer_lanes = defer > 64 ? 64 : defer;
     hipError_t e = launch_query(a, d, view->d_bin, (hipStream_t)stream);
     return e == hipSuccess ? FG_OK : FG_ERR_LAUNCH;
