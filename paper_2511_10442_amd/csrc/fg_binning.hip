@@ -2,6 +2,7 @@
 // sorted by bin, cumulative bin boundaries).  gfx950, wave64.
 //
 // Stages, all enqueued on one stream:
+// (few points: all but the last in one launch, see k_bin_few)
 //   prepare   zero the bin counters, reset the bounding-box keys
 //   bbox      per row split, min/max of the first d_bin coordinates (register, wave and block
 //             reduction, one atomic pair per block and dimension on an order-preserving key)
@@ -155,10 +156,8 @@ k_bbox(const float* __restrict__ coords, const int32_t* __restrict__ row_splits,
 //           floor((x-lo)*inv_w) and of lo + j*w together err by < 2^-21 * max(|lo|,|hi|,hi-lo).
 struct DimGeom { float lo, inv_w, w, slack; };
 
-__device__ __forceinline__ DimGeom dim_geometry(const uint32_t* __restrict__ bbox_keys, int32_t n_keys, int32_t t, int32_t n_bins)
+__device__ __forceinline__ DimGeom box_geometry(float lo, float hi, int32_t n_bins)
 {
-    float lo = key_to_float(bbox_keys[(int64_t)t * kKeyStride]);
-    const float hi = key_to_float(bbox_keys[(int64_t)(n_keys + t) * kKeyStride]);
     const float ext = hi - lo;
     float inv_w = 0.0f, w = 0.0f, slack = 0.0f;
     if (ext >= 1e-30f && ext <= 3.0e38f) {          // false for NaN and for the empty-split sentinels
@@ -171,6 +170,27 @@ __device__ __forceinline__ DimGeom dim_geometry(const uint32_t* __restrict__ bbo
     }
     if (!(lo >= -3.0e38f && lo <= 3.0e38f)) lo = 0.0f;   // empty split: keep the record finite
     return DimGeom{lo, inv_w, w, slack};
+}
+__device__ __forceinline__ DimGeom dim_geometry(const uint32_t* __restrict__ bbox_keys, int32_t n_keys, int32_t t, int32_t n_bins)
+{
+    return box_geometry(key_to_float(bbox_keys[(int64_t)t * kKeyStride]), key_to_float(bbox_keys[(int64_t)(n_keys + t) * kKeyStride]), n_bins);
+}
+
+// number of a cell inside its row split
+template <int DB>
+__device__ __forceinline__ int32_t flat_cell(const int32_t (&cell)[DB], int32_t n_bins, int32_t sub_shift, int32_t morton_bits)
+{
+    int32_t f = 0;
+    if (morton_bits == 0) {                 // row-major, last dimension fastest (what the query kernels expect)
+#pragma unroll
+        for (int c = 0; c < DB; ++c) f = f * ((c == DB - 1) ? n_bins << sub_shift : n_bins) + cell[c];
+    } else {                                // bit-interleaved: consecutive bins form compact blocks in space
+        for (int b = 0; b < morton_bits; ++b) {
+#pragma unroll
+            for (int c = 0; c < DB; ++c) f |= ((cell[c] >> b) & 1) << (b * DB + (DB - 1 - c));
+        }
+    }
+    return f;
 }
 
 // Bin of every point and its arrival rank inside the bin.  The rank comes from an atomic add on
@@ -219,16 +239,7 @@ k_assign(const float* __restrict__ coords, const int32_t* __restrict__ row_split
             const DimGeom r = dim_geometry(bbox_keys, n_keys, s * DB + c, nb_c);
             cell[c] = cell_of(p[c], r.lo, r.inv_w, nb_c);
         }
-        int32_t f = 0;
-        if (morton_bits == 0) {                 // row-major, last dimension fastest (what the query kernels expect)
-#pragma unroll
-            for (int c = 0; c < DB; ++c) f = f * ((c == DB - 1) ? n_bins << sub_shift : n_bins) + cell[c];
-        } else {                                // bit-interleaved: consecutive bins form compact blocks in space
-            for (int b = 0; b < morton_bits; ++b) {
-#pragma unroll
-                for (int c = 0; c < DB; ++c) f |= ((cell[c] >> b) & 1) << (b * DB + (DB - 1 - c));
-            }
-        }
+        int32_t f = flat_cell<DB>(cell, n_bins, sub_shift, morton_bits);
         f += s * cells_per_segment;
         flat[it] = f;
         bin_idx[i] = f;
@@ -349,6 +360,102 @@ k_scan_apply(int32_t* __restrict__ counters, int64_t n_counters, const int32_t* 
     }
 }
 
+// Few points: bounding box, cells, ranks and boundaries in one launch, one workgroup per row split, the counters (16 bits each)
+// in LDS.  A launch costs some 4.5 us however little it does, and five of them (counters, boxes, cells, two for the prefix
+// sum) were nearly all of the 28 us that binning 5000 to 20,000 points took.  What bounds it: one CU reads a split's
+// coordinates twice and adds its points to the LDS counters.  The records are written by k_scatter as otherwise: scattered
+// stores of one CU take as long as the launch that they would save.
+constexpr int kFewThreads = 1024;
+constexpr int32_t kFewCells = 30000;              // of a row split: 60 KB of counters, what a workgroup gets without asking
+constexpr int32_t kFewSplits = 1024;
+// Points of an average split: one of 20,000 points, fg_bin_points six launches against two, in us: d = 2 26.5 / 16.1, d = 3 27.6 / 19.5,
+// d = 5 29.7 / 23.0, d = 10 29.0 / 24.6; of 32,000 27.2 / 21.2, 28.6 / 24.2, 30.4 / 30.5 (fg_knn_backward, which bins for itself: d = 3 42.7 / 43.2).
+// 16 splits of 1250 points 31 to 41 / 13 (the caller's own 12 us a call); 200 of 100 38 to 52 / 13.
+// A split may hold all the points, so their number is bounded, too (and positions in a split fit 16 bits).
+constexpr int32_t kFewN = 49152;
+inline bool bins_in_one_launch(int32_t n, int32_t d, int32_t n_segments, int32_t cells_per_segment)
+{
+    return n <= kFewN && n_segments <= kFewSplits && cells_per_segment <= kFewCells && (int64_t)n * (d + 8) <= (int64_t)n_segments * 327680;
+}
+
+template <int DB>
+__global__ void __launch_bounds__(kFewThreads)
+k_bin_few(const float* __restrict__ coords, const int32_t* __restrict__ row_splits, int32_t n, int32_t d, int32_t n_segments,
+          int32_t n_bins, int32_t sub_shift, int32_t cells_per_segment, int32_t morton_bits, float* __restrict__ geom,
+          int32_t* __restrict__ bin_idx, int32_t* __restrict__ rank, int32_t* __restrict__ bounds)
+{
+    extern __shared__ uint32_t cnt[];             // two counters a word
+    __shared__ float red[2][kFewThreads / 64][DB];
+    __shared__ int32_t wave_tot[kFewThreads / 64];
+    const int32_t t = threadIdx.x, s = blockIdx.x;
+    const int32_t first = row_splits[s], end = row_splits[s + 1];
+    const int32_t words = (cells_per_segment + 1) / 2;
+    for (int32_t i = t; i < words; i += kFewThreads) cnt[i] = 0;
+    float mn[DB], mx[DB];
+#pragma unroll
+    for (int c = 0; c < DB; ++c) { mn[c] = 3.4028235e38f; mx[c] = -3.4028235e38f; }
+#pragma unroll 4
+    for (int32_t i = first + t; i < end; i += kFewThreads) {
+#pragma unroll
+        for (int c = 0; c < DB; ++c) {
+            const float x = coords[(int64_t)i * d + c];
+            mn[c] = fminf(mn[c], x);
+            mx[c] = fmaxf(mx[c], x);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < DB; ++c) {
+        const float a = wave_min(mn[c]), b = wave_max(mx[c]);
+        if ((t & 63) == 0) { red[0][t >> 6][c] = a; red[1][t >> 6][c] = b; }
+    }
+    __syncthreads();
+    DimGeom g[DB];
+#pragma unroll
+    for (int c = 0; c < DB; ++c) {
+        float a = red[0][0][c], b = red[1][0][c];
+#pragma unroll
+        for (int w = 1; w < kFewThreads / 64; ++w) { a = fminf(a, red[0][w][c]); b = fmaxf(b, red[1][w][c]); }
+        g[c] = box_geometry(a, b, (c == DB - 1) ? n_bins << sub_shift : n_bins);
+        if (first >= end) g[c].lo = 0.0f;         // an empty split: no extent (the sentinels' difference overflows), keep the record finite
+        if (t == 0) {
+            float* o = geom + (int64_t)(s * DB + c) * kGeomStride;
+            o[0] = g[c].lo; o[1] = g[c].inv_w; o[2] = g[c].w; o[3] = g[c].slack;
+        }
+    }
+    const int32_t cell0 = s * cells_per_segment;
+#pragma unroll 4
+    for (int32_t i = first + t; i < end; i += kFewThreads) {
+        int32_t cell[DB];
+#pragma unroll
+        for (int c = 0; c < DB; ++c)
+            cell[c] = cell_of(coords[(int64_t)i * d + c], g[c].lo, g[c].inv_w, (c == DB - 1) ? n_bins << sub_shift : n_bins);
+        const int32_t f = flat_cell<DB>(cell, n_bins, sub_shift, morton_bits);
+        const uint32_t half = (f & 1) * 16;
+        const uint32_t old = atomicAdd(&cnt[f >> 1], 1u << half);
+        bin_idx[i] = cell0 + f;
+        rank[i] = (int32_t)(old >> half & 0xffffu);
+    }
+    __syncthreads();
+    // exclusive prefix: a run of words per thread, then the threads' totals
+    const int32_t per = (words + kFewThreads - 1) / kFewThreads;
+    const int32_t w0 = min(t * per, words), w1 = min(w0 + per, words);
+    int32_t sum = 0;
+    for (int32_t i = w0; i < w1; ++i) sum += (int32_t)((cnt[i] & 0xffffu) + (cnt[i] >> 16));
+    const int32_t incl = wave_incl_scan(sum);
+    if ((t & 63) == 63) wave_tot[t >> 6] = incl;
+    __syncthreads();
+    uint32_t run = (uint32_t)(incl - sum);
+    for (int32_t w = 0; w < t >> 6; ++w) run += (uint32_t)wave_tot[w];
+    for (int32_t i = w0; i < w1; ++i) {
+        const uint32_t v = cnt[i];
+        cnt[i] = run | (run + (v & 0xffffu)) << 16;
+        run += (v & 0xffffu) + (v >> 16);
+    }
+    __syncthreads();
+    for (int32_t i = t; i < cells_per_segment; i += kFewThreads) bounds[cell0 + i] = first + (int32_t)(cnt[i >> 1] >> (i & 1) * 16 & 0xffffu);
+    if (s == n_segments - 1 && t == 0) bounds[cell0 + cells_per_segment] = n;
+}
+
 // Forward order: every point becomes one record (coordinates, original row, zero padding: whole 16-byte
 // vectors) at its sorted position; that is one scattered 16-byte store per vector, where separate coordinate
 // and permutation arrays took a scattered 4-byte store each (measured 103 MB written for a 16 MB payload).
@@ -420,6 +527,18 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
     const int64_t n_counters = total_bins + 1;
     const int32_t n_keys = n_segments * d_bin;
     const int32_t cells_per_segment = (int32_t)(total_bins / n_segments);
+    if (bins_in_one_launch(n, d, n_segments, cells_per_segment)) {
+#define FG_FEW(DB) hipLaunchKernelGGL(k_bin_few<DB>, dim3(n_segments), dim3(kFewThreads), (size_t)(cells_per_segment + 1) / 2 * 4, stream, coords, \
+                                      row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, morton_bits, geom, bin_idx, rank, bounds)
+        switch (d_bin) {
+            case 2: FG_FEW(2); break;
+            case 3: FG_FEW(3); break;
+            case 4: FG_FEW(4); break;
+            case 5: FG_FEW(5); break;
+            default: return hipErrorInvalidValue;
+        }
+#undef FG_FEW
+    } else {
     {
         int64_t work = n_counters > 2 * (int64_t)n_keys ? n_counters : 2 * (int64_t)n_keys;
         int64_t grid = (work + kBlock - 1) / kBlock;
@@ -454,6 +573,7 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
             hipLaunchKernelGGL(k_scan_apply<false>, dim3((unsigned)n_chunks), dim3(kBlock), 0, stream, bounds, n_counters,
                                scan_partials);
         }
+    }
     }
     switch (d) {
         case 2: launch_scatter<2>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream); break;
