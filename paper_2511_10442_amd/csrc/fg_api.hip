@@ -2,6 +2,7 @@
 #include <math.h>
 #include <mutex>
 #include "fg_internal.hpp"
+#include "fg_order.hpp"
 
 // Workspace of fg_binned_select_knn_static: device memory that belongs to the library, one copy per GPU, held
 // until the process ends.  In host code this name is only a handle for hipGetSymbolAddress, never an address.
@@ -73,13 +74,14 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 // The query stage's scratch block (fg_binning::scratch): hand-over counter first (the one word documented in the
 // header), then the work list, the tile order and an [n] array that the counting sort uses for the ranks inside
 // the cells and the query stage afterwards for the tiles' hand-over marks (8 bytes per 64 points).
-struct ScratchLayout { size_t work_count, work_list, tile_order, rank, total; };
+struct ScratchLayout { size_t work_count, order_counters, work_list, tile_order, rank, total; };
 
 ScratchLayout scratch_layout(int64_t n)
 {
     ScratchLayout S;
     size_t off = 0;
-    S.work_count = off; off = align_up(off + 2 * sizeof(int32_t));
+    S.work_count = off; off += 16 * sizeof(int32_t);
+    S.order_counters = off; off = align_up(off + 3 * sizeof(int32_t));
     S.work_list = off;  off = align_up(off + sizeof(int32_t) * (size_t)n);
     S.tile_order = off; off = align_up(off + sizeof(int32_t) * (size_t)(2 * ((n + 63) / 64) + 128));
     S.rank = off;       off = align_up(off + sizeof(int32_t) * (size_t)n);
@@ -275,10 +277,16 @@ static fg_status bin_points_impl(const float* coords, const int32_t* row_splits,
     view->sub_bins = 1 << sub_shift;
     view->scratch = ws + L.scratch;
     if (n == 0 || check_only) return FG_OK;
+    const ScratchLayout S = scratch_layout(n);
+    char* const sc = ws + L.scratch;
+    // the ordering's lists lie in the work list, its rows where the backward and the counting sort keep theirs
+    const OrderArgs order = order_args(coords, view->bin_bounds, (float*)(ws + L.rec), (int32_t*)(ws + L.perm), (int32_t*)(sc + S.rank),
+                                       (int32_t*)(sc + S.order_counters), (int32_t*)(sc + S.work_list), n);
+    const bool ordered = morton_bits == 0 && takes_dense_order(n, d);
     hipError_t e = launch_binning(coords, row_splits, (int32_t)n, d, n_segments, n_bins, d_bin, sub_shift, L.total_bins,
                                   (uint32_t*)(ws + L.keys), (float*)(ws + L.geom), (int32_t*)(ws + L.bin_idx),
-                                  (int32_t*)(ws + L.scratch + scratch_layout(n).rank), (int32_t*)(ws + L.perm), (float*)(ws + L.rec),
-                                  (int32_t*)(ws + L.bounds), (int32_t*)(ws + L.partials), morton_bits,
+                                  (int32_t*)(sc + S.rank), (int32_t*)(ws + L.perm), (float*)(ws + L.rec),
+                                  (int32_t*)(ws + L.bounds), (int32_t*)(ws + L.partials), morton_bits, ordered ? &order : nullptr,
                                   (hipStream_t)stream);
     return e == hipSuccess ? FG_OK : FG_ERR_LAUNCH;
 }

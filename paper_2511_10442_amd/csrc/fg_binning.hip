@@ -17,7 +17,9 @@
 //   scan      exclusive prefix over the counters (per-chunk totals, then apply; a pass over the
 //             totals in between only when there are many chunks)
 //   scatter   sorted position = bounds[cell] + rank: one record per point (coordinates, original row)
+//   order     where the query stage profits: dense cells' points along a space-filling curve (fg_order.hip)
 #include "fg_internal.hpp"
+#include "fg_order.hpp"
 
 namespace fg {
 
@@ -37,8 +39,10 @@ __device__ __forceinline__ float key_to_float(uint32_t k)
 }
 
 __global__ void __launch_bounds__(kBlock)
-k_prepare(int32_t* __restrict__ counters, int64_t n_counters, uint32_t* __restrict__ bbox_keys, int32_t n_keys)
+k_prepare(int32_t* __restrict__ counters, int64_t n_counters, uint32_t* __restrict__ bbox_keys, int32_t n_keys,
+          int32_t* __restrict__ order_counters /* of the lists of dense cells, nullptr: not asked */)
 {
+    if (order_counters && blockIdx.x == 0 && threadIdx.x < 3) order_counters[threadIdx.x] = 0;
     int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     int64_t step = (int64_t)gridDim.x * kBlock;
     for (int64_t j = i; j < n_counters; j += step) counters[j] = 0;
@@ -329,9 +333,11 @@ k_scan_tops(int32_t* __restrict__ partials, int32_t n_partials)
 
 // partials hold exclusive prefixes (after k_scan_tops) or, with totals = true, the raw per-chunk totals, of
 // which every block then sums those before its own (cheaper than a third launch while there are few chunks)
-template <bool TOTALS>
+// ORDER: cells of more than kOrderMin points go to the lists of the ordering kernels, one atomic pair per block.
+template <bool TOTALS, bool ORDER>
 __global__ void __launch_bounds__(kBlock)
-k_scan_apply(int32_t* __restrict__ counters, int64_t n_counters, const int32_t* __restrict__ partials)
+k_scan_apply(int32_t* __restrict__ counters, int64_t n_counters, const int32_t* __restrict__ partials, int32_t* __restrict__ order_counters,
+             int32_t* __restrict__ small, int32_t* __restrict__ large)
 {
     int32_t chunk_base;
     if (TOTALS) {
@@ -357,6 +363,26 @@ k_scan_apply(int32_t* __restrict__ counters, int64_t n_counters, const int32_t* 
         int64_t q = base + j;
         if (q < n_counters) counters[q] = run;
         run += v[j];
+    }
+    if constexpr (ORDER) {
+        int32_t dense = 0;                        // cells for the one list, and for the other in the upper half
+#pragma unroll
+        for (int j = 0; j < kScanItems; ++j) dense += v[j] > kOrderChunk ? 1 << 16 : (v[j] > kOrderMin ? 1 : 0);
+        if (!__syncthreads_or(dense)) return;
+        __shared__ int32_t base_small, base_large;
+        int32_t all;
+        const int32_t mine = block_excl_scan(dense, &all);
+        if (threadIdx.x == 0) {
+            base_small = atomicAdd(&order_counters[kOrderSmall], all & 0xffff);
+            base_large = atomicAdd(&order_counters[kOrderLarge], all >> 16);
+        }
+        __syncthreads();
+        int32_t to_small = base_small + (mine & 0xffff), to_large = base_large + (mine >> 16);
+#pragma unroll
+        for (int j = 0; j < kScanItems; ++j) {
+            if (v[j] > kOrderChunk) large[to_large++] = (int32_t)(base + j);
+            else if (v[j] > kOrderMin) small[to_small++] = (int32_t)(base + j);
+        }
     }
 }
 
@@ -522,12 +548,12 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
                           int32_t n_segments, int32_t n_bins, int32_t d_bin, int32_t sub_shift, int64_t total_bins,
                           uint32_t* bbox_keys, float* geom, int32_t* bin_idx, int32_t* rank,
                           int32_t* perm, float* rec, int32_t* bounds,
-                          int32_t* scan_partials, int32_t morton_bits, hipStream_t stream)
+                          int32_t* scan_partials, int32_t morton_bits, const OrderArgs* order, hipStream_t stream)
 {
     const int64_t n_counters = total_bins + 1;
     const int32_t n_keys = n_segments * d_bin;
     const int32_t cells_per_segment = (int32_t)(total_bins / n_segments);
-    if (bins_in_one_launch(n, d, n_segments, cells_per_segment)) {
+    if (!order && bins_in_one_launch(n, d, n_segments, cells_per_segment)) {
 #define FG_FEW(DB) hipLaunchKernelGGL(k_bin_few<DB>, dim3(n_segments), dim3(kFewThreads), (size_t)(cells_per_segment + 1) / 2 * 4, stream, coords, \
                                       row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, morton_bits, geom, bin_idx, rank, bounds)
         switch (d_bin) {
@@ -544,7 +570,7 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
         int64_t grid = (work + kBlock - 1) / kBlock;
         if (grid > 4096) grid = 4096;
         hipLaunchKernelGGL(k_prepare, dim3((unsigned)grid), dim3(kBlock), 0, stream, bounds, n_counters, bbox_keys,
-                           n_keys);
+                           n_keys, order ? order->counters : nullptr);
     }
 #define FG_DB_SWITCH(ASSIGN)                                                                                       \
     switch (d_bin) {                                                                                               \
@@ -565,14 +591,17 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
         int64_t n_chunks = (n_counters + kScanChunk - 1) / kScanChunk;
         hipLaunchKernelGGL(k_scan_partials, dim3((unsigned)n_chunks), dim3(kBlock), 0, stream, bounds, n_counters,
                            scan_partials);
-        if (n_chunks <= 2048) {
-            hipLaunchKernelGGL(k_scan_apply<true>, dim3((unsigned)n_chunks), dim3(kBlock), 0, stream, bounds, n_counters,
-                               scan_partials);
+        if (n_chunks > 2048) hipLaunchKernelGGL(k_scan_tops, dim3(1), dim3(kBlock), 0, stream, scan_partials, (int32_t)n_chunks);
+#define FG_APPLY(TOTALS, ORDER, COUNTERS, SMALL, LARGE) hipLaunchKernelGGL((k_scan_apply<TOTALS, ORDER>), dim3((unsigned)n_chunks), dim3(kBlock), 0, stream, \
+                                                                           bounds, n_counters, scan_partials, COUNTERS, SMALL, LARGE)
+        if (order) {
+            if (n_chunks <= 2048) FG_APPLY(true, true, order->counters, order->small, order->large);
+            else FG_APPLY(false, true, order->counters, order->small, order->large);
         } else {
-            hipLaunchKernelGGL(k_scan_tops, dim3(1), dim3(kBlock), 0, stream, scan_partials, (int32_t)n_chunks);
-            hipLaunchKernelGGL(k_scan_apply<false>, dim3((unsigned)n_chunks), dim3(kBlock), 0, stream, bounds, n_counters,
-                               scan_partials);
+            if (n_chunks <= 2048) FG_APPLY(true, false, nullptr, nullptr, nullptr);
+            else FG_APPLY(false, false, nullptr, nullptr, nullptr);
         }
+#undef FG_APPLY
     }
     }
     switch (d) {
@@ -587,6 +616,7 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
         case 10: launch_scatter<10>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream); break;
         default: return hipErrorInvalidValue;
     }
+    if (order) return launch_order(*order, stream);
     return hipGetLastError();
 }
 

@@ -42,6 +42,8 @@ struct QueryArgs {
     const float* coords;       // [n][d] the points in their original order: given (and rec not) where nothing was binned, else nullptr
 };
 
+struct OrderArgs;
+
 // Host-side launchers, one per translation unit.  Each returns hipGetLastError() of its launches.
 hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_t n, int32_t d,
                           int32_t n_segments, int32_t n_bins, int32_t d_bin, int32_t sub_shift /* last binning dimension:
@@ -53,6 +55,7 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
                                                  b > 0 (the backward's row order): n_bins = 2^b, bit-interleaved bin order,
                                                  only perm is written, plus for d = 3 a copy of coords in the original
                                                  order padded to float4 in place of the records */,
+                          const OrderArgs* order /* dense cells' points are put in order, nullptr: not */,
                           hipStream_t stream);
 
 // Up to this many points and one list of keys (K <= 65) every pair is compared, one wavefront per query, without bins.
@@ -83,6 +86,12 @@ inline bool takes_group_kernel(int64_t n, int32_t d, int32_t n_segments, int32_t
     if ((d == 4 || d == 5) && n <= (int64_t)n_segments * 16384) most *= 2;
     return n <= most && !(n <= 8192 && d <= 3 && k < 16);
 }
+
+// Two dimensions and many points: the densest tiles are the leaf kernel's (dense_class_for), and the points of dense cells are
+// ordered for it when they are binned.  (Ordered in three to five dimensions, too, the kernels that search by boxes gained 0 to 5 %
+// on clusters, and the sort took more.)
+constexpr int64_t kDenseMinN = 1 << 20;
+inline bool takes_dense_order(int64_t n, int32_t d) { return d == 2 && n > kDenseMinN; }
 
 // d = 2..10, d_bin = 2..min(d,5)
 hipError_t launch_query(const QueryArgs& a, int32_t d, int32_t d_bin, hipStream_t stream);

@@ -235,7 +235,6 @@ static void allow_lds(K kernel, size_t bytes)
 // Where no tile qualifies the four launches cost some 10 us from 1M points on (6 at 200k): of a whole call on uniform
 // points 3 % at 1M and 1 % at 4M, so the line lies at 2^20.
 constexpr int32_t kDenseClass = 18;
-constexpr int32_t kDenseMinN = 1 << 20;
 static inline int32_t dense_class_for(int32_t k_list)
 {
     int32_t c = kDenseClass;
@@ -266,7 +265,7 @@ static void launch_query_pass(const QueryArgs& a_in, hipStream_t stream)
                        ordered ? a.tile_order + 2 * grid : nullptr);
     if (ordered) {
         hipLaunchKernelGGL(k_tile_work<DB>, dim3((grid + 4 * kTilesPerWave - 1) / (4 * kTilesPerWave)), dim3(256), 0, stream, a, grid);
-        if (D == 2 && !COUNT && a.algo == 0 && a.n > kDenseMinN) a.dense_class = dense_class_for(a.k_list);
+        if (D == 2 && !COUNT && a.algo == 0 && takes_dense_order(a.n, D)) a.dense_class = dense_class_for(a.k_list);
         hipLaunchKernelGGL(k_tile_rank, dim3((grid + 255) / 256), dim3(256), 0, stream, a.tile_order, grid, a.dense_class,
                            a.dense_class > 0 ? a.work_count + 1 : nullptr);
     } else {
