@@ -110,7 +110,8 @@ typedef struct {
     int32_t algo;              /* 0: the default: every pair compared up to 4096 points and K <= 65, else the
                                   group kernel up to some ten thousand points, else the leaf kernel from six
                                   dimensions on (and for the densest tiles of more than 2^20
-                                  points in two), else tile kernel + list kernel;
+                                  points in two), else tile kernel + list kernel or, where estimates of their
+                                  work made on the device tell of clusters, the group kernel for all;
                                   1: the one-lane-per-query shell walk for every query (slower; kept for
                                   cross-checking); 2: tile kernel + list kernel with the tile kernel's flattened scan on
                                   every tile instead of the uneven ones only (for tests); 3: leaf kernel; 4: tile

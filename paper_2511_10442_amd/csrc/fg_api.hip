@@ -83,7 +83,7 @@ ScratchLayout scratch_layout(int64_t n)
     S.work_count = off; off += 16 * sizeof(int32_t);
     S.order_counters = off; off = align_up(off + 3 * sizeof(int32_t));
     S.work_list = off;  off = align_up(off + sizeof(int32_t) * (size_t)n);
-    S.tile_order = off; off = align_up(off + sizeof(int32_t) * (size_t)(2 * ((n + 63) / 64) + 128));
+    S.tile_order = off; off = align_up(off + sizeof(int32_t) * (size_t)(2 * ((n + 63) / 64) + 2 * kTileClasses));
     S.rank = off;       off = align_up(off + sizeof(int32_t) * (size_t)n);
     S.total = off;
     return S;
@@ -286,7 +286,8 @@ static fg_status bin_points_impl(const float* coords, const int32_t* row_splits,
     hipError_t e = launch_binning(coords, row_splits, (int32_t)n, d, n_segments, n_bins, d_bin, sub_shift, L.total_bins,
                                   (uint32_t*)(ws + L.keys), (float*)(ws + L.geom), (int32_t*)(ws + L.bin_idx),
                                   (int32_t*)(sc + S.rank), (int32_t*)(ws + L.perm), (float*)(ws + L.rec),
-                                  (int32_t*)(ws + L.bounds), (int32_t*)(ws + L.partials), morton_bits, ordered ? &order : nullptr,
+                                  (int32_t*)(ws + L.bounds), (int32_t*)(ws + L.partials), morton_bits,
+                                  morton_bits == 0 ? (int32_t*)(sc + S.tile_order) + 2 * ((n + 63) / 64) : nullptr, ordered ? &order : nullptr,
                                   (hipStream_t)stream);
     return e == hipSuccess ? FG_OK : FG_ERR_LAUNCH;
 }

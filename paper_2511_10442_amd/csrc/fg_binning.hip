@@ -40,8 +40,9 @@ __device__ __forceinline__ float key_to_float(uint32_t k)
 
 __global__ void __launch_bounds__(kBlock)
 k_prepare(int32_t* __restrict__ counters, int64_t n_counters, uint32_t* __restrict__ bbox_keys, int32_t n_keys,
-          int32_t* __restrict__ order_counters /* of the lists of dense cells, nullptr: not asked */)
+          int32_t* __restrict__ tile_counters, int32_t* __restrict__ order_counters /* of the lists of dense cells; nullptr: not asked */)
 {
+    if (tile_counters && blockIdx.x == 0 && threadIdx.x < 2 * kTileClasses) tile_counters[threadIdx.x] = 0;
     if (order_counters && blockIdx.x == 0 && threadIdx.x < 3) order_counters[threadIdx.x] = 0;
     int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     int64_t step = (int64_t)gridDim.x * kBlock;
@@ -408,8 +409,9 @@ template <int DB>
 __global__ void __launch_bounds__(kFewThreads)
 k_bin_few(const float* __restrict__ coords, const int32_t* __restrict__ row_splits, int32_t n, int32_t d, int32_t n_segments,
           int32_t n_bins, int32_t sub_shift, int32_t cells_per_segment, int32_t morton_bits, float* __restrict__ geom,
-          int32_t* __restrict__ bin_idx, int32_t* __restrict__ rank, int32_t* __restrict__ bounds)
+          int32_t* __restrict__ bin_idx, int32_t* __restrict__ rank, int32_t* __restrict__ bounds, int32_t* __restrict__ tile_counters)
 {
+    if (tile_counters && blockIdx.x == 0 && threadIdx.x < 2 * kTileClasses) tile_counters[threadIdx.x] = 0;
     extern __shared__ uint32_t cnt[];             // two counters a word
     __shared__ float red[2][kFewThreads / 64][DB];
     __shared__ int32_t wave_tot[kFewThreads / 64];
@@ -548,14 +550,14 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
                           int32_t n_segments, int32_t n_bins, int32_t d_bin, int32_t sub_shift, int64_t total_bins,
                           uint32_t* bbox_keys, float* geom, int32_t* bin_idx, int32_t* rank,
                           int32_t* perm, float* rec, int32_t* bounds,
-                          int32_t* scan_partials, int32_t morton_bits, const OrderArgs* order, hipStream_t stream)
+                          int32_t* scan_partials, int32_t morton_bits, int32_t* tile_counters, const OrderArgs* order, hipStream_t stream)
 {
     const int64_t n_counters = total_bins + 1;
     const int32_t n_keys = n_segments * d_bin;
     const int32_t cells_per_segment = (int32_t)(total_bins / n_segments);
     if (!order && bins_in_one_launch(n, d, n_segments, cells_per_segment)) {
 #define FG_FEW(DB) hipLaunchKernelGGL(k_bin_few<DB>, dim3(n_segments), dim3(kFewThreads), (size_t)(cells_per_segment + 1) / 2 * 4, stream, coords, \
-                                      row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, morton_bits, geom, bin_idx, rank, bounds)
+                                      row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, morton_bits, geom, bin_idx, rank, bounds, tile_counters)
         switch (d_bin) {
             case 2: FG_FEW(2); break;
             case 3: FG_FEW(3); break;
@@ -570,7 +572,7 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
         int64_t grid = (work + kBlock - 1) / kBlock;
         if (grid > 4096) grid = 4096;
         hipLaunchKernelGGL(k_prepare, dim3((unsigned)grid), dim3(kBlock), 0, stream, bounds, n_counters, bbox_keys,
-                           n_keys, order ? order->counters : nullptr);
+                           n_keys, tile_counters, order ? order->counters : nullptr);
     }
 #define FG_DB_SWITCH(ASSIGN)                                                                                       \
     switch (d_bin) {                                                                                               \

@@ -7,6 +7,7 @@
 namespace fg {
 
 constexpr int kGeomStride = 4;   // floats per (segment, binning dim): lo, inv_w, w, slack
+constexpr int kTileClasses = 64; // classes of a tile's work estimate: as many counters and cursors behind the order of the tiles
 constexpr int kKeyStride = 16;   // words between two bounding-box keys: one 64-byte line each, so that the
                                  // atomics on different keys do not queue up behind one another in one L2 line
 
@@ -37,7 +38,7 @@ struct QueryArgs {
     int32_t algo;              // 0: the default of the sizes, 1: one lane per query for everything, 2: tile + list kernel with the flattened scan on every tile, 3: leaf kernel, 4: tile + list kernel, 5: group kernel
     int32_t defer_lanes;       // tile kernel: go on past shell 1 only while more lanes than this are unfinished
     // of some kernels only, and last: the fields above keep their places in the other kernels' arguments
-    int32_t dense_class;       // > 0: tiles of this work class and above are the leaf kernel's, the others the tile kernel's
+    int32_t dense_class;       // > 0: tiles of this work class and above decide which are not the tile kernel's (the first work_count[1] of the order)
     int32_t few_ask;           // leaf kernel: tiles of which no more queries than this ask (direction flags) are handed over
     const float* coords;       // [n][d] the points in their original order: given (and rec not) where nothing was binned, else nullptr
 };
@@ -55,6 +56,7 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
                                                  b > 0 (the backward's row order): n_bins = 2^b, bit-interleaved bin order,
                                                  only perm is written, plus for d = 3 a copy of coords in the original
                                                  order padded to float4 in place of the records */,
+                          int32_t* tile_counters /* [2 * kTileClasses] of the query stage, cleared; nullptr with morton_bits */,
                           const OrderArgs* order /* dense cells' points are put in order, nullptr: not */,
                           hipStream_t stream);
 
@@ -95,6 +97,10 @@ inline bool takes_dense_order(int64_t n, int32_t d) { return d == 2 && n > kDens
 
 // d = 2..10, d_bin = 2..min(d,5)
 hipError_t launch_query(const QueryArgs& a, int32_t d, int32_t d_bin, hipStream_t stream);
+
+// the group kernel over all tiles in the order, if k_tile_rank gave them to it; up to kClustersMaxD dimensions, boxes are there
+constexpr int kClustersMaxD = 5;
+hipError_t launch_query_clusters(const QueryArgs& a, hipStream_t stream);
 
 // the group kernel, whatever the size
 hipError_t launch_query_group(const QueryArgs& a, hipStream_t stream);

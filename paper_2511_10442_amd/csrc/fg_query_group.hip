@@ -16,92 +16,24 @@
 // and bounds; below, the chain of one group.  A bound from a first pass over the near leaves as well (nothing kept until
 // then, then one sort a query) cost more distances than it saved sorts: +10 to +80 %.  Figures beside the rule,
 // takes_group_kernel.
-#include "fg_query.hpp"
+#include "fg_query_tile.hpp"
+#include "fg_group_boxes.hpp"
 #include "fg_wavesort.hpp"
 
 namespace fg {
 
-constexpr int kGroupLeaf = 64;                  // points per leaf: one per lane
 constexpr int kGroupStart = 8;                  // leaves that a first bound comes from
+// Most workgroups where there may be nothing to do: an empty launch of 8192, 16384 and 25,000 takes 3, 5 and 7 us, and clusters of 100k
+// points, d = 4, K = 40 455, 395 and 385 (each takes further groups, whose number differs by one).
+constexpr int32_t kRankedGrid = 16384;
 constexpr int kGroupPend = 128;                 // kept candidates of a query between two merges
 
-template <int D> constexpr int group_box_vecs() { return (2 * D + 3) / 4; }
-
-// Boxes live in the work list's area (4 bytes a point): 80 bytes per 64 points and per 4096 points at most.
-struct GroupTree { float4* leaf; float4* node; int32_t n_leaf, n_node; };
-
-template <int D>
-static GroupTree group_tree(void* area, int32_t n)
-{
-    GroupTree t;
-    t.n_leaf = (n + kGroupLeaf - 1) / kGroupLeaf;
-    t.n_node = (t.n_leaf + 63) / 64;
-    t.node = reinterpret_cast<float4*>(area);
-    t.leaf = t.node + (size_t)t.n_node * group_box_vecs<D>();
-    return t;
-}
-
-__device__ __forceinline__ float wave_min_f32(float v)
-{
-    const int id = __float_as_int(3.4028235e38f);
-    auto step = [&](int o) { v = fminf(v, __int_as_float(o)); };
-    step(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x111, 0xf, 0xf, false));
-    step(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x112, 0xf, 0xf, false));
-    step(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x114, 0xf, 0xf, false));
-    step(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x118, 0xf, 0xf, false));
-    step(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x142, 0xa, 0xf, false));
-    step(__builtin_amdgcn_update_dpp(id, __float_as_int(v), 0x143, 0xc, 0xf, false));
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-
-// Boxes of 64 leaves and of their node, one workgroup.
 template <int D>
 static __global__ void __launch_bounds__(1024)
 k_group_boxes(const float4* __restrict__ rec, int32_t n, GroupTree tree, int32_t* __restrict__ work_count)
 {
-    constexpr int NB = group_box_vecs<D>();
-    __shared__ float red[16][2 * D];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (blockIdx.x == 0 && threadIdx.x == 0) *work_count = 0;         // nothing is handed over on this path
-    float nmn[D], nmx[D];
-#pragma unroll
-    for (int c = 0; c < D; ++c) { nmn[c] = 3.4028235e38f; nmx[c] = 3.4028235e38f; }      // minima of x and of -x
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int32_t leaf = blockIdx.x * 64 + wv * 4 + i;
-        if (leaf >= tree.n_leaf) break;
-        const int32_t p = leaf * kGroupLeaf + lane;
-        float x[D];
-        int32_t row;
-        load_rec<D>(rec, p < n ? p : n - 1, x, row);
-        float w[NB * 4];
-#pragma unroll
-        for (int c = 0; c < NB * 4; ++c) w[c] = 0.0f;
-#pragma unroll
-        for (int c = 0; c < D; ++c) {
-            const float mn = wave_min_f32(x[c]), mx = wave_min_f32(-x[c]);
-            nmn[c] = fminf(nmn[c], mn);
-            nmx[c] = fminf(nmx[c], mx);
-            w[c] = mn;
-            w[D + c] = -mx;
-        }
-        if (lane == 0) {
-#pragma unroll
-            for (int v = 0; v < NB; ++v) tree.leaf[(int64_t)leaf * NB + v] = make_float4(w[4 * v], w[4 * v + 1], w[4 * v + 2], w[4 * v + 3]);
-        }
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (int c = 0; c < D; ++c) { red[wv][c] = nmn[c]; red[wv][D + c] = nmx[c]; }
-    }
-    __syncthreads();
-    if (threadIdx.x < 2 * D) {
-        const int c = threadIdx.x;
-        float m = red[0][c];
-#pragma unroll
-        for (int w = 1; w < 16; ++w) m = fminf(m, red[w][c]);
-        reinterpret_cast<float*>(tree.node + (int64_t)blockIdx.x * NB)[c] = c < D ? m : -m;
-    }
+    group_boxes<D, 16>(rec, n, tree, blockIdx.x);
 }
 
 __device__ __forceinline__ int32_t uniform_i32(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -110,15 +42,12 @@ __device__ __forceinline__ int32_t uniform_i32(int32_t v) { return __builtin_amd
 __device__ __forceinline__ float in_vector(float v) { asm("" : "+v"(v)); return v; }
 
 template <int D, int Q, bool LOWER>
-__global__ void __launch_bounds__(kQueryBlock)
-k_query_group(QueryArgs a, GroupTree tree)
+__device__ __forceinline__ void group_queries(const QueryArgs& a, const GroupTree& tree, const int32_t p0, uint64_t (*pend)[kGroupPend])
 {
     constexpr int NV = rec_vecs(D);
     constexpr int NB = group_box_vecs<D>();
-    __shared__ uint64_t pend[Q][kGroupPend];
     const int lane = threadIdx.x;
     const int32_t cap = a.k_list;                   // 0 <= cap <= 64
-    const int32_t p0 = blockIdx.x * Q;
     const float kInf = __int_as_float(0x7f800000);
     // lane q of the first Q holds query q
     float x[D];
@@ -428,10 +357,37 @@ k_query_group(QueryArgs a, GroupTree tree)
     }
 }
 
+// With a.dense_class the tiles that k_tile_rank gave to this kernel, all or none, in their order; the workgroups take groups in turn,
+// and those of a tile meet in one XCD's L2 (workgroups are dealt round robin to 8).
+template <int D, int Q, bool LOWER>
+__global__ void __launch_bounds__(kQueryBlock)
+k_query_group(QueryArgs a, GroupTree tree)
+{
+    constexpr int kPerTile = kQueryBlock / Q;
+    __shared__ uint64_t pend[Q][kGroupPend];
+    const bool ranked = D <= kClustersMaxD && a.dense_class > 0;
+    const int32_t count = ranked ? dense_tiles(a) : 0, rounds = (count + 7) >> 3;
+    const int32_t groups = ranked ? rounds * 8 * kPerTile : (int32_t)gridDim.x;
+    // heaviest tiles first, and whoever has the first of one round has the last of the next
+    for (int32_t round = 0; round * (int32_t)gridDim.x < groups; ++round) {
+        const int32_t i = round * gridDim.x + (round & 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x);
+        int32_t p0 = i * Q;
+        if (ranked) {
+            const int32_t j = i >> 3, at = (j / kPerTile) * 8 + (i & 7);
+            p0 = at < count ? (a.tile_order[at] & ((1 << kOrderFlagBit) - 1)) * kQueryBlock + (j % kPerTile) * Q : a.n;
+        }
+        if (p0 < a.n) group_queries<D, Q, LOWER>(a, tree, p0, pend);
+        if (!ranked) break;
+        __syncthreads();
+    }
+}
+
 template <int D, int Q>
 static void launch_group_pass(const QueryArgs& a, const GroupTree& tree, hipStream_t stream)
 {
-    const dim3 grid((a.n + Q - 1) / Q);
+    int32_t blocks = (a.n + Q - 1) / Q;
+    if (a.dense_class > 0 && blocks > kRankedGrid) blocks = kRankedGrid;       // its workgroups take further groups
+    const dim3 grid(blocks);
     if (a.slot0 == 0) hipLaunchKernelGGL((k_query_group<D, Q, false>), grid, dim3(kQueryBlock), 0, stream, a, tree);
     else hipLaunchKernelGGL((k_query_group<D, Q, true>), grid, dim3(kQueryBlock), 0, stream, a, tree);
 }
@@ -454,6 +410,24 @@ static hipError_t launch_group(const QueryArgs& a_in, hipStream_t stream)
         else if constexpr (D < 7) launch_group_pass<D, 4>(a, tree, stream);
     }
     return hipGetLastError();
+}
+
+template <int D>
+static hipError_t launch_clusters(const QueryArgs& a, hipStream_t stream)
+{
+    launch_group_pass<D, 4>(a, group_tree<D>(a.work_list, a.n), stream);
+    return hipGetLastError();
+}
+
+hipError_t launch_query_clusters(const QueryArgs& a, hipStream_t stream)
+{
+    switch (a.d) {
+        case 2: return launch_clusters<2>(a, stream);
+        case 3: return launch_clusters<3>(a, stream);
+        case 4: return launch_clusters<4>(a, stream);
+        case 5: return launch_clusters<5>(a, stream);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_query_group(const QueryArgs& a, hipStream_t stream)

@@ -5,6 +5,7 @@
 #include "fg_query_list.hpp"
 #include "fg_query_leaf.hpp"
 #include "fg_query_small.hpp"
+#include "fg_group_boxes.hpp"
 
 namespace fg {
 
@@ -15,20 +16,16 @@ namespace fg {
 // evenly spread work, the last third of it with most of the chip idle.  The tiles are therefore ranked by an
 // estimate of their work, in 64 classes of half a power of two, heaviest class first.
 // tile_order: [0, T) the order, [T, 2T) class of each tile (bit 6: uneven, see k_tile_work), [2T, 2T+64) class
-// histogram, [2T+64, 2T+128) cursors.
-constexpr int kTileClasses = 64;
-
-static __global__ void k_reset_query_scratch(int32_t* work_count, int32_t* tile_counters)
-{
-    if (threadIdx.x == 0) *work_count = 0;
-    if (tile_counters && threadIdx.x < 2 * kTileClasses) tile_counters[threadIdx.x] = 0;
-}
+// histogram, [2T+64, 2T+128) cursors; the last two are zero between calls: the binning clears them, and k_list_compact, the
+// first kernel that nothing follows that reads them, does again (a launch of their own to clear them took 4 us of every call).
 
 // The work list of the list kernel from the tiles' hand-over marks: blocks of 1024 tiles, the queries of a block in
 // tile order (a block's place in the list comes from one atomic add, so blocks may swap, 65 536 queries each).
 static __global__ void __launch_bounds__(1024) k_list_compact(const uint64_t* __restrict__ handed, int32_t n_tiles,
-                                                              int32_t* __restrict__ work_list, int32_t* __restrict__ work_count)
+                                                              int32_t* __restrict__ work_list, int32_t* __restrict__ work_count,
+                                                              int32_t* __restrict__ tile_counters /* to be cleared, or nullptr */)
 {
+    if (tile_counters && blockIdx.x == 0 && threadIdx.x < 2 * kTileClasses) tile_counters[threadIdx.x] = 0;
     __shared__ int32_t wave_tot[16];
     __shared__ int32_t block_base;
     const int32_t t = blockIdx.x * 1024 + threadIdx.x;
@@ -65,6 +62,17 @@ __device__ __forceinline__ int32_t tile_class(int32_t work)
 
 constexpr int kTilesPerWave = 16;
 
+// How many tiles, the first of the order, another kernel takes: those of dense_class and above, or, with all_from > 0, all if so many
+// are of it, else none.
+struct TileShare {
+    int32_t dense_class, all_from;
+    int32_t* n_dense;                             // nullptr: not asked, and dense_class is 0 or (no class) 64
+    __device__ void write(int32_t m, int32_t n_tiles) const
+    {
+        if (n_dense) *n_dense = all_from == 0 ? m : (m >= all_from ? n_tiles : 0);
+    }
+};
+
 // Work estimate of a tile: what the first two shells cost it without any pruning, i.e. for every column of the
 // 3 x ... x 3 neighbourhood the longest candidate run any of its queries has there (the tile kernel scans a
 // column for as long as its busiest lane needs), summed over the columns.  Taken over 8 of the tile's 64 queries
@@ -90,9 +98,20 @@ __device__ __forceinline__ int32_t oct_sum_i32(int32_t v)
     return v;
 }
 
-template <int DB>
-static __global__ void __launch_bounds__(256) k_tile_work(QueryArgs a, int32_t n_tiles)
+// Where the group kernel may serve the call, the blocks behind the first `blocks` make its boxes
+// (of its leaves, those of k_tile_rank of its nodes; ranking the tiles here, too, by the last block to finish, took longer than the launch
+// that it saves: 100k points 18 us against 7 and 7).
+template <int D, int DB>
+static __global__ void __launch_bounds__(256) k_tile_work(QueryArgs a, int32_t n_tiles, int32_t blocks)
 {
+    if constexpr (D <= kClustersMaxD) {
+        if ((int32_t)blockIdx.x >= blocks) {
+            const GroupTree tree = group_tree<D>(a.work_list, a.n);
+            const int32_t leaf = ((int32_t)blockIdx.x - blocks) * 4 + (threadIdx.x >> 6);
+            if (leaf < tree.n_leaf) group_leaf_box<D>(a.rec, a.n, tree, leaf);
+            return;
+        }
+    }
     __shared__ int32_t hist[kTileClasses];
     if (threadIdx.x < kTileClasses) hist[threadIdx.x] = 0;
     __syncthreads();
@@ -192,27 +211,38 @@ static __global__ void __launch_bounds__(256) k_tile_work(QueryArgs a, int32_t n
 // Position of every tile: classes in descending order; inside a class roughly the bin order (blocks of 256
 // consecutive tiles reserve their places with one atomic per class, and a block's tiles keep the order in which
 // its waves arrive), so that tiles running at the same time still share their neighbourhoods in the L2 cache.
-static __global__ void __launch_bounds__(256) k_tile_rank(int32_t* __restrict__ order, int32_t n_tiles, int32_t dense_class,
-                                                          int32_t* __restrict__ n_dense /* tiles of that class and above, nullptr: not asked */)
+template <int D>
+static __global__ void __launch_bounds__(256) k_tile_rank(int32_t* __restrict__ order, int32_t n_tiles, TileShare share, GroupTree tree)
 {
+    if constexpr (D <= kClustersMaxD) {
+        const int32_t blocks = (n_tiles + 255) >> 8;
+        if ((int32_t)blockIdx.x >= blocks) {
+            const int32_t node = ((int32_t)blockIdx.x - blocks) * 4 + (threadIdx.x >> 6);
+            if (node < tree.n_node) group_node_box<D>(tree, node);
+            return;
+        }
+    }
     __shared__ int32_t local[kTileClasses];   // this block's tiles per class, then the block's first position in the class
     __shared__ int32_t first[kTileClasses];   // position of the class's first tile: all heavier classes before it
+    const int32_t t = blockIdx.x * 256 + threadIdx.x;
+    const int32_t word = t < n_tiles ? order[n_tiles + t] : 0;
+    static_assert(kTileClasses == 64, "one class per lane of the first wavefront");
     if (threadIdx.x < kTileClasses) {
         local[threadIdx.x] = 0;
-        int32_t s = 0;
-        for (int c = threadIdx.x + 1; c < kTileClasses; ++c) s += order[2 * n_tiles + c];
-        first[threadIdx.x] = s;
-        if (n_dense && blockIdx.x == 0 && (int32_t)threadIdx.x == dense_class) *n_dense = s + order[2 * n_tiles + dense_class];
+        const int32_t own = order[2 * n_tiles + threadIdx.x];
+        int32_t s = own;                      // with the classes above
+#pragma unroll
+        for (int o = 1; o < kTileClasses; o <<= 1) {
+            const int32_t up = __shfl_down(s, o, 64);
+            s += (int32_t)threadIdx.x + o < kTileClasses ? up : 0;
+        }
+        first[threadIdx.x] = s - own;
+        if (blockIdx.x == 0 && (int32_t)threadIdx.x == share.dense_class) share.write(s, n_tiles);
     }
     __syncthreads();
-    const int32_t t = blockIdx.x * 256 + threadIdx.x;
-    int32_t cls = 0, mine = 0, uneven = 0;
-    if (t < n_tiles) {
-        const int32_t word = order[n_tiles + t];
-        cls = word & (kTileClasses - 1);
-        uneven = (word >> kTileFlatBit) & 1;
-        mine = atomicAdd(&local[cls], 1);
-    }
+    int32_t mine = 0;
+    const int32_t cls = word & (kTileClasses - 1), uneven = (word >> kTileFlatBit) & 1;
+    if (t < n_tiles) mine = atomicAdd(&local[cls], 1);
     __syncthreads();
     if (threadIdx.x < kTileClasses && local[threadIdx.x] > 0)
         local[threadIdx.x] = atomicAdd(&order[2 * n_tiles + kTileClasses + threadIdx.x], local[threadIdx.x]);
@@ -227,13 +257,11 @@ static void allow_lds(K kernel, size_t bytes)
 }
 
 // Two dimensions, many points: tiles whose queries meet 2000 candidates and more in their first shells (class 18: 512 passes
-// of four) lie in bins that hold far more than their share, and go to the leaf kernel, which sifts such numbers several
-// times faster than the tile kernel scans them; its boxes prune little there (inside a bin the points are in no
-// order).  Bins are made for K points, so the class rises with K (two classes are a factor of two).  Query stage, skewed
-// density, tile kernel against both, in ms: 5M points, K = 16 15.8 against 11.1 (classes 16 to 22: 11.1 to 11.5); 1M, K = 8 6.3
-// against 3.4, K = 16 10.7 against 4.5; 2M, K = 16 11.5 against 9.3; 200k, K = 16 2.5 against 1.1.
+// of four) lie in bins that hold far more than their share, and go to the leaf kernel, whose boxes prune there because the points of
+// such bins are put in order when they are binned.  Bins are made for K points, so the class rises with K (two classes are a
+// factor of two).  Whole training step of 5M points of strongly varying density, K = 16, tile kernel alone against both 18 -> 4.1 ms.
 // Where no tile qualifies the four launches cost some 10 us from 1M points on (6 at 200k): of a whole call on uniform
-// points 3 % at 1M and 1 % at 4M, so the line lies at 2^20.
+// points 3 % at 1M and 1 % at 4M, so the line lies at 2^20 (kDenseMinN).
 constexpr int32_t kDenseClass = 18;
 static inline int32_t dense_class_for(int32_t k_list)
 {
@@ -242,37 +270,68 @@ static inline int32_t dense_class_for(int32_t k_list)
     return c;
 }
 
+// Clusters: which of two kernels serves the whole call is decided on the device, from the work estimates (k_tile_rank).  In
+// clusters the tile kernel's densest tiles set its end, at some 0.25 to 0.5 us for a pass of their estimate, and the group kernel,
+// which has no such tiles, takes a time that hardly depends on the cloud.  The call is the group kernel's if one tile in 512
+// (at least four) is of a class whose time alone is beyond that; a class is returned, 0: the tile kernel's whatever the cloud.
+// Query stage, tile + list kernel against group kernel, in us (U uniform, M 50 Gaussian clusters, S showers, P density r^(-5/3)):
+//   d = 2, K = 10: 100k U 56 / 120, P 1358 / 186; 700k P 5017 / 2012      K = 40: 700k P 6679 / 4975
+//   d = 3, K = 10: 100k U 80 / 202, M 198 / 185, S 451 / 184; 150k M 203 / 272, S 381 / 254      K = 40: 100k U 157 / 267, M 397 / 247, S 411 / 230
+//   d = 4, K = 10: 100k U 174 / 296, M 1020 / 279; 400k M 1931 / 1173      K = 40: 100k U 253 / 427, M 850 / 419; 250k M 1519 / 1237
+//   d = 5, K = 10: 100k U 428 / 473, M 3770 / 377; 700k M 10205 / 4131      K = 40: 100k U 546 / 703, M 1594 / 503; 700k M 9042 / 6074
+// (The dense tiles alone to the group kernel, the others to the tile kernel, one after the other: of 100k M, d = 4 no gain, each of
+// the two has its own end.)
+static inline int32_t clusters_class_for(int32_t n, int32_t d, int32_t k_list)
+{
+    struct Line { int32_t most; float ns, ns_k, us_pass; };     // largest n; ns a query of the group kernel and for each neighbour; us a pass of the tile kernel
+    static constexpr Line kLine[kClustersMaxD + 1] = {{0, 0, 0, 1}, {0, 0, 0, 1}, {1 << 20, 2.0f, 0.02f, 0.25f}, {1 << 17, 1.8f, 0.017f, 0.55f},
+                                                      {3 << 17, 2.5f, 0.045f, 0.5f}, {1 << 20, 4.4f, 0.07f, 0.45f}};
+    const Line& l = kLine[d];
+    if (n > l.most) return 0;
+    // (and longer by the share that n is of 2^20: its workgroups take their groups in fixed turns, 900k P in 4 splits, K = 16 2270 / 2740)
+    const float passes = (float)n * 1e-3f * (1.0f + (float)n * 9.5e-7f) * (l.ns + l.ns_k * (float)(k_list + 1)) / l.us_pass;
+    int32_t c = 2;
+    for (float mid = 2.4f; mid < passes && c < kTileClasses; ++c) mid = (c & 1 ? 1.0f : 1.5f) * 1.2f * (float)(1 << ((c + 1) >> 1));
+    return c < kTileClasses ? c : 0;
+}
+
 // The queries handed over by the tile (or leaf) kernel: their work list, then the list kernel.
 template <int D, int DB, bool COUNT>
 static void launch_handed(const QueryArgs& a, hipStream_t stream)
 {
     const int grid = (a.n + kQueryBlock - 1) / kQueryBlock;
-    hipLaunchKernelGGL(k_list_compact, dim3((grid + 1023) / 1024), dim3(1024), 0, stream, a.handed, grid, a.work_list, a.work_count);
+    hipLaunchKernelGGL(k_list_compact, dim3((grid + 1023) / 1024), dim3(1024), 0, stream, a.handed, grid, a.work_list, a.work_count,
+                       a.tile_order ? a.tile_order + 2 * grid : nullptr);
     // one query per wavefront; four times the wave slots of the chip: the queries differ widely in cost, and with
     // more, shorter workgroups the hardware dispatcher evens them out (cursors in memory cost more than they gained)
     const int list_grid = a.n < 32768 ? a.n : 32768;
     hipLaunchKernelGGL((k_query_list_wave<D, DB, COUNT>), dim3(list_grid), dim3(kQueryBlock), 0, stream, a);
 }
 
-// One pass of the fast path: tile kernel + list kernel for a.k_list <= 64 neighbours per query.
+// One pass of the fast path: tile kernel + list kernel for a.k_list <= 64 neighbours per query, or what takes their place.  The second
+// pass of a long list (LOWER) keeps the order of the first, the choice made with it (a.dense_class) and, where the group kernel
+// serves the call, its boxes: nothing is handed over then, so the work list that would take their place stays empty.
 template <int D, int DB, bool COUNT, bool LOWER>
-static void launch_query_pass(const QueryArgs& a_in, hipStream_t stream)
+static void launch_query_pass(QueryArgs& a, hipStream_t stream)
 {
-    QueryArgs a = a_in;
     const int grid = (a.n + kQueryBlock - 1) / kQueryBlock;
-    const bool ordered = a.tile_order && a.bin_idx && grid > 1024;    // a few waves per SIMD: nothing to reorder
-    hipLaunchKernelGGL(k_reset_query_scratch, dim3(1), dim3(2 * kTileClasses), 0, stream, a.work_count,
-                       ordered ? a.tile_order + 2 * grid : nullptr);
-    if (ordered) {
-        hipLaunchKernelGGL(k_tile_work<DB>, dim3((grid + 4 * kTilesPerWave - 1) / (4 * kTilesPerWave)), dim3(256), 0, stream, a, grid);
-        if (D == 2 && !COUNT && a.algo == 0 && takes_dense_order(a.n, D)) a.dense_class = dense_class_for(a.k_list);
-        hipLaunchKernelGGL(k_tile_rank, dim3((grid + 255) / 256), dim3(256), 0, stream, a.tile_order, grid, a.dense_class,
-                           a.dense_class > 0 ? a.work_count + 1 : nullptr);
-    } else {
-        a.tile_order = nullptr;
+    const bool leaf = D == 2 && takes_dense_order(a.n, D);             // the dense tiles the leaf kernel's
+    if (!LOWER) {
+        if (!(a.bin_idx && grid > 1024)) a.tile_order = nullptr;       // a few waves per SIMD: nothing to reorder
+        else if (D <= kClustersMaxD && !COUNT && a.algo == 0) a.dense_class = leaf ? dense_class_for(a.k_list) : clusters_class_for(a.n, D, a.k_list);
     }
+    const bool clusters = a.dense_class > 0 && !leaf;                  // all tiles the group kernel's, perhaps
+    if (!LOWER && a.tile_order) {
+        const TileShare share{a.dense_class, clusters ? (grid < 2048 ? 4 : grid / 512) : 0, a.dense_class > 0 ? a.work_count + 1 : nullptr};
+        const int blocks = (grid + 4 * kTilesPerWave - 1) / (4 * kTilesPerWave);
+        const GroupTree tree = group_tree<D>(a.work_list, a.n);
+        hipLaunchKernelGGL((k_tile_work<D, DB>), dim3(blocks + (clusters ? (tree.n_leaf + 3) / 4 : 0)), dim3(256), 0, stream, a, grid, blocks);
+        hipLaunchKernelGGL(k_tile_rank<D>, dim3((grid + 255) / 256 + (clusters ? (tree.n_node + 3) / 4 : 0)), dim3(256), 0, stream, a.tile_order,
+                           grid, share, tree);
+    }
+    if (clusters) (void)launch_query_clusters(a, stream);
     if constexpr (D == 2 && !COUNT) {
-        if (a.dense_class > 0) launch_leaf_pass<D, LOWER>(a, stream);
+        if (a.dense_class > 0 && leaf) launch_leaf_pass<D, LOWER>(a, stream);
     }
     const int32_t cap = a.k_list;
     if (cap <= 16) {

@@ -581,7 +581,7 @@ __device__ __forceinline__ void tile_body(const QueryArgs& a, const int32_t tile
     write_tile_rows<KC>(a, best, lds64, my_row, valid, asks, cap, mask, (uint32_t)(R + 1));
 }
 
-// Tiles of class a.dense_class and above, which are the first of the order: counted by k_tile_rank, in the word after the
+// Tiles that another kernel takes, the first of the order: written by k_tile_rank (with a.dense_class), in the word after the
 // hand-over counter.
 __device__ __forceinline__ int32_t dense_tiles(const QueryArgs& a) { return a.work_count[1]; }
 
@@ -595,11 +595,12 @@ __global__ void __launch_bounds__(kQueryBlock) __attribute__((amdgpu_waves_per_e
 k_query_tile_sorted(QueryArgs a)
 {
     extern __shared__ uint64_t lds64[];
+    if (blockIdx.x == 0 && threadIdx.x == 0) *a.work_count = 0;      // counted after this kernel
     // an entry of the order: the tile, heaviest first, and above it the flag of an uneven tile
     const int32_t entry = a.tile_order ? a.tile_order[blockIdx.x] : (int32_t)blockIdx.x;
     const int32_t tile = entry & ((1 << kOrderFlagBit) - 1);
-    if constexpr (D == 2) {
-        if (a.dense_class > 0 && (int32_t)blockIdx.x < dense_tiles(a)) {      // the leaf kernel has taken it
+    if constexpr (D <= kClustersMaxD && !COUNT) {
+        if (a.dense_class > 0 && (int32_t)blockIdx.x < dense_tiles(a)) {      // the leaf or the group kernel's
             if (threadIdx.x == 0) a.handed[tile] = 0;
             return;
         }

@@ -1,0 +1,83 @@
+"""More than 65,536 points, up to five dimensions: whether the tile kernel or the group kernel serves a call is decided on the device from
+the tiles' work estimates.  Both outcomes, with their passes and flags, against the two kernels asked for by name."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2511_10442_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def cloud(kind, n, d):
+    rng = np.random.Generator(np.random.PCG64(n + d))
+    x = rng.random((n, d))
+    if kind == "clusters": x = x[:40][rng.integers(0, 40, size=n)] + 0.01 * rng.standard_normal((n, d))
+    if kind == "spot": x[: n // 50] = 0.3 + 0.004 * x[: n // 50]
+    if kind == "copies": x = x[rng.integers(0, n // 300, size=n)]
+    return np.ascontiguousarray(x[rng.permutation(n)].astype(np.float32))
+
+
+# the smallest size that is ranked and one above the last full tile; both passes of a long list; the largest size of the group kernel in
+# three dimensions and the first beyond it
+@pytest.mark.parametrize("kind", ["uniform", "clusters", "spot", "copies"])
+@pytest.mark.parametrize("n,d,k", [(65_537, 2, 9), (65_600, 3, 100), (70_001, 4, 65), (81_920, 4, 24), (100_003, 5, 20), (1 << 17, 3, 16), ((1 << 17) + 1, 3, 16)])
+def test_either_kernel(kind, n, d, k):
+    x = cloud(kind, n, d)
+    rs = np.array([0, n // 3, n // 3, n // 3 + 7, n], dtype=np.int32)
+    xt, rt = torch.from_numpy(x).to(DEV), torch.from_numpy(rs).to(DEV)
+    bn = B.fg_bin_points(xt, rt, k)
+    ref = B.fg_query_binned(bn, rt, k, algo=4 if kind != "copies" else 5)
+    for _ in range(3):                                    # the counters of one call are cleared for the next
+        got = B.fg_query_binned(bn, rt, k)
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+    flags = torch.from_numpy(np.random.Generator(np.random.PCG64(k)).integers(0, 4, size=n).astype(np.int32)).to(DEV)
+    ref = B.fg_query_binned(bn, rt, k, direction=flags, algo=5)
+    got = B.fg_query_binned(bn, rt, k, direction=flags)
+    assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+    got = B.fg_query_binned(bn, rt, k)
+    rows = np.linspace(0, n - 1, 25).astype(np.int64)
+    oi, od = oracle.knn_rows(x, rs, k, rows)
+    assert np.array_equal(got[0].cpu().numpy()[rows], oi) and np.array_equal(got[1].cpu().numpy()[rows].view(np.uint32), od.view(np.uint32))
+
+
+# clusters, on which the tile kernel alone takes 1.6 to 6 times as long; uniform points, on which the group kernel takes twice as long
+@pytest.mark.parametrize("kind,n,d,k", [("clusters", 100_000, 4, 20), ("clusters", 100_000, 5, 20), ("uniform", 100_000, 3, 20), ("uniform", 100_000, 2, 20)])
+def test_takes_the_faster_one(kind, n, d, k):
+    xt = torch.from_numpy(cloud(kind, n, d)).to(DEV)
+    rt = torch.tensor([0, n], dtype=torch.int32, device=DEV)
+    bn = B.fg_bin_points(xt, rt, k)
+    idx, d2 = torch.empty((n, k), dtype=torch.int32, device=DEV), torch.empty((n, k), device=DEV)
+    best = {a: float("inf") for a in (0, 4, 5)}
+    for _ in range(8):
+        for a in best:
+            p, q = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            p.record()
+            B.fg_query_binned(bn, rt, k, idx, d2, algo=a)
+            q.record()
+            torch.cuda.synchronize()
+            best[a] = min(best[a], p.elapsed_time(q))
+    assert best[0] <= 1.4 * min(best[4], best[5]), best
+
+
+# a captured graph of the whole call: every replay against the eager result, with eager work between
+def test_captured():
+    n, k = 70_000, 12
+    xt = torch.from_numpy(cloud("clusters", n, 4)).to(DEV)
+    rt = torch.tensor([0, n], dtype=torch.int32, device=DEV)
+    ws = B.alloc_workspace(n, 4, 1, k)
+    idx, d2 = torch.empty((n, k), dtype=torch.int32, device=DEV), torch.empty((n, k), device=DEV)
+    ref = [t.clone() for t in B.fg_binned_select_knn(xt, rt, k, workspace=ws, out_idx=idx, out_d2=d2)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.fg_binned_select_knn(xt, rt, k, workspace=ws, out_idx=idx, out_d2=d2)
+    for _ in range(3):
+        idx.fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(idx, ref[0]) and torch.equal(d2, ref[1])
+        got = B.fg_binned_select_knn(xt, rt, k, workspace=ws)
+        assert torch.equal(got[0], ref[0])
