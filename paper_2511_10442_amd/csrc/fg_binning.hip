@@ -399,10 +399,9 @@ constexpr int32_t kFewSplits = 1024;
 // d = 5 29.7 / 23.0, d = 10 29.0 / 24.6; of 32,000 27.2 / 21.2, 28.6 / 24.2, 30.4 / 30.5 (fg_knn_backward, which bins for itself: d = 3 42.7 / 43.2).
 // 16 splits of 1250 points 31 to 41 / 13 (the caller's own 12 us a call); 200 of 100 38 to 52 / 13.
 // A split may hold all the points, so their number is bounded, too (and positions in a split fit 16 bits).
-constexpr int32_t kFewN = 49152;
 inline bool bins_in_one_launch(int32_t n, int32_t d, int32_t n_segments, int32_t cells_per_segment)
 {
-    return n <= kFewN && n_segments <= kFewSplits && cells_per_segment <= kFewCells && (int64_t)n * (d + 8) <= (int64_t)n_segments * 327680;
+    return few_points(n, d, n_segments) && n_segments <= kFewSplits && cells_per_segment <= kFewCells;
 }
 
 template <int DB>

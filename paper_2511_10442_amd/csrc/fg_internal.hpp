@@ -41,6 +41,8 @@ struct QueryArgs {
     int32_t dense_class;       // > 0: tiles of this work class and above decide which are not the tile kernel's (the first work_count[1] of the order)
     int32_t few_ask;           // leaf kernel: tiles of which no more queries than this ask (direction flags) are handed over
     const float* coords;       // [n][d] the points in their original order: given (and rec not) where nothing was binned, else nullptr
+    const int32_t* votes;      // few tiles, which are not ranked: as many of them are of dense_class and above; votes_for of them and all are the group kernel's
+    int32_t votes_for;
 };
 
 struct OrderArgs;
@@ -88,6 +90,10 @@ inline bool takes_group_kernel(int64_t n, int32_t d, int32_t n_segments, int32_t
     if ((d == 4 || d == 5) && n <= (int64_t)n_segments * 16384) most *= 2;
     return n <= most && !(n <= 8192 && d <= 3 && k < 16);
 }
+
+// Few points: binned in one launch before the scatter (figures in fg_binning.hip), and the query stage asks for the tiles' votes.
+constexpr int32_t kFewN = 49152;
+inline bool few_points(int64_t n, int32_t d, int32_t n_segments) { return n <= kFewN && n * (d + 8) <= (int64_t)n_segments * 327680; }
 
 // Two dimensions and many points: the densest tiles are the leaf kernel's (dense_class_for), and the points of dense cells are
 // ordered for it when they are binned.  (Ordered in three to five dimensions, too, the kernels that search by boxes gained 0 to 5 %

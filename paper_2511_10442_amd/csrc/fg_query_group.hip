@@ -254,7 +254,7 @@ __device__ __forceinline__ void group_queries(const QueryArgs& a, const GroupTre
                 const int32_t i = node64 + lane;
                 node64 += 64;
                 nodes = __ballot(i <= nb);
-                if (nb - na > 1) {
+                if (nb - na > 1 && !a.votes) {                         // (with votes the nodes have no boxes)
                     measure(tree.node, min(i, nb));
                     uint64_t hit = 0;
 #pragma unroll
@@ -357,7 +357,7 @@ __device__ __forceinline__ void group_queries(const QueryArgs& a, const GroupTre
     }
 }
 
-// With a.dense_class the tiles that k_tile_rank gave to this kernel, all or none, in their order; the workgroups take groups in turn,
+// With a.dense_class only if the tiles are this kernel's, all or none; ranked tiles in their order, of which the workgroups take groups in turn,
 // and those of a tile meet in one XCD's L2 (workgroups are dealt round robin to 8).
 template <int D, int Q, bool LOWER>
 __global__ void __launch_bounds__(kQueryBlock)
@@ -365,8 +365,10 @@ k_query_group(QueryArgs a, GroupTree tree)
 {
     constexpr int kPerTile = kQueryBlock / Q;
     __shared__ uint64_t pend[Q][kGroupPend];
-    const bool ranked = D <= kClustersMaxD && a.dense_class > 0;
-    const int32_t count = ranked ? dense_tiles(a) : 0, rounds = (count + 7) >> 3;
+    const bool asked = D <= kClustersMaxD && a.dense_class > 0, ranked = asked && !a.votes;
+    const int32_t count = asked ? dense_tiles(a) : 0;
+    if (asked && count == 0) return;
+    const int32_t rounds = ranked ? (count + 7) >> 3 : 0;
     const int32_t groups = ranked ? rounds * 8 * kPerTile : (int32_t)gridDim.x;
     // heaviest tiles first, and whoever has the first of one round has the last of the next
     for (int32_t round = 0; round * (int32_t)gridDim.x < groups; ++round) {

@@ -60,7 +60,13 @@ __device__ __forceinline__ int32_t tile_class(int32_t work)
     return c < kTileClasses ? c : kTileClasses - 1;
 }
 
-constexpr int kTilesPerWave = 16;
+constexpr int kTilesPerWave = 16, kTilesPerWaveFew = 8;      // the second up to kFewTiles tiles: one round of the chain of loads instead of two
+constexpr int kFewTiles = 8192;
+// Up to 1024 tiles are not ranked.  Their estimates are made all the same, to vote whether the call is the group kernel's, from kVotesMin
+// tiles on and while the points are few (few_points): two launches, 5 us of such a call's 50 to 80 on uniform points, against a third or a
+// sixth of its time on clusters (30k points: mixture, d = 3, K = 12 275 / 130 us; showers in 16 splits 570 / 86).  From there to 65,536
+// points uniform calls would be 6 to 12 us slower, 8 % (60k, d = 2, K = 16 66 / 72; d = 4, K = 20 170 / 182); clusters would gain as much.
+constexpr int kVotesMin = 256;
 
 // How many tiles, the first of the order, another kernel takes: those of dense_class and above, or, with all_from > 0, all if so many
 // are of it, else none.
@@ -102,7 +108,7 @@ __device__ __forceinline__ int32_t oct_sum_i32(int32_t v)
 // (of its leaves, those of k_tile_rank of its nodes; ranking the tiles here, too, by the last block to finish, took longer than the launch
 // that it saves: 100k points 18 us against 7 and 7).
 template <int D, int DB>
-static __global__ void __launch_bounds__(256) k_tile_work(QueryArgs a, int32_t n_tiles, int32_t blocks)
+static __global__ void __launch_bounds__(256) k_tile_work(QueryArgs a, int32_t n_tiles, int32_t blocks, int32_t tiles_per_wave)
 {
     if constexpr (D <= kClustersMaxD) {
         if ((int32_t)blockIdx.x >= blocks) {
@@ -117,11 +123,11 @@ static __global__ void __launch_bounds__(256) k_tile_work(QueryArgs a, int32_t n
     __syncthreads();
     const int lane = threadIdx.x & 63;
     const int sample = lane & (kTileSamples - 1);
-    const int32_t wave_t0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kTilesPerWave;
+    const int32_t wave_t0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * tiles_per_wave;
     int32_t ncols = 1;
 #pragma unroll
     for (int c = 0; c < DB - 1; ++c) ncols *= 3;
-    for (int32_t tb = wave_t0; tb < wave_t0 + kTilesPerWave; tb += kQueryBlock / kTileSamples) {
+    for (int32_t tb = wave_t0; tb < wave_t0 + tiles_per_wave; tb += kQueryBlock / kTileSamples) {
         const int32_t t = tb + (lane >> 3);
         const int32_t p = t * kQueryBlock + sample * 9;            // queries 0, 9, ..., 63 of the tile
         const bool live = t < n_tiles && p < a.n;
@@ -204,8 +210,10 @@ static __global__ void __launch_bounds__(256) k_tile_work(QueryArgs a, int32_t n
         }
     }
     __syncthreads();
-    if (threadIdx.x < kTileClasses && hist[threadIdx.x] > 0)
-        atomicAdd(&a.tile_order[2 * n_tiles + threadIdx.x], hist[threadIdx.x]);
+    if (threadIdx.x < kTileClasses && hist[threadIdx.x] > 0) {
+        if (!a.votes) atomicAdd(&a.tile_order[2 * n_tiles + threadIdx.x], hist[threadIdx.x]);
+        else if ((int32_t)threadIdx.x >= a.dense_class) atomicAdd(const_cast<int32_t*>(a.votes), hist[threadIdx.x]);
+    }
 }
 
 // Position of every tile: classes in descending order; inside a class roughly the bin order (blocks of 256
@@ -300,8 +308,10 @@ template <int D, int DB, bool COUNT>
 static void launch_handed(const QueryArgs& a, hipStream_t stream)
 {
     const int grid = (a.n + kQueryBlock - 1) / kQueryBlock;
+    const bool last = a.slot0 + a.k_list >= a.k - 1;                  // pass of a long list
+    int32_t* const counters = a.tile_order ? a.tile_order + 2 * grid : (a.votes ? const_cast<int32_t*>(a.votes) - kTileClasses : nullptr);
     hipLaunchKernelGGL(k_list_compact, dim3((grid + 1023) / 1024), dim3(1024), 0, stream, a.handed, grid, a.work_list, a.work_count,
-                       a.tile_order ? a.tile_order + 2 * grid : nullptr);
+                       last ? counters : nullptr);
     // one query per wavefront; four times the wave slots of the chip: the queries differ widely in cost, and with
     // more, shorter workgroups the hardware dispatcher evens them out (cursors in memory cost more than they gained)
     const int list_grid = a.n < 32768 ? a.n : 32768;
@@ -316,19 +326,29 @@ static void launch_query_pass(QueryArgs& a, hipStream_t stream)
 {
     const int grid = (a.n + kQueryBlock - 1) / kQueryBlock;
     const bool leaf = D == 2 && takes_dense_order(a.n, D);             // the dense tiles the leaf kernel's
-    if (!LOWER) {
-        if (!(a.bin_idx && grid > 1024)) a.tile_order = nullptr;       // a few waves per SIMD: nothing to reorder
-        else if (D <= kClustersMaxD && !COUNT && a.algo == 0) a.dense_class = leaf ? dense_class_for(a.k_list) : clusters_class_for(a.n, D, a.k_list);
-    }
+    int32_t* const order = a.tile_order;
+    if (!LOWER && D <= kClustersMaxD && !COUNT && a.algo == 0 && a.bin_idx && (grid > 1024 || (grid > kVotesMin && few_points(a.n, D, a.n_segments))))
+        a.dense_class = leaf ? dense_class_for(a.k_list) : clusters_class_for(a.n, D, a.k_list);
+    const bool ranked = a.bin_idx && grid > 1024;                      // else a few waves per SIMD: nothing to reorder
     const bool clusters = a.dense_class > 0 && !leaf;                  // all tiles the group kernel's, perhaps
-    if (!LOWER && a.tile_order) {
-        const TileShare share{a.dense_class, clusters ? (grid < 2048 ? 4 : grid / 512) : 0, a.dense_class > 0 ? a.work_count + 1 : nullptr};
-        const int blocks = (grid + 4 * kTilesPerWave - 1) / (4 * kTilesPerWave);
-        const GroupTree tree = group_tree<D>(a.work_list, a.n);
-        hipLaunchKernelGGL((k_tile_work<D, DB>), dim3(blocks + (clusters ? (tree.n_leaf + 3) / 4 : 0)), dim3(256), 0, stream, a, grid, blocks);
-        hipLaunchKernelGGL(k_tile_rank<D>, dim3((grid + 255) / 256 + (clusters ? (tree.n_node + 3) / 4 : 0)), dim3(256), 0, stream, a.tile_order,
-                           grid, share, tree);
+    const int32_t all_from = clusters ? (grid < 2048 ? 4 : grid / 512) : 0;
+    if (!LOWER && clusters && !ranked) {
+        a.votes = order + 2 * grid + kTileClasses;                     // a cursor that nothing else uses then
+        a.votes_for = all_from;
     }
+    if (!LOWER && (ranked || clusters)) {
+        const int per_wave = grid <= kFewTiles ? kTilesPerWaveFew : kTilesPerWave;
+        const int blocks = (grid + 4 * per_wave - 1) / (4 * per_wave);
+        const GroupTree tree = group_tree<D>(a.work_list, a.n);
+        hipLaunchKernelGGL((k_tile_work<D, DB>), dim3(blocks + (clusters ? (tree.n_leaf + 3) / 4 : 0)), dim3(256), 0, stream, a, grid,
+                           blocks, per_wave);
+        if (ranked) {
+            const TileShare share{a.dense_class, all_from, a.dense_class > 0 ? a.work_count + 1 : nullptr};
+            hipLaunchKernelGGL(k_tile_rank<D>, dim3((grid + 255) / 256 + (clusters ? (tree.n_node + 3) / 4 : 0)), dim3(256), 0, stream, order,
+                               grid, share, tree);
+        }
+    }
+    if (!ranked) a.tile_order = nullptr;
     if (clusters) (void)launch_query_clusters(a, stream);
     if constexpr (D == 2 && !COUNT) {
         if (a.dense_class > 0 && leaf) launch_leaf_pass<D, LOWER>(a, stream);

@@ -576,14 +576,21 @@ __device__ __forceinline__ void tile_body(const QueryArgs& a, const int32_t tile
     // kernel with unrelated queries); their lists so far leave with the finished rows, and the first shell still
     // to search travels in slot 0 of the distance row
     const uint64_t mask = __ballot(active);
-    if (lane == 0) a.handed[tile] = mask;
+    if (lane == 0) {
+        a.handed[tile] = mask;
+        if (tile == 0) *a.work_count = 0;                     // counted after this kernel
+    }
     if (COUNT && valid) a.out_cand[my_row] = LOWER ? a.out_cand[my_row] + cand : cand;
     write_tile_rows<KC>(a, best, lds64, my_row, valid, asks, cap, mask, (uint32_t)(R + 1));
 }
 
-// Tiles that another kernel takes, the first of the order: written by k_tile_rank (with a.dense_class), in the word after the
-// hand-over counter.
-__device__ __forceinline__ int32_t dense_tiles(const QueryArgs& a) { return a.work_count[1]; }
+// Tiles that another kernel takes (with a.dense_class), the first of the order: written by k_tile_rank, in the word after the
+// hand-over counter; or, where they are not ranked, all or none by the votes of k_tile_work.
+__device__ __forceinline__ int32_t dense_tiles(const QueryArgs& a)
+{
+    if (a.votes) return *a.votes >= a.votes_for ? 0x7fffffff : 0;
+    return a.work_count[1];
+}
 
 // The kernel: one workgroup of one wavefront per tile.  Tiles the ordering kernels marked as uneven take the
 // flattened scan, all others, and every tile of an unordered launch, the direct one.  One kernel with a branch,
@@ -595,14 +602,18 @@ __global__ void __launch_bounds__(kQueryBlock) __attribute__((amdgpu_waves_per_e
 k_query_tile_sorted(QueryArgs a)
 {
     extern __shared__ uint64_t lds64[];
-    if (blockIdx.x == 0 && threadIdx.x == 0) *a.work_count = 0;      // counted after this kernel
     // an entry of the order: the tile, heaviest first, and above it the flag of an uneven tile
     const int32_t entry = a.tile_order ? a.tile_order[blockIdx.x] : (int32_t)blockIdx.x;
     const int32_t tile = entry & ((1 << kOrderFlagBit) - 1);
     if constexpr (D <= kClustersMaxD && !COUNT) {
-        if (a.dense_class > 0 && (int32_t)blockIdx.x < dense_tiles(a)) {      // the leaf or the group kernel's
-            if (threadIdx.x == 0) a.handed[tile] = 0;
-            return;
+        if (__builtin_expect(a.dense_class > 0, 0)) {
+            if ((int32_t)blockIdx.x < dense_tiles(a)) {          // the leaf or the group kernel's
+                if (threadIdx.x == 0) {
+                    a.handed[tile] = 0;
+                    if (tile == 0) *a.work_count = 0;
+                }
+                return;
+            }
         }
     }
     if constexpr (!COUNT && tile_has_flat<KC, D>()) {
