@@ -62,22 +62,25 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
-// One block per chunk of kBboxChunk consecutive points.  A chunk that lies inside one row split
+// One block per chunk of kBlock * items consecutive points.  A chunk that lies inside one row split
 // (the common case) is reduced in registers, then across the wave, then across the block, and
 // issues one atomic pair per dimension; a chunk straddling a split boundary falls back to
 // one pair per wavefront, split and dimension, or per lane.  Same-address atomics serialise, so their number matters.
-constexpr int kBboxItems = 4;     // few points per thread: the launch needs well over 256 blocks to keep loads in flight
-constexpr int kBboxChunk = kBlock * kBboxItems;
+// Few points per thread: the launch needs well over 256 blocks to keep loads in flight; but every block of a row split adds to the
+// queue at its keys (some 20 ns each: 5M points of one split, 4883 blocks, 98 us), so no more than some kBboxBlocks a split
+// (fg_bin_points of 5M uniform points, d = 3, 459 -> 380 us, of 1M, d = 5, 111 -> 98.5).
+constexpr int kBboxItems = 4, kBboxMostItems = 64;
+constexpr int kBboxBlocks = 384;
 constexpr int kBboxSplits = 24;   // more row splits than this in a wavefront's 64 points: atomics per lane
 
 template <int DB>
 __global__ void __launch_bounds__(kBlock)
 k_bbox(const float* __restrict__ coords, const int32_t* __restrict__ row_splits, int32_t n, int32_t d,
-       int32_t n_segments, uint32_t* __restrict__ bbox_keys)
+       int32_t n_segments, int32_t items, uint32_t* __restrict__ bbox_keys)
 {
     __shared__ float red[2][kBlock / 64][DB];
-    const int64_t base = (int64_t)blockIdx.x * kBboxChunk;
-    const int32_t last = (int32_t)(base + kBboxChunk < n ? base + kBboxChunk : n) - 1;
+    const int64_t base = (int64_t)blockIdx.x * kBlock * items, end = base + (int64_t)kBlock * items;
+    const int32_t last = (int32_t)(end < n ? end : n) - 1;
     uint32_t* kmin = bbox_keys;
     uint32_t* kmax = bbox_keys + (int64_t)n_segments * DB * kKeyStride;
     const int32_t s_first = segment_of(row_splits, n_segments, (int32_t)base);
@@ -86,9 +89,10 @@ k_bbox(const float* __restrict__ coords, const int32_t* __restrict__ row_splits,
         float mn[DB], mx[DB];
 #pragma unroll
         for (int c = 0; c < DB; ++c) { mn[c] = 3.4028235e38f; mx[c] = -3.4028235e38f; }
-        for (int it = 0; it < kBboxItems; ++it) {
-            const int64_t i = base + it * kBlock + threadIdx.x;
-            if (i <= last) {
+        for (int it0 = 0; it0 < items; it0 += kBboxItems) {
+#pragma unroll
+            for (int it = 0; it < kBboxItems; ++it) {
+                const int64_t at = base + (it0 + it) * kBlock + threadIdx.x, i = at <= last ? at : last;     // past the end: the last point once more
 #pragma unroll
                 for (int c = 0; c < DB; ++c) {
                     const float x = coords[i * d + c];
@@ -114,8 +118,9 @@ k_bbox(const float* __restrict__ coords, const int32_t* __restrict__ row_splits,
         }
         return;
     }
-    for (int it = 0; it < kBboxItems; ++it) {
+    for (int it = 0; it < items; ++it) {
         const int64_t i = base + it * kBlock + threadIdx.x;
+        if (i - (threadIdx.x & 63) > last) break;                     // nothing for the wavefront
         const bool live = i <= last;
         const int32_t ii = live ? (int32_t)i : last;
         const int32_t s = segment_of(row_splits, n_segments, ii);     // dead lanes repeat the chunk's last point: harmless
@@ -523,9 +528,14 @@ static void launch_bbox_assign(bool assign, const float* coords, const int32_t* 
                                float* geom, int32_t* bin_idx, int32_t* rank, int32_t* counters,
                                hipStream_t stream)
 {
-    if (!assign)
-        hipLaunchKernelGGL(k_bbox<DB>, dim3((unsigned)(((int64_t)n + kBboxChunk - 1) / kBboxChunk)), dim3(kBlock), 0, stream, coords,
-                           row_splits, n, d, n_segments, bbox_keys);
+    if (!assign) {
+        const int64_t full = (int64_t)n_segments * kBboxBlocks * kBlock * kBboxItems;
+        const int64_t items = kBboxItems * (((int64_t)n + full - 1) / full);
+        const int32_t per = items < kBboxMostItems ? (int32_t)items : kBboxMostItems;
+        const int64_t chunk = (int64_t)kBlock * per;
+        hipLaunchKernelGGL(k_bbox<DB>, dim3((unsigned)(((int64_t)n + chunk - 1) / chunk)), dim3(kBlock), 0, stream, coords,
+                           row_splits, n, d, n_segments, per, bbox_keys);
+    }
     else
         hipLaunchKernelGGL(k_assign<DB>, dim3((unsigned)(((int64_t)n + kAssignChunk - 1) / kAssignChunk)), dim3(kBlock), 0, stream, coords,
                            row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, morton_bits, bbox_keys, geom,

@@ -66,3 +66,18 @@ def test_cells_bounds_and_records(sizes, d, nb, db, kind):
     torch.cuda.synchronize()
     ref, asum = oracle.knn_backward(g, idx, x)
     assert np.all(np.abs(grad.cpu().numpy() - ref) <= 1e-5 * np.maximum(np.abs(ref), asum) + 1e-30)
+
+
+# the bounding boxes of many points: more points a thread from 393,216 a row split on, chunks that end in the middle of a wavefront and
+# straddle a split
+@pytest.mark.parametrize("sizes", [[393_216], [393_217], [800_001], [500_000, 0, 7, 1_000_100]])
+@pytest.mark.parametrize("d", [2, 5])
+def test_boxes_of_many_points(sizes, d):
+    n = sum(sizes)
+    x, rs = W.uniform(n, d, seed=n, sizes=sizes)
+    x[n - 1] = 2.0
+    x[rs[-2]] = -1.0                                     # first and last point of the last split hold its box
+    bn = B.fg_bin_points(torch.from_numpy(x).to(DEV), torch.from_numpy(rs).to(DEV), 12)
+    torch.cuda.synchronize()
+    cells, _ = expected_cells(x, rs, bn.n_bins, bn.d_bin, bn.sub_bins)
+    assert np.array_equal(bn.bin_idx.cpu().numpy(), cells)
