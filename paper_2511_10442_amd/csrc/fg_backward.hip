@@ -302,26 +302,28 @@ k_backward_tiled(const float* __restrict__ grad_d2, const int32_t* __restrict__ 
 }
 
 template <int D>
-static void launch_bwd_tiled(const float* grad_d2, const int32_t* idx, const float* coords, const float4* coords4,
+static hipError_t launch_bwd_tiled(const float* grad_d2, const int32_t* idx, const float* coords, const float4* coords4,
                              const int32_t* perm, int32_t perm_stride, int32_t n, int32_t k, float* grad_coords,
                              hipStream_t stream)
 {
     unsigned grid = (unsigned)(((int64_t)n + bwd_rows<D>() - 1) / bwd_rows<D>());
     if (((uintptr_t)coords % 16) == 0)
-        hipLaunchKernelGGL((k_backward_tiled<D, true>), dim3(grid), dim3(bwd_block<D>()), 0, stream, grad_d2, idx, coords,
-                           coords4, perm, perm_stride, n, k, grad_coords);
+        FG_LAUNCH((k_backward_tiled<D, true>), dim3(grid), dim3(bwd_block<D>()), 0, stream, grad_d2, idx, coords,
+                  coords4, perm, perm_stride, n, k, grad_coords);
     else
-        hipLaunchKernelGGL((k_backward_tiled<D, false>), dim3(grid), dim3(bwd_block<D>()), 0, stream, grad_d2, idx, coords,
-                           coords4, perm, perm_stride, n, k, grad_coords);
+        FG_LAUNCH((k_backward_tiled<D, false>), dim3(grid), dim3(bwd_block<D>()), 0, stream, grad_d2, idx, coords,
+                  coords4, perm, perm_stride, n, k, grad_coords);
+    return hipSuccess;
 }
 
 template <int D>
-static void launch_bwd(const float* grad_d2, const int32_t* idx, const float* coords, int32_t n, int32_t k,
+static hipError_t launch_bwd(const float* grad_d2, const int32_t* idx, const float* coords, int32_t n, int32_t k,
                        float* grad_coords, hipStream_t stream)
 {
     int64_t threads = (int64_t)n * kLanesPerRow;
     unsigned grid = (unsigned)((threads + kBwdBlock - 1) / kBwdBlock);
-    hipLaunchKernelGGL(k_backward<D>, dim3(grid), dim3(kBwdBlock), 0, stream, grad_d2, idx, coords, n, k, grad_coords);
+    FG_LAUNCH(k_backward<D>, dim3(grid), dim3(kBwdBlock), 0, stream, grad_d2, idx, coords, n, k, grad_coords);
+    return hipSuccess;
 }
 
 hipError_t launch_backward(const float* grad_d2, const int32_t* idx, const float* coords, const float* coords4,
@@ -332,36 +334,34 @@ hipError_t launch_backward(const float* grad_d2, const int32_t* idx, const float
         int64_t total = (int64_t)n * d;
         int64_t grid = (total + kBwdBlock - 1) / kBwdBlock;
         if (grid > 4096) grid = 4096;
-        hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)grid), dim3(kBwdBlock), 0, stream, grad_coords, total);
+        FG_LAUNCH(k_fill_zero, dim3((unsigned)grid), dim3(kBwdBlock), 0, stream, grad_coords, total);
     }
     if (perm) {
         switch (d) {
-            case 2: launch_bwd_tiled<2>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream); break;
-            case 3: launch_bwd_tiled<3>(grad_d2, idx, coords, reinterpret_cast<const float4*>(coords4), perm, perm_stride, n, k, grad_coords, stream); break;
-            case 4: launch_bwd_tiled<4>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream); break;
-            case 5: launch_bwd_tiled<5>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream); break;
-            case 6: launch_bwd_tiled<6>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream); break;
-            case 7: launch_bwd_tiled<7>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream); break;
-            case 8: launch_bwd_tiled<8>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream); break;
-            case 9: launch_bwd_tiled<9>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream); break;
-            case 10: launch_bwd_tiled<10>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream); break;
+            case 2: return launch_bwd_tiled<2>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream);
+            case 3: return launch_bwd_tiled<3>(grad_d2, idx, coords, reinterpret_cast<const float4*>(coords4), perm, perm_stride, n, k, grad_coords, stream);
+            case 4: return launch_bwd_tiled<4>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream);
+            case 5: return launch_bwd_tiled<5>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream);
+            case 6: return launch_bwd_tiled<6>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream);
+            case 7: return launch_bwd_tiled<7>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream);
+            case 8: return launch_bwd_tiled<8>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream);
+            case 9: return launch_bwd_tiled<9>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream);
+            case 10: return launch_bwd_tiled<10>(grad_d2, idx, coords, nullptr, perm, perm_stride, n, k, grad_coords, stream);
             default: return hipErrorInvalidValue;
         }
-        return hipGetLastError();
     }
     switch (d) {
-        case 2: launch_bwd<2>(grad_d2, idx, coords, n, k, grad_coords, stream); break;
-        case 3: launch_bwd<3>(grad_d2, idx, coords, n, k, grad_coords, stream); break;
-        case 4: launch_bwd<4>(grad_d2, idx, coords, n, k, grad_coords, stream); break;
-        case 5: launch_bwd<5>(grad_d2, idx, coords, n, k, grad_coords, stream); break;
-        case 6: launch_bwd<6>(grad_d2, idx, coords, n, k, grad_coords, stream); break;
-        case 7: launch_bwd<7>(grad_d2, idx, coords, n, k, grad_coords, stream); break;
-        case 8: launch_bwd<8>(grad_d2, idx, coords, n, k, grad_coords, stream); break;
-        case 9: launch_bwd<9>(grad_d2, idx, coords, n, k, grad_coords, stream); break;
-        case 10: launch_bwd<10>(grad_d2, idx, coords, n, k, grad_coords, stream); break;
+        case 2: return launch_bwd<2>(grad_d2, idx, coords, n, k, grad_coords, stream);
+        case 3: return launch_bwd<3>(grad_d2, idx, coords, n, k, grad_coords, stream);
+        case 4: return launch_bwd<4>(grad_d2, idx, coords, n, k, grad_coords, stream);
+        case 5: return launch_bwd<5>(grad_d2, idx, coords, n, k, grad_coords, stream);
+        case 6: return launch_bwd<6>(grad_d2, idx, coords, n, k, grad_coords, stream);
+        case 7: return launch_bwd<7>(grad_d2, idx, coords, n, k, grad_coords, stream);
+        case 8: return launch_bwd<8>(grad_d2, idx, coords, n, k, grad_coords, stream);
+        case 9: return launch_bwd<9>(grad_d2, idx, coords, n, k, grad_coords, stream);
+        case 10: return launch_bwd<10>(grad_d2, idx, coords, n, k, grad_coords, stream);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 }  // namespace fg

@@ -522,7 +522,7 @@ k_scatter(const float* __restrict__ coords, int32_t n, const int32_t* __restrict
 }
 
 template <int DB>
-static void launch_bbox_assign(bool assign, const float* coords, const int32_t* row_splits, int32_t n, int32_t d,
+static hipError_t launch_bbox_assign(bool assign, const float* coords, const int32_t* row_splits, int32_t n, int32_t d,
                                int32_t n_segments, int32_t n_bins, int32_t sub_shift, int32_t cells_per_segment,
                                int32_t morton_bits, uint32_t* bbox_keys,
                                float* geom, int32_t* bin_idx, int32_t* rank, int32_t* counters,
@@ -533,26 +533,28 @@ static void launch_bbox_assign(bool assign, const float* coords, const int32_t* 
         const int64_t items = kBboxItems * (((int64_t)n + full - 1) / full);
         const int32_t per = items < kBboxMostItems ? (int32_t)items : kBboxMostItems;
         const int64_t chunk = (int64_t)kBlock * per;
-        hipLaunchKernelGGL(k_bbox<DB>, dim3((unsigned)(((int64_t)n + chunk - 1) / chunk)), dim3(kBlock), 0, stream, coords,
-                           row_splits, n, d, n_segments, per, bbox_keys);
+        FG_LAUNCH(k_bbox<DB>, dim3((unsigned)(((int64_t)n + chunk - 1) / chunk)), dim3(kBlock), 0, stream, coords,
+                  row_splits, n, d, n_segments, per, bbox_keys);
     }
     else
-        hipLaunchKernelGGL(k_assign<DB>, dim3((unsigned)(((int64_t)n + kAssignChunk - 1) / kAssignChunk)), dim3(kBlock), 0, stream, coords,
-                           row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, morton_bits, bbox_keys, geom,
-                           bin_idx, rank, counters);
+        FG_LAUNCH(k_assign<DB>, dim3((unsigned)(((int64_t)n + kAssignChunk - 1) / kAssignChunk)), dim3(kBlock), 0, stream, coords,
+                  row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, morton_bits, bbox_keys, geom,
+                  bin_idx, rank, counters);
+    return hipSuccess;
 }
 
 template <int D>
-static void launch_scatter(bool rows_only, const float* coords, int32_t n, const int32_t* bin_idx, const int32_t* rank,
+static hipError_t launch_scatter(bool rows_only, const float* coords, int32_t n, const int32_t* bin_idx, const int32_t* rank,
                            const int32_t* bounds, int32_t* perm, float* rec, hipStream_t stream)
 {
     const unsigned grid = (unsigned)(((int64_t)n + kBlock - 1) / kBlock);
     if (rows_only)
-        hipLaunchKernelGGL((k_scatter<D, true>), dim3(grid), dim3(kBlock), 0, stream, coords, n, bin_idx, rank, bounds,
-                           perm, rec);
+        FG_LAUNCH((k_scatter<D, true>), dim3(grid), dim3(kBlock), 0, stream, coords, n, bin_idx, rank, bounds,
+                  perm, rec);
     else
-        hipLaunchKernelGGL((k_scatter<D, false>), dim3(grid), dim3(kBlock), 0, stream, coords, n, bin_idx, rank, bounds,
-                           perm, rec);
+        FG_LAUNCH((k_scatter<D, false>), dim3(grid), dim3(kBlock), 0, stream, coords, n, bin_idx, rank, bounds,
+                  perm, rec);
+    return hipSuccess;
 }
 
 hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_t n, int32_t d,
@@ -565,8 +567,8 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
     const int32_t n_keys = n_segments * d_bin;
     const int32_t cells_per_segment = (int32_t)(total_bins / n_segments);
     if (!order && bins_in_one_launch(n, d, n_segments, cells_per_segment)) {
-#define FG_FEW(DB) hipLaunchKernelGGL(k_bin_few<DB>, dim3(n_segments), dim3(kFewThreads), (size_t)(cells_per_segment + 1) / 2 * 4, stream, coords, \
-                                      row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, morton_bits, geom, bin_idx, rank, bounds, tile_counters)
+#define FG_FEW(DB) FG_LAUNCH(k_bin_few<DB>, dim3(n_segments), dim3(kFewThreads), (size_t)(cells_per_segment + 1) / 2 * 4, stream, coords, \
+                             row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, morton_bits, geom, bin_idx, rank, bounds, tile_counters)
         switch (d_bin) {
             case 2: FG_FEW(2); break;
             case 3: FG_FEW(3); break;
@@ -580,19 +582,19 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
         int64_t work = n_counters > 2 * (int64_t)n_keys ? n_counters : 2 * (int64_t)n_keys;
         int64_t grid = (work + kBlock - 1) / kBlock;
         if (grid > 4096) grid = 4096;
-        hipLaunchKernelGGL(k_prepare, dim3((unsigned)grid), dim3(kBlock), 0, stream, bounds, n_counters, bbox_keys,
-                           n_keys, tile_counters, order ? order->counters : nullptr);
+        FG_LAUNCH(k_prepare, dim3((unsigned)grid), dim3(kBlock), 0, stream, bounds, n_counters, bbox_keys,
+                  n_keys, tile_counters, order ? order->counters : nullptr);
     }
 #define FG_DB_SWITCH(ASSIGN)                                                                                       \
     switch (d_bin) {                                                                                               \
-        case 2: launch_bbox_assign<2>(ASSIGN, coords, row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, \
-                                      morton_bits, bbox_keys, geom, bin_idx, rank, bounds, stream); break;                      \
-        case 3: launch_bbox_assign<3>(ASSIGN, coords, row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, \
-                                      morton_bits, bbox_keys, geom, bin_idx, rank, bounds, stream); break;                      \
-        case 4: launch_bbox_assign<4>(ASSIGN, coords, row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, \
-                                      morton_bits, bbox_keys, geom, bin_idx, rank, bounds, stream); break;                      \
-        case 5: launch_bbox_assign<5>(ASSIGN, coords, row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, \
-                                      morton_bits, bbox_keys, geom, bin_idx, rank, bounds, stream); break;                      \
+        case 2: FG_TRY(launch_bbox_assign<2>(ASSIGN, coords, row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, \
+                                      morton_bits, bbox_keys, geom, bin_idx, rank, bounds, stream)); break; \
+        case 3: FG_TRY(launch_bbox_assign<3>(ASSIGN, coords, row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, \
+                                      morton_bits, bbox_keys, geom, bin_idx, rank, bounds, stream)); break; \
+        case 4: FG_TRY(launch_bbox_assign<4>(ASSIGN, coords, row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, \
+                                      morton_bits, bbox_keys, geom, bin_idx, rank, bounds, stream)); break; \
+        case 5: FG_TRY(launch_bbox_assign<5>(ASSIGN, coords, row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, \
+                                      morton_bits, bbox_keys, geom, bin_idx, rank, bounds, stream)); break; \
         default: return hipErrorInvalidValue;                                                                      \
     }
     FG_DB_SWITCH(false)
@@ -600,11 +602,11 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
 #undef FG_DB_SWITCH
     {
         int64_t n_chunks = (n_counters + kScanChunk - 1) / kScanChunk;
-        hipLaunchKernelGGL(k_scan_partials, dim3((unsigned)n_chunks), dim3(kBlock), 0, stream, bounds, n_counters,
-                           scan_partials);
-        if (n_chunks > 2048) hipLaunchKernelGGL(k_scan_tops, dim3(1), dim3(kBlock), 0, stream, scan_partials, (int32_t)n_chunks);
-#define FG_APPLY(TOTALS, ORDER, COUNTERS, SMALL, LARGE) hipLaunchKernelGGL((k_scan_apply<TOTALS, ORDER>), dim3((unsigned)n_chunks), dim3(kBlock), 0, stream, \
-                                                                           bounds, n_counters, scan_partials, COUNTERS, SMALL, LARGE)
+        FG_LAUNCH(k_scan_partials, dim3((unsigned)n_chunks), dim3(kBlock), 0, stream, bounds, n_counters,
+                  scan_partials);
+        if (n_chunks > 2048) FG_LAUNCH(k_scan_tops, dim3(1), dim3(kBlock), 0, stream, scan_partials, (int32_t)n_chunks);
+#define FG_APPLY(TOTALS, ORDER, COUNTERS, SMALL, LARGE) FG_LAUNCH((k_scan_apply<TOTALS, ORDER>), dim3((unsigned)n_chunks), dim3(kBlock), 0, stream, \
+                                                                  bounds, n_counters, scan_partials, COUNTERS, SMALL, LARGE)
         if (order) {
             if (n_chunks <= 2048) FG_APPLY(true, true, order->counters, order->small, order->large);
             else FG_APPLY(false, true, order->counters, order->small, order->large);
@@ -616,19 +618,18 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
     }
     }
     switch (d) {
-        case 2: launch_scatter<2>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream); break;
-        case 3: launch_scatter<3>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream); break;
-        case 4: launch_scatter<4>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream); break;
-        case 5: launch_scatter<5>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream); break;
-        case 6: launch_scatter<6>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream); break;
-        case 7: launch_scatter<7>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream); break;
-        case 8: launch_scatter<8>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream); break;
-        case 9: launch_scatter<9>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream); break;
-        case 10: launch_scatter<10>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream); break;
+        case 2: FG_TRY(launch_scatter<2>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
+        case 3: FG_TRY(launch_scatter<3>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
+        case 4: FG_TRY(launch_scatter<4>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
+        case 5: FG_TRY(launch_scatter<5>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
+        case 6: FG_TRY(launch_scatter<6>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
+        case 7: FG_TRY(launch_scatter<7>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
+        case 8: FG_TRY(launch_scatter<8>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
+        case 9: FG_TRY(launch_scatter<9>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
+        case 10: FG_TRY(launch_scatter<10>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
         default: return hipErrorInvalidValue;
     }
-    if (order) return launch_order(*order, stream);
-    return hipGetLastError();
+    return order ? launch_order(*order, stream) : hipSuccess;
 }
 
 }  // namespace fg

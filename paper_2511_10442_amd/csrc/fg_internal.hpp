@@ -47,7 +47,20 @@ struct QueryArgs {
 
 struct OrderArgs;
 
-// Host-side launchers, one per translation unit.  Each returns hipGetLastError() of its launches.
+// A chain of launches ends at the first that fails: what follows would run on what that one has not written (counters not
+// cleared, an order not made).
+#define FG_TRY(call)                                            \
+    do {                                                        \
+        const hipError_t fg_try_ = (call);                      \
+        if (fg_try_ != hipSuccess) return fg_try_;              \
+    } while (0)
+#define FG_LAUNCH(...)                                          \
+    do {                                                        \
+        hipLaunchKernelGGL(__VA_ARGS__);                        \
+        FG_TRY(hipGetLastError());                              \
+    } while (0)
+
+// Host-side launchers, one per translation unit.  Each returns the error of its first launch that failed.
 hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_t n, int32_t d,
                           int32_t n_segments, int32_t n_bins, int32_t d_bin, int32_t sub_shift /* last binning dimension:
                           n_bins << sub_shift slices */, int64_t total_bins,

@@ -363,26 +363,26 @@ hipError_t launch_oc_helper(const int32_t* asso_idx, const int32_t* unique_idx, 
     const unsigned groups = (unsigned)((n_unique + kOcBlock - 1) / kOcBlock);
     const int32_t n_chunks = (n_maxrs + kOcChunk - 1) / kOcChunk;
     if (!counts || n_chunks + 1 > 65535) {
-        hipLaunchKernelGGL(k_oc_helper, dim3(groups), dim3(kOcBlock), 0, stream, asso_idx, unique_idx, unique_rs_asso, rs,
-                           n_vert, n_unique, n_splits, n_maxuq, n_maxrs, calc_m_not, rot_block, M, M_not);
-        return hipGetLastError();
+        FG_LAUNCH(k_oc_helper, dim3(groups), dim3(kOcBlock), 0, stream, asso_idx, unique_idx, unique_rs_asso, rs,
+                  n_vert, n_unique, n_splits, n_maxuq, n_maxrs, calc_m_not, rot_block, M, M_not);
+        return hipSuccess;
     }
-    hipLaunchKernelGGL(k_oc_count, dim3(groups, n_chunks), dim3(kOcBlock), 0, stream, asso_idx, unique_idx, unique_rs_asso,
-                       rs, n_vert, n_unique, n_splits, n_maxrs, rot_block, counts);
-    hipLaunchKernelGGL(k_oc_scan, dim3(groups), dim3(kOcBlock * kOcScanWaves), 0, stream, counts, n_unique, n_chunks);
+    FG_LAUNCH(k_oc_count, dim3(groups, n_chunks), dim3(kOcBlock), 0, stream, asso_idx, unique_idx, unique_rs_asso,
+              rs, n_vert, n_unique, n_splits, n_maxrs, rot_block, counts);
+    FG_LAUNCH(k_oc_scan, dim3(groups), dim3(kOcBlock * kOcScanWaves), 0, stream, counts, n_unique, n_chunks);
     int64_t pads = ((int64_t)n_maxuq + kOcPadRows - 1) / kOcPadRows;
     if (pads > 65535 - n_chunks) pads = 65535 - n_chunks;
-    hipLaunchKernelGGL(k_oc_members, dim3(groups, n_chunks + (unsigned)pads), dim3(kOcBlock), 0, stream, asso_idx, unique_idx,
-                       unique_rs_asso, rs, n_vert, n_unique, n_splits, n_maxuq, n_maxrs, rot_block, n_chunks, counts, M);
+    FG_LAUNCH(k_oc_members, dim3(groups, n_chunks + (unsigned)pads), dim3(kOcBlock), 0, stream, asso_idx, unique_idx,
+              unique_rs_asso, rs, n_vert, n_unique, n_splits, n_maxuq, n_maxrs, rot_block, n_chunks, counts, M);
     if (calc_m_not) {
         // rows per wavefront: its search for the first one is paid once, but the chip holds some 5000 of these wavefronts
         int32_t rows = 4 * kOcTile;
         while (rows > kOcTile && (int64_t)groups * ((n_maxrs + rows - 1) / rows) < kOcOthersWaves) rows >>= 1;
-        hipLaunchKernelGGL(k_oc_others, dim3(groups, (unsigned)((n_maxrs + (int64_t)rows - 1) / rows)), dim3(kOcBlock), 0, stream,
-                           asso_idx, unique_idx, unique_rs_asso, rs, n_vert, n_unique, n_splits, n_maxuq, n_maxrs, rot_block,
-                           n_chunks, rows, counts, M, M_not);
+        FG_LAUNCH(k_oc_others, dim3(groups, (unsigned)((n_maxrs + (int64_t)rows - 1) / rows)), dim3(kOcBlock), 0, stream,
+                  asso_idx, unique_idx, unique_rs_asso, rs, n_vert, n_unique, n_splits, n_maxuq, n_maxrs, rot_block,
+                  n_chunks, rows, counts, M, M_not);
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 }  // namespace fg

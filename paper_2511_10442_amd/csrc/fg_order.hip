@@ -333,9 +333,9 @@ k_order_chunk(OrderArgs a)
 
 hipError_t launch_order(const OrderArgs& a, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_order_split<2>, dim3(kSplitGrid), dim3(kSplitThreads), 0, stream, a);
-    hipLaunchKernelGGL(k_order_chunk<2>, dim3(kChunkGrid), dim3(kChunkThreads), 0, stream, a);
-    return hipGetLastError();
+    FG_LAUNCH(k_order_split<2>, dim3(kSplitGrid), dim3(kSplitThreads), 0, stream, a);
+    FG_LAUNCH(k_order_chunk<2>, dim3(kChunkGrid), dim3(kChunkThreads), 0, stream, a);
+    return hipSuccess;
 }
 
 }  // namespace fg

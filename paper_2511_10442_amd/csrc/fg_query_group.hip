@@ -385,13 +385,14 @@ k_query_group(QueryArgs a, GroupTree tree)
 }
 
 template <int D, int Q>
-static void launch_group_pass(const QueryArgs& a, const GroupTree& tree, hipStream_t stream)
+static hipError_t launch_group_pass(const QueryArgs& a, const GroupTree& tree, hipStream_t stream)
 {
     int32_t blocks = (a.n + Q - 1) / Q;
     if (a.dense_class > 0 && blocks > kRankedGrid) blocks = kRankedGrid;       // its workgroups take further groups
     const dim3 grid(blocks);
-    if (a.slot0 == 0) hipLaunchKernelGGL((k_query_group<D, Q, false>), grid, dim3(kQueryBlock), 0, stream, a, tree);
-    else hipLaunchKernelGGL((k_query_group<D, Q, true>), grid, dim3(kQueryBlock), 0, stream, a, tree);
+    if (a.slot0 == 0) FG_LAUNCH((k_query_group<D, Q, false>), grid, dim3(kQueryBlock), 0, stream, a, tree);
+    else FG_LAUNCH((k_query_group<D, Q, true>), grid, dim3(kQueryBlock), 0, stream, a, tree);
+    return hipSuccess;
 }
 
 // Two queries a wavefront where four would leave the chip short of wavefronts, and from seven dimensions on, where the second
@@ -404,21 +405,20 @@ static hipError_t launch_group(const QueryArgs& a_in, hipStream_t stream)
 {
     QueryArgs a = a_in;
     const GroupTree tree = group_tree<D>(a.work_list, a.n);
-    hipLaunchKernelGGL(k_group_boxes<D>, dim3(tree.n_node), dim3(1024), 0, stream, a.rec, a.n, tree, a.work_count);
+    FG_LAUNCH(k_group_boxes<D>, dim3(tree.n_node), dim3(1024), 0, stream, a.rec, a.n, tree, a.work_count);
     const int32_t cap = a.k - 1;
     for (a.slot0 = 0; a.slot0 == 0 || a.slot0 < cap; a.slot0 += 64) {
         a.k_list = cap - a.slot0 < 64 ? cap - a.slot0 : 64;
-        if (D >= 7 || a.n <= kGroupPairsN) launch_group_pass<D, 2>(a, tree, stream);
-        else if constexpr (D < 7) launch_group_pass<D, 4>(a, tree, stream);
+        if (D >= 7 || a.n <= kGroupPairsN) FG_TRY((launch_group_pass<D, 2>(a, tree, stream)));
+        else if constexpr (D < 7) FG_TRY((launch_group_pass<D, 4>(a, tree, stream)));
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 template <int D>
 static hipError_t launch_clusters(const QueryArgs& a, hipStream_t stream)
 {
-    launch_group_pass<D, 4>(a, group_tree<D>(a.work_list, a.n), stream);
-    return hipGetLastError();
+    return launch_group_pass<D, 4>(a, group_tree<D>(a.work_list, a.n), stream);
 }
 
 hipError_t launch_query_clusters(const QueryArgs& a, hipStream_t stream)

@@ -305,24 +305,25 @@ static inline int32_t clusters_class_for(int32_t n, int32_t d, int32_t k_list)
 
 // The queries handed over by the tile (or leaf) kernel: their work list, then the list kernel.
 template <int D, int DB, bool COUNT>
-static void launch_handed(const QueryArgs& a, hipStream_t stream)
+static hipError_t launch_handed(const QueryArgs& a, hipStream_t stream)
 {
     const int grid = (a.n + kQueryBlock - 1) / kQueryBlock;
     const bool last = a.slot0 + a.k_list >= a.k - 1;                  // pass of a long list
     int32_t* const counters = a.tile_order ? a.tile_order + 2 * grid : (a.votes ? const_cast<int32_t*>(a.votes) - kTileClasses : nullptr);
-    hipLaunchKernelGGL(k_list_compact, dim3((grid + 1023) / 1024), dim3(1024), 0, stream, a.handed, grid, a.work_list, a.work_count,
-                       last ? counters : nullptr);
+    FG_LAUNCH(k_list_compact, dim3((grid + 1023) / 1024), dim3(1024), 0, stream, a.handed, grid, a.work_list, a.work_count,
+              last ? counters : nullptr);
     // one query per wavefront; four times the wave slots of the chip: the queries differ widely in cost, and with
     // more, shorter workgroups the hardware dispatcher evens them out (cursors in memory cost more than they gained)
     const int list_grid = a.n < 32768 ? a.n : 32768;
-    hipLaunchKernelGGL((k_query_list_wave<D, DB, COUNT>), dim3(list_grid), dim3(kQueryBlock), 0, stream, a);
+    FG_LAUNCH((k_query_list_wave<D, DB, COUNT>), dim3(list_grid), dim3(kQueryBlock), 0, stream, a);
+    return hipSuccess;
 }
 
 // One pass of the fast path: tile kernel + list kernel for a.k_list <= 64 neighbours per query, or what takes their place.  The second
 // pass of a long list (LOWER) keeps the order of the first, the choice made with it (a.dense_class) and, where the group kernel
 // serves the call, its boxes: nothing is handed over then, so the work list that would take their place stays empty.
 template <int D, int DB, bool COUNT, bool LOWER>
-static void launch_query_pass(QueryArgs& a, hipStream_t stream)
+static hipError_t launch_query_pass(QueryArgs& a, hipStream_t stream)
 {
     const int grid = (a.n + kQueryBlock - 1) / kQueryBlock;
     const bool leaf = D == 2 && takes_dense_order(a.n, D);             // the dense tiles the leaf kernel's
@@ -340,34 +341,34 @@ static void launch_query_pass(QueryArgs& a, hipStream_t stream)
         const int per_wave = grid <= kFewTiles ? kTilesPerWaveFew : kTilesPerWave;
         const int blocks = (grid + 4 * per_wave - 1) / (4 * per_wave);
         const GroupTree tree = group_tree<D>(a.work_list, a.n);
-        hipLaunchKernelGGL((k_tile_work<D, DB>), dim3(blocks + (clusters ? (tree.n_leaf + 3) / 4 : 0)), dim3(256), 0, stream, a, grid,
-                           blocks, per_wave);
+        FG_LAUNCH((k_tile_work<D, DB>), dim3(blocks + (clusters ? (tree.n_leaf + 3) / 4 : 0)), dim3(256), 0, stream, a, grid,
+                  blocks, per_wave);
         if (ranked) {
             const TileShare share{a.dense_class, all_from, a.dense_class > 0 ? a.work_count + 1 : nullptr};
-            hipLaunchKernelGGL(k_tile_rank<D>, dim3((grid + 255) / 256 + (clusters ? (tree.n_node + 3) / 4 : 0)), dim3(256), 0, stream, order,
-                               grid, share, tree);
+            FG_LAUNCH(k_tile_rank<D>, dim3((grid + 255) / 256 + (clusters ? (tree.n_node + 3) / 4 : 0)), dim3(256), 0, stream, order,
+                      grid, share, tree);
         }
     }
     if (!ranked) a.tile_order = nullptr;
-    if (clusters) (void)launch_query_clusters(a, stream);
+    if (clusters) FG_TRY(launch_query_clusters(a, stream));
     if constexpr (D == 2 && !COUNT) {
-        if (a.dense_class > 0 && leaf) launch_leaf_pass<D, LOWER>(a, stream);
+        if (a.dense_class > 0 && leaf) FG_TRY((launch_leaf_pass<D, LOWER>(a, stream)));
     }
     const int32_t cap = a.k_list;
     if (cap <= 16) {
         const size_t lds = tile_sorted_lds_bytes<16, D>();
-        hipLaunchKernelGGL((k_query_tile_sorted<D, DB, 16, COUNT, LOWER>), dim3(grid), dim3(kQueryBlock), lds, stream, a);
+        FG_LAUNCH((k_query_tile_sorted<D, DB, 16, COUNT, LOWER>), dim3(grid), dim3(kQueryBlock), lds, stream, a);
     } else if (cap <= 32) {
         const size_t lds = tile_sorted_lds_bytes<32, D>();
-        hipLaunchKernelGGL((k_query_tile_sorted<D, DB, 32, COUNT, LOWER>), dim3(grid), dim3(kQueryBlock), lds, stream, a);
+        FG_LAUNCH((k_query_tile_sorted<D, DB, 32, COUNT, LOWER>), dim3(grid), dim3(kQueryBlock), lds, stream, a);
     } else if (cap <= 48) {
         const size_t lds = tile_sorted_lds_bytes<48, D>();
-        hipLaunchKernelGGL((k_query_tile_sorted<D, DB, 48, COUNT, LOWER>), dim3(grid), dim3(kQueryBlock), lds, stream, a);
+        FG_LAUNCH((k_query_tile_sorted<D, DB, 48, COUNT, LOWER>), dim3(grid), dim3(kQueryBlock), lds, stream, a);
     } else {
         const size_t lds = tile_sorted_lds_bytes<64, D>();
-        hipLaunchKernelGGL((k_query_tile_sorted<D, DB, 64, COUNT, LOWER>), dim3(grid), dim3(kQueryBlock), lds, stream, a);
+        FG_LAUNCH((k_query_tile_sorted<D, DB, 64, COUNT, LOWER>), dim3(grid), dim3(kQueryBlock), lds, stream, a);
     }
-    launch_handed<D, DB, COUNT>(a, stream);
+    return launch_handed<D, DB, COUNT>(a, stream);
 }
 
 // From this many dimensions on the leaf kernel is the default.  Query stage, tile + list kernel against leaf kernel, in ms:
@@ -396,37 +397,37 @@ static hipError_t launch_query_impl(const QueryArgs& a_in, hipStream_t stream)
         const int grid = (a.n + kQueryBlock - 1) / kQueryBlock;
         const size_t heap_bytes = (size_t)(a.k > 1 ? a.k - 1 : 1) * kQueryBlock * sizeof(uint64_t);
         allow_lds(k_query_shell<D, DB, COUNT>, heap_bytes);
-        hipLaunchKernelGGL((k_query_shell<D, DB, COUNT>), dim3(grid), dim3(kQueryBlock), heap_bytes, stream, a);
-        return hipGetLastError();
+        FG_LAUNCH((k_query_shell<D, DB, COUNT>), dim3(grid), dim3(kQueryBlock), heap_bytes, stream, a);
+        return hipSuccess;
     }
     const int32_t cap = a.k - 1;
     a.slot0 = 0;
     a.k_list = cap < 64 ? cap : 64;
     if constexpr (!COUNT) {
         if (a.algo == 0 && takes_small_path(a.n, a.k)) {
-            if (a.coords) hipLaunchKernelGGL((k_query_small<D, false>), dim3(a.n), dim3(kQueryBlock), 0, stream, a);
-            else hipLaunchKernelGGL((k_query_small<D, true>), dim3(a.n), dim3(kQueryBlock), 0, stream, a);
-            return hipGetLastError();
+            if (a.coords) FG_LAUNCH((k_query_small<D, false>), dim3(a.n), dim3(kQueryBlock), 0, stream, a);
+            else FG_LAUNCH((k_query_small<D, true>), dim3(a.n), dim3(kQueryBlock), 0, stream, a);
+            return hipSuccess;
         }
         if (a.algo == 3 || (a.algo == 0 && D >= kLeafMinD)) {
-            launch_leaf_pass<D, false>(a, stream);
-            if (a.dir) launch_handed<D, DB, false>(a, stream);
+            FG_TRY((launch_leaf_pass<D, false>(a, stream)));
+            if (a.dir) FG_TRY((launch_handed<D, DB, false>(a, stream)));
             if (cap > 64) {
                 a.slot0 = 64;
                 a.k_list = cap - 64;
-                launch_leaf_pass<D, true>(a, stream);
-                if (a.dir) launch_handed<D, DB, false>(a, stream);
+                FG_TRY((launch_leaf_pass<D, true>(a, stream)));
+                if (a.dir) FG_TRY((launch_handed<D, DB, false>(a, stream)));
             }
-            return hipGetLastError();
+            return hipSuccess;
         }
     }
-    launch_query_pass<D, DB, COUNT, false>(a, stream);
+    FG_TRY((launch_query_pass<D, DB, COUNT, false>(a, stream)));
     if (cap > 64) {
         a.slot0 = 64;
         a.k_list = cap - 64;
-        launch_query_pass<D, DB, COUNT, true>(a, stream);
+        FG_TRY((launch_query_pass<D, DB, COUNT, true>(a, stream)));
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 template <int D, int DB>

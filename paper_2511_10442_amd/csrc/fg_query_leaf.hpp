@@ -775,7 +775,7 @@ static inline int32_t leaf_few_ask(int32_t d, int32_t n, int32_t n_segments, int
 }
 
 template <int D, bool LOWER>
-static void launch_leaf_pass(const QueryArgs& a_in, hipStream_t stream)
+static hipError_t launch_leaf_pass(const QueryArgs& a_in, hipStream_t stream)
 {
     QueryArgs a = a_in;
     const LeafTree t = leaf_tree(a.work_list, a.n);
@@ -784,19 +784,20 @@ static void launch_leaf_pass(const QueryArgs& a_in, hipStream_t stream)
     if (!LOWER || a.dense_class > 0 || a.dir) {       // the second pass of a long list finds the boxes of the first, unless the work list took their place
         constexpr int NB = box_vecs<D>();
         const int box_grid = (a.n + 255) / 256;
-        hipLaunchKernelGGL(k_leaf_boxes<D>, dim3(a.dense_class > 0 && box_grid > kDenseGrid ? kDenseGrid : box_grid), dim3(256), 0, stream, a, t.boxes);
+        FG_LAUNCH(k_leaf_boxes<D>, dim3(a.dense_class > 0 && box_grid > kDenseGrid ? kDenseGrid : box_grid), dim3(256), 0, stream, a, t.boxes);
         float4* const box2 = t.boxes + (int64_t)t.n1 * NB;
-        if (t.has2) hipLaunchKernelGGL(k_node_boxes<D>, dim3((t.n2 + 3) / 4), dim3(256), 0, stream, a, t.boxes, t.n1, box2, t.n2);
-        if (t.has3) hipLaunchKernelGGL(k_node_boxes<D>, dim3((t.n3 + 3) / 4), dim3(256), 0, stream, a, box2, t.n2, box2 + (int64_t)t.n2 * NB, t.n3);
+        if (t.has2) FG_LAUNCH(k_node_boxes<D>, dim3((t.n2 + 3) / 4), dim3(256), 0, stream, a, t.boxes, t.n1, box2, t.n2);
+        if (t.has3) FG_LAUNCH(k_node_boxes<D>, dim3((t.n3 + 3) / 4), dim3(256), 0, stream, a, box2, t.n2, box2 + (int64_t)t.n2 * NB, t.n3);
     }
     const int32_t cap = a.k_list;
     a.few_ask = leaf_few_ask(D, a.n, a.n_segments, a.k_list);
-#define FG_LEAF(KC) hipLaunchKernelGGL((k_query_leaf<D, KC, LOWER>), dim3(grid), dim3(kQueryBlock), (leaf_lds_bytes<KC, D>()), stream, a, t)
+#define FG_LEAF(KC) FG_LAUNCH((k_query_leaf<D, KC, LOWER>), dim3(grid), dim3(kQueryBlock), (leaf_lds_bytes<KC, D>()), stream, a, t)
     if (cap <= 16) FG_LEAF(16);
     else if (cap <= 32) FG_LEAF(32);
     else if (cap <= 48) FG_LEAF(48);
     else FG_LEAF(64);
 #undef FG_LEAF
+    return hipSuccess;
 }
 
 }  // namespace fg
