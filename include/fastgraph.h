@@ -16,7 +16,8 @@
  *   - `workspace` is device memory of at least fg_workspace_size() bytes, 256-byte aligned.
  *     Its contents are scratch: undefined on entry, undefined after the call except for the
  *     arrays an fg_binning view points into (valid until the workspace is reused).
- *   - Every call returns an fg_status; on any status other than FG_OK nothing was enqueued.
+ *   - Every call returns an fg_status; on any status other than FG_OK nothing was enqueued, except that FG_ERR_LAUNCH may come
+ *     after some of a call's kernels: outputs are then undefined, and a binning made by that call is not to be used.
  *   - Preconditions that cannot be checked without a device round trip are documented, not
  *     checked: row_splits[0] = 0, row_splits[S] = n, non-decreasing; all coordinates finite.
  *   - n <= FG_MAX_N (indices are int32, and the launch arithmetic keeps a margin below 2^31).
@@ -190,7 +191,9 @@ fg_status fg_binned_select_knn_counted(const float* coords, const int32_t* row_s
 
 /* Query stage alone on an existing binning (what fg_binned_select_knn runs after
  * fg_bin_points); `view` must come from fg_bin_points on the same coords/row_splits and its
- * workspace must still be intact.  Used to time the query kernel on its own.
+ * workspace must still be intact, `scratch` included: it carries counters from the binning to the first query and from
+ * one query to the next.  A view may be queried again and again, but one call after the other (on one stream, or
+ * ordered by events).  Used to time the query kernel on its own.
  * options: host pointer, may be NULL. */
 fg_status fg_query_binned(const fg_binning* view, const int32_t* row_splits, int64_t n, int32_t d,
                           int32_t n_segments, int32_t k, int32_t* out_idx, float* out_d2,

@@ -16,8 +16,9 @@ namespace fg {
 // evenly spread work, the last third of it with most of the chip idle.  The tiles are therefore ranked by an
 // estimate of their work, in 64 classes of half a power of two, heaviest class first.
 // tile_order: [0, T) the order, [T, 2T) class of each tile (bit 6: uneven, see k_tile_work), [2T, 2T+64) class
-// histogram, [2T+64, 2T+128) cursors; the last two are zero between calls: the binning clears them, and k_list_compact, the
-// first kernel that nothing follows that reads them, does again (a launch of their own to clear them took 4 us of every call).
+// histogram, [2T+64, 2T+128) cursors.  The histogram is zero between calls: the binning clears it, and k_list_compact, the
+// first kernel that nothing follows that reads it, does again (a launch of its own to clear it took 4 us of every call); should a
+// call have ended between the two, k_tile_rank sees that it counts too many tiles.  The cursors are cleared by k_tile_work.
 
 // The work list of the list kernel from the tiles' hand-over marks: blocks of 1024 tiles, the queries of a block in
 // tile order (a block's place in the list comes from one atomic add, so blocks may swap, 65 536 queries each).
@@ -119,7 +120,10 @@ static __global__ void __launch_bounds__(256) k_tile_work(QueryArgs a, int32_t n
         }
     }
     __shared__ int32_t hist[kTileClasses];
-    if (threadIdx.x < kTileClasses) hist[threadIdx.x] = 0;
+    if (threadIdx.x < kTileClasses) {
+        hist[threadIdx.x] = 0;
+        if (blockIdx.x == 0 && !a.votes) a.tile_order[2 * n_tiles + kTileClasses + threadIdx.x] = 0;
+    }
     __syncthreads();
     const int lane = threadIdx.x & 63;
     const int sample = lane & (kTileSamples - 1);
@@ -232,6 +236,7 @@ static __global__ void __launch_bounds__(256) k_tile_rank(int32_t* __restrict__ 
     }
     __shared__ int32_t local[kTileClasses];   // this block's tiles per class, then the block's first position in the class
     __shared__ int32_t first[kTileClasses];   // position of the class's first tile: all heavier classes before it
+    __shared__ int32_t counted;               // tiles in the histogram: all of them, or it holds an unfinished call's, too
     const int32_t t = blockIdx.x * 256 + threadIdx.x;
     const int32_t word = t < n_tiles ? order[n_tiles + t] : 0;
     static_assert(kTileClasses == 64, "one class per lane of the first wavefront");
@@ -245,9 +250,15 @@ static __global__ void __launch_bounds__(256) k_tile_rank(int32_t* __restrict__ 
             s += (int32_t)threadIdx.x + o < kTileClasses ? up : 0;
         }
         first[threadIdx.x] = s - own;
+        if (threadIdx.x == 0) counted = s;
         if (blockIdx.x == 0 && (int32_t)threadIdx.x == share.dense_class) share.write(s, n_tiles);
     }
     __syncthreads();
+    if (counted != n_tiles) {                 // no places can be had from it: tiles as they come, none another kernel's
+        if (t < n_tiles) order[t] = t;
+        if (blockIdx.x == 0 && threadIdx.x == 0 && share.n_dense) *share.n_dense = 0;
+        return;
+    }
     int32_t mine = 0;
     const int32_t cls = word & (kTileClasses - 1), uneven = (word >> kTileFlatBit) & 1;
     if (t < n_tiles) mine = atomicAdd(&local[cls], 1);

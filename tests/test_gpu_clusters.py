@@ -82,3 +82,29 @@ def test_captured():
         assert torch.equal(idx, ref[0]) and torch.equal(d2, ref[1])
         got = B.fg_binned_select_knn(xt, rt, k, workspace=ws)
         assert torch.equal(got[0], ref[0])
+
+
+# a call that ended before its last kernels leaves its counts of tiles behind (here: put there): the next one on the binning does not take
+# places from them, and the one after that is as fast as ever
+@pytest.mark.parametrize("kind,n,d,k", [("uniform", 70_001, 3, 12), ("clusters", 100_003, 4, 20), ("uniform", 70_001, 3, 80), ("clusters", (1 << 20) + 77, 2, 10),
+                                          ("uniform", 70_001, 6, 12), ("clusters", 24_000, 3, 12)])
+def test_counts_left_behind(kind, n, d, k):
+    xt = torch.from_numpy(cloud(kind, n, d)).to(DEV)
+    rt = torch.tensor([0, n // 3, n], dtype=torch.int32, device=DEV)
+    bn = B.fg_bin_points(xt, rt, k)
+    algo = 4 if d == 6 else 0
+    ref = [t.clone() for t in B.fg_query_binned(bn, rt, k, algo=algo)]
+    tiles = (n + 63) // 64
+    at = bn.raw.scratch - bn.workspace.data_ptr() + 256 + (4 * n + 255) // 256 * 256 + 8 * tiles     # class counts, then cursors
+    counters = bn.workspace[at:at + 512].view(torch.int32)
+    torch.cuda.synchronize()
+    assert not counters.any()
+    classes = bn.workspace[at - 4 * tiles:at].view(torch.int32) & 63
+    for left in (torch.bincount(classes.long(), minlength=64)[:64], torch.full((64,), tiles, device=DEV), torch.eye(64, device=DEV)[9]):
+        counters[:64] = left.int()
+        counters[64:] = left.int()
+        got = B.fg_query_binned(bn, rt, k, algo=algo)
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+        assert not counters.any()
+        got = B.fg_query_binned(bn, rt, k, algo=algo)
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
