@@ -22,8 +22,10 @@ hipError_t launch_query_d10(const QueryArgs&, int32_t, hipStream_t);
 
 hipError_t launch_query(const QueryArgs& a, int32_t d, int32_t d_bin, hipStream_t stream)
 {
-    if (!a.out_cand && (a.algo == 5 || (a.algo == 0 && !takes_small_path(a.n, a.k) && takes_group_kernel(a.n, d, a.n_segments, a.k))))
-        return launch_query_group(a, stream);
+    if (!a.out_cand) {
+        if (a.algo == 0 && takes_small_path(a.n, a.k)) return launch_query_small(a, stream);
+        if (a.algo == 5 || (a.algo == 0 && takes_group_kernel(a.n, d, a.n_segments, a.k))) return launch_query_group(a, stream);
+    }
     switch (d) {
         case 2: return launch_query_d2(a, d_bin, stream);
         case 3: return launch_query_d3(a, d_bin, stream);

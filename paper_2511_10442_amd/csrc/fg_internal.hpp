@@ -121,6 +121,9 @@ hipError_t launch_query(const QueryArgs& a, int32_t d, int32_t d_bin, hipStream_
 constexpr int kClustersMaxD = 5;
 hipError_t launch_query_clusters(const QueryArgs& a, hipStream_t stream);
 
+// every pair compared: takes_small_path
+hipError_t launch_query_small(const QueryArgs& a, hipStream_t stream);
+
 // the group kernel, whatever the size
 hipError_t launch_query_group(const QueryArgs& a, hipStream_t stream);
 

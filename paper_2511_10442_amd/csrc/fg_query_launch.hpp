@@ -4,7 +4,6 @@
 #include "fg_query_tile.hpp"
 #include "fg_query_list.hpp"
 #include "fg_query_leaf.hpp"
-#include "fg_query_small.hpp"
 #include "fg_group_boxes.hpp"
 
 namespace fg {
@@ -415,11 +414,6 @@ static hipError_t launch_query_impl(const QueryArgs& a_in, hipStream_t stream)
     a.slot0 = 0;
     a.k_list = cap < 64 ? cap : 64;
     if constexpr (!COUNT) {
-        if (a.algo == 0 && takes_small_path(a.n, a.k)) {
-            if (a.coords) FG_LAUNCH((k_query_small<D, false>), dim3(a.n), dim3(kQueryBlock), 0, stream, a);
-            else FG_LAUNCH((k_query_small<D, true>), dim3(a.n), dim3(kQueryBlock), 0, stream, a);
-            return hipSuccess;
-        }
         if (a.algo == 3 || (a.algo == 0 && D >= kLeafMinD)) {
             FG_TRY((launch_leaf_pass<D, false>(a, stream)));
             if (a.dir) FG_TRY((launch_handed<D, DB, false>(a, stream)));

@@ -5,7 +5,6 @@
 // chip.  The list is the one of the list kernel: one key per lane, ascending.  256 candidates are requested at a time
 // (four per lane), so a thousand points are four trips to memory.
 // REC: candidates are the bin-ordered records of a binning, else the caller's coordinates in their own order.
-#pragma once
 #include "fg_query_list.hpp"
 
 namespace fg {
@@ -90,6 +89,33 @@ k_query_small(QueryArgs a)
         const bool real = best < kEmptyKey;
         oi[j] = real ? (int32_t)(uint32_t)best : -1;
         od[j] = real ? __uint_as_float((uint32_t)(best >> 32)) : 0.0f;
+    }
+}
+
+template <int D>
+static hipError_t launch_small(const QueryArgs& a, hipStream_t stream)
+{
+    if (a.coords) FG_LAUNCH((k_query_small<D, false>), dim3(a.n), dim3(kQueryBlock), 0, stream, a);
+    else FG_LAUNCH((k_query_small<D, true>), dim3(a.n), dim3(kQueryBlock), 0, stream, a);
+    return hipSuccess;
+}
+
+hipError_t launch_query_small(const QueryArgs& a_in, hipStream_t stream)
+{
+    QueryArgs a = a_in;
+    a.slot0 = 0;
+    a.k_list = a.k - 1;
+    switch (a.d) {
+        case 2: return launch_small<2>(a, stream);
+        case 3: return launch_small<3>(a, stream);
+        case 4: return launch_small<4>(a, stream);
+        case 5: return launch_small<5>(a, stream);
+        case 6: return launch_small<6>(a, stream);
+        case 7: return launch_small<7>(a, stream);
+        case 8: return launch_small<8>(a, stream);
+        case 9: return launch_small<9>(a, stream);
+        case 10: return launch_small<10>(a, stream);
+        default: return hipErrorInvalidValue;
     }
 }
 
