@@ -87,21 +87,19 @@ inline bool takes_small_path(int64_t n, int32_t k) { return n <= kSmallN && k <=
 // points on, where the kernels of one wavefront for 64 queries have fewer wavefronts than SIMDs and the densest tile sets their
 // end, but it does not share a query's candidates with 64 others.  The lines are those of uniform points, which suit the others
 // best.  Query stage of one uniform split, the other kernels against the group kernel, in us:
-//   d = 2, K = 10: 10k points 31 against 24, 20k 32 / 37; K = 40: 20k 69 / 39      d = 3, K = 10: 20k 47 / 48; K = 40: 20k 102 / 66, 40k 111 / 111
+//   d = 2, K = 10: 5k points 27 against 20, 10k 31 / 24, 20k 32 / 37; K = 40: 20k 69 / 39      d = 3, K = 10: 5k 45 / 25, 20k 47 / 48; K = 40: 20k 102 / 66, 40k 111 / 111
 //   d = 4, K = 10: 40k 123 / 117; K = 40: 40k 184 / 168      d = 5, K = 10: 80k 423 / 349; K = 40: 80k 533 / 510
 //   d = 6, K = 10: 40k 363 / 272, 80k 423 / 566; K = 40: 80k 916 / 801      d = 7, K = 10: 40k 597 / 403, 80k 743 / 909
 //   d = 8: 40k, K = 10 608 / 524, K = 40 861 / 722      d = 9, K = 40: 40k 924 / 969      d = 10, K = 40: 20k 546 / 442, 40k 906 / 1125
 // In 16 splits: d = 4 80k 162 / 159 and 247 / 221, d = 5 160k 451 / 441 and 720 / 611.  Clusters, where a tile's queries differ most:
 // 55k points in showers, d = 3, K = 9 437 / 81; 16k, K = 70 581 / 77; 59k in a mixture, d = 6, K = 37 683 / 203.
-// Up to 8192 points, d <= 3 and K < 16 the tile and list kernels stay although they are slower (5000 points, d = 3, K = 10 45 / 25):
-// the count of queries handed to the list kernel is read after such calls.
 inline bool takes_group_kernel(int64_t n, int32_t d, int32_t n_segments, int32_t k)
 {
     static constexpr int32_t kMost[11] = {0, 0, 16384, 20480, 40960, 90112, 61440, 61440, 49152, 36864, 28672};
     int64_t most = kMost[d];
     if (d <= 3 && k >= 24) most *= 2;
     if ((d == 4 || d == 5) && n <= (int64_t)n_segments * 16384) most *= 2;
-    return n <= most && !(n <= 8192 && d <= 3 && k < 16);
+    return n <= most;
 }
 
 // Few points: binned in one launch before the scatter (figures in fg_binning.hip), and the query stage asks for the tiles' votes.

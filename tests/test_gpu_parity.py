@@ -210,9 +210,9 @@ def test_deterministic_across_runs():
 
 
 def test_tile_and_list_kernels_both_run_and_agree_with_the_plain_walk():
-    """Default path = tile kernel + list kernel for the queries it defers; algo = 1 sends
+    """algo = 4: tile kernel + list kernel for the queries it defers; algo = 1 sends
     every query through the one-lane-per-query walk.  Isolated points far from a dense core need
-    many shells, so some queries must reach the list kernel."""
+    many shells, so some queries must reach the list kernel.  The default, another kernel at this size, hands none over."""
     rng = np.random.Generator(np.random.PCG64(29))
     core = rng.standard_normal((6000, 3)) * 0.05
     far = rng.random((600, 3)) * 20.0 - 10.0
@@ -224,11 +224,15 @@ def test_tile_and_list_kernels_both_run_and_agree_with_the_plain_walk():
     xt, rt = torch.from_numpy(x).to(DEV), torch.from_numpy(rs).to(DEV)
     for nb in (0, 40):
         bn = B.fg_bin_points(xt, rt, k, nb, 3 if nb else 0)
-        gi, gd = B.fg_query_binned(bn, rt, k)
+        gi, gd = B.fg_query_binned(bn, rt, k, algo=4)
         torch.cuda.synchronize()
         deferred = int(bn.work_count.item())
         assert_exact(gi.cpu().numpy(), gd.cpu().numpy(), oi, od, "tile+list nb=%d" % nb)
         assert 0 < deferred < x.shape[0]
+        gi, gd = B.fg_query_binned(bn, rt, k)
+        torch.cuda.synchronize()
+        assert int(bn.work_count.item()) == 0
+        assert_exact(gi.cpu().numpy(), gd.cpu().numpy(), oi, od, "default nb=%d" % nb)
         gi, gd = B.fg_query_binned(bn, rt, k, algo=1)
         torch.cuda.synchronize()
         assert_exact(gi.cpu().numpy(), gd.cpu().numpy(), oi, od, "plain walk nb=%d" % nb)
