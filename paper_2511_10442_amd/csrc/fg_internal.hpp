@@ -93,13 +93,33 @@ inline bool takes_small_path(int64_t n, int32_t k) { return n <= kSmallN && k <=
 //   d = 8: 40k, K = 10 608 / 524, K = 40 861 / 722      d = 9, K = 40: 40k 924 / 969      d = 10, K = 40: 20k 546 / 442, 40k 906 / 1125
 // In 16 splits: d = 4 80k 162 / 159 and 247 / 221, d = 5 160k 451 / 441 and 720 / 611.  Clusters, where a tile's queries differ most:
 // 55k points in showers, d = 3, K = 9 437 / 81; 16k, K = 70 581 / 77; 59k in a mixture, d = 6, K = 37 683 / 203.
+// Splits of a few points (K < 24): up to five dimensions a grid of one bin, which the tile kernel scans for 64 queries at once, best
+// where the lists fill; beyond, few leaves for a tile of many splits.  A group has two or four queries to share what it costs
+// to start.  Query stage, the other kernels against the group kernel, in us:
+//   10k points: d = 2, K = 10 6 points a split 17 / 20, 18 23 / 20; d = 3, K = 10 6 19 / 21, 12 30 / 21, K = 20 22 23 / 21; d = 4, K = 10 6 29 / 23, 12 18 / 23,
+//   18 64 / 23; d = 5, K = 20 18 63 / 26, 27 24 / 27, 45 28 / 27, K = 16 40 169 / 26; d = 8, K = 16 5 27 / 31, 10 27 / 29
+//   16k: d = 2, K = 10 12 22 / 25, K = 20 18 28 / 25; d = 3, K = 17 18 23 / 27, 22 39 / 27; d = 4, K = 17 12 34 / 29, 22 26 / 29, 27 77 / 31
+//   30k: d = 4, K = 20 6 38 / 46, 27 29 / 45, 34 85 / 45; d = 5, K = 20 18 69 / 49, 27 29 / 48, 45 33 / 48; d = 6, K = 16 10 26 / 48, 40 38 / 45, 80 45 / 45
+inline bool few_points_a_split(int64_t n, int32_t d, int32_t n_segments, int32_t k)
+{
+    static constexpr int32_t kOneBin[6] = {0, 0, 88, 110, 156, 244};     // percent of K: the automatic grid has one bin up to there
+    if (k >= 24) return false;
+    const int64_t splits = n_segments;
+    const bool many = n > 12288;
+    if (d >= 6) return n <= splits * (many ? 48 : 6);
+    const bool fill = n >= splits * k;
+    if (d <= 3 ? k > 17 && (d == 2 || !many) : !fill && (d == 5 || n <= 20480)) return false;
+    const int32_t percent = d <= 3 && many && k >= 10 && k <= 17 ? 130 : kOneBin[d];      // (whole call, 20k points in splits of 11, d = 3, K = 10 85 / 98)
+    return 100 * n <= splits * k * percent;
+}
+
 inline bool takes_group_kernel(int64_t n, int32_t d, int32_t n_segments, int32_t k)
 {
     static constexpr int32_t kMost[11] = {0, 0, 16384, 20480, 40960, 90112, 61440, 61440, 49152, 36864, 28672};
     int64_t most = kMost[d];
     if (d <= 3 && k >= 24) most *= 2;
     if ((d == 4 || d == 5) && n <= (int64_t)n_segments * 16384) most *= 2;
-    return n <= most;
+    return n <= most && !few_points_a_split(n, d, n_segments, k);
 }
 
 // Few points: binned in one launch before the scatter (figures in fg_binning.hip), and the query stage asks for the tiles' votes.

@@ -94,3 +94,16 @@ def test_default_on_both_sides_of_the_line(d, k, splits, line):
         rows = np.linspace(0, n - 1, 40).astype(np.int64)
         oi, od = oracle.knn_rows(x, rs, k, rows)
         assert np.array_equal(ref[0].cpu().numpy()[rows], oi) and np.array_equal(ref[1].cpu().numpy()[rows].view(np.uint32), od.view(np.uint32))
+
+
+# splits of a few points: the kernel for 64 queries serves them up to a grid of one bin (up to five dimensions), of up to 48 points (beyond)
+@pytest.mark.parametrize("n,d,k,per", [(15_000, 2, 16, 14), (15_000, 2, 16, 15), (20_000, 3, 10, 1), (20_000, 3, 10, 2), (20_000, 3, 10, 11), (20_000, 3, 10, 13), (20_000, 3, 10, 14), (10_000, 8, 16, 6), (10_000, 8, 16, 7),
+                                        (40_000, 4, 8, 12), (40_000, 4, 8, 13), (40_000, 5, 16, 15), (40_000, 5, 16, 20), (40_000, 5, 16, 40), (40_000, 8, 16, 2),
+                                        (40_000, 8, 16, 48), (40_000, 8, 16, 49), (40_000, 3, 10, 63), (40_000, 3, 10, 64), (30_000, 6, 24, 5)])
+def test_splits_of_a_few_points(n, d, k, per):
+    x, _ = W.uniform(n, d, seed=n + k + per)
+    rs = np.append(np.arange(0, n, per), n).astype(np.int32)
+    rs[5] = rs[4]                                        # an empty one
+    oi, od = oracle.knn(x, rs, k)
+    gi, gd = run(x, rs, k, algo=0)
+    assert np.array_equal(gi, oi) and np.array_equal(gd, od.view(np.uint32))

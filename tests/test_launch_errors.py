@@ -1,14 +1,9 @@
 """A launch that fails, at every place of every chain of launches: the call says so, and nothing that would have run on what that launch did not
-write is launched after it.  The runtime's launch call is replaced (launch_shim.c): no GPU, no kernel runs, pointers are never read."""
-import ctypes
-import json
-import os
-import subprocess
-import sys
-
+write is launched after it."""
 import pytest
 
-HERE = os.path.dirname(os.path.abspath(__file__))
+from launches import launches
+
 FG_ERR_LAUNCH = 5
 
 CHAINS = {
@@ -33,52 +28,14 @@ CHAINS = {
     "index matrices without scratch": ("oc", 20000, 0, 2, 16, 0),
 }
 
-# (child: ctypes alone, so that nothing else uses the replaced calls)
-CHILD = """
-import ctypes, json, sys
-lib = ctypes.CDLL(sys.argv[1])
-shim = ctypes.CDLL(None)
-i32, i64, sz = ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t
-P = lambda: ctypes.c_void_p(1 << 20)
-big = sz(1 << 40)
-def call(kind, n, d, s, k, flag):
-    if kind == "knn":
-        return lib.fg_binned_select_knn_dir(P(), P(), P() if flag else None, i64(n), i32(d), i32(s), i32(k), i32(0), i32(0), P(), P(), P(), big, None)
-    if kind == "counted":
-        return lib.fg_binned_select_knn_counted(P(), P(), i64(n), i32(d), i32(s), i32(k), i32(0), i32(0), P(), P(), P(), P(), big, None)
-    if kind == "bwd":
-        return lib.fg_knn_backward(P(), P(), P(), P() if flag else None, i64(n), i32(d), i32(s), i32(k), P(), P() if flag else None, big, None)
-    return lib.fg_oc_helper(P(), P(), P(), P(), i64(n), i64(40), i32(s), i32(100), i32(n // s), i32(1), i32(1), P(), P(), P() if flag else None, big, None)
-out = {}
-for name, args in json.loads(sys.argv[2]).items():
-    rows = []
-    fail = 0
-    while True:
-        shim.shim_reset(fail)
-        status = call(*args)
-        rows.append((fail, status, shim.shim_made()))
-        fail += 1
-        if fail > rows[0][2]: break
-    out[name] = rows
-print(json.dumps(out))
-"""
-
-
 @pytest.fixture(scope="module")
-def answers(tmp_path_factory):
-    from paper_2511_10442_amd import binding
-    binding.lib()                                        # built if it is not there
-    shim = str(tmp_path_factory.mktemp("shim") / "launch_shim.so")
-    subprocess.check_call(["gcc", "-O1", "-shared", "-fPIC", "-o", shim, os.path.join(HERE, "launch_shim.c")])
-    r = subprocess.run([sys.executable, "-c", CHILD, binding.LIB_PATH, json.dumps(CHAINS)], capture_output=True, text=True,
-                       env=dict(os.environ, LD_PRELOAD=shim), timeout=100)
-    assert r.returncode == 0, r.stdout + r.stderr
-    return json.loads(r.stdout.splitlines()[-1])
+def answers():
+    return dict(zip(CHAINS, launches(list(CHAINS.values()), every_failure=True)))
 
 
 @pytest.mark.parametrize("name", list(CHAINS))
 def test_first_error_ends_the_chain(answers, name):
-    rows = answers[name]
-    assert rows[0][1] == 0 and rows[0][2] >= 1, rows[0]
-    for fail, status, made in rows[1:]:
-        assert status == FG_ERR_LAUNCH and made == fail, "launch %d of %d failed: status %d, %d launches" % (fail, rows[0][2], status, made)
+    status, names, rows = answers[name]
+    assert status == 0 and len(names) >= 1 and len(rows) == len(names)
+    for fail, status, made in rows:
+        assert status == FG_ERR_LAUNCH and made == fail, "launch %d of %d failed: status %d, %d launches" % (fail, len(names), status, made)
