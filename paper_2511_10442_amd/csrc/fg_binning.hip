@@ -398,8 +398,11 @@ k_scan_apply(int32_t* __restrict__ counters, int64_t n_counters, const int32_t* 
 // coordinates twice and adds its points to the LDS counters.  The records are written by k_scatter as otherwise: scattered
 // stores of one CU take as long as the launch that they would save.
 constexpr int kFewThreads = 1024;
-constexpr int32_t kFewCells = 30000;              // of a row split: 60 KB of counters, what a workgroup gets without asking
+constexpr int32_t kFewCells = 48000;              // of a row split: 96 KB of counters; the automatic grids of few_points stay below from K = 8 on
+constexpr int32_t kFewCellsFree = 30000;          // 60 KB, what a workgroup gets without asking
 constexpr int32_t kFewSplits = 1024;
+// Fine grids of few points (K = 8 to 10, more than kFewCellsFree cells): fg_bin_points of 22,000 points, d = 3 29.2 / 22.0, 29,789 29.9 / 26.2, 32,768,
+// d = 2 28.5 / 24.9, 27,300, d = 4 30.6 / 27.7, 25,200, d = 5 31.1 / 29.5.
 // Points of an average split: one of 20,000 points, fg_bin_points six launches against two, in us: d = 2 26.5 / 16.1, d = 3 27.6 / 19.5,
 // d = 5 29.7 / 23.0, d = 10 29.0 / 24.6; of 32,000 27.2 / 21.2, 28.6 / 24.2, 30.4 / 30.5 (fg_knn_backward, which bins for itself: d = 3 42.7 / 43.2).
 // 16 splits of 1250 points 31 to 41 / 13 (the caller's own 12 us a call); 200 of 100 38 to 52 / 13.
@@ -468,8 +471,9 @@ k_bin_few(const float* __restrict__ coords, const int32_t* __restrict__ row_spli
         rank[i] = (int32_t)(old >> half & 0xffffu);
     }
     __syncthreads();
-    // exclusive prefix: a run of words per thread, then the threads' totals
-    const int32_t per = (words + kFewThreads - 1) / kFewThreads;
+    // exclusive prefix: a run of words per thread, then the threads' totals (an odd number of words, else the lanes' meet in the same LDS
+    // banks: 32,000 cells, 16 words each, 31 us of fg_bin_points against 23)
+    const int32_t per = (words + kFewThreads - 1) / kFewThreads | 1;
     const int32_t w0 = min(t * per, words), w1 = min(w0 + per, words);
     int32_t sum = 0;
     for (int32_t i = w0; i < w1; ++i) sum += (int32_t)((cnt[i] & 0xffffu) + (cnt[i] >> 16));
@@ -567,8 +571,12 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
     const int32_t n_keys = n_segments * d_bin;
     const int32_t cells_per_segment = (int32_t)(total_bins / n_segments);
     if (!order && bins_in_one_launch(n, d, n_segments, cells_per_segment)) {
-#define FG_FEW(DB) FG_LAUNCH(k_bin_few<DB>, dim3(n_segments), dim3(kFewThreads), (size_t)(cells_per_segment + 1) / 2 * 4, stream, coords, \
-                             row_splits, n, d, n_segments, n_bins, sub_shift, cells_per_segment, morton_bits, geom, bin_idx, rank, bounds, tile_counters)
+        const size_t lds = (size_t)(cells_per_segment + 1) / 2 * 4;
+#define FG_FEW(DB)                                                                                                                       \
+    if (cells_per_segment > kFewCellsFree)                                                                                               \
+        FG_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_bin_few<DB>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));  \
+    FG_LAUNCH(k_bin_few<DB>, dim3(n_segments), dim3(kFewThreads), lds, stream, coords, row_splits, n, d, n_segments, n_bins, sub_shift,   \
+              cells_per_segment, morton_bits, geom, bin_idx, rank, bounds, tile_counters)
         switch (d_bin) {
             case 2: FG_FEW(2); break;
             case 3: FG_FEW(3); break;

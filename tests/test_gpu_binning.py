@@ -31,12 +31,13 @@ def expected_cells(x, rs, n_bins, d_bin, sub):
     return cells, per_split
 
 
-# (sizes, d, n_bins, d_bin): one launch up to 1024 splits, 30,000 cells a split, 49,152 points, and n (d + 8) <= 327,680 a split
+# (sizes, d, n_bins, d_bin): one launch up to 1024 splits, 48,000 cells a split, 49,152 points, and n (d + 8) <= 327,680 a split
 @pytest.mark.parametrize("sizes,d,nb,db", [
     ([1], 2, 3, 2), ([0, 2, 0], 3, 5, 3), ([63, 0, 64, 1025], 4, 0, 0), ([5000], 5, 0, 0), ([3000, 17], 3, 7, 3),     # 343 cells and slices
     ([20000], 3, 0, 0), ([29789], 3, 0, 0), ([29790], 3, 0, 0),                     # the line of one split
     ([1] * 1024, 2, 2, 2), ([1] * 1025, 2, 2, 2),                                   # of the splits
-    ([14000], 2, 86, 2), ([14000], 2, 87, 2),                                       # of the cells: 4 x 7396 and 4 x 7569
+    ([14000], 2, 86, 2), ([14000], 2, 87, 2),                                       # of the LDS that is free: 4 x 7396 and 4 x 7569 cells
+    ([24000], 2, 109, 2), ([24000], 2, 110, 2), ([25000], 3, 20, 3),                # of the cells: 4 x 11,881 and 4 x 12,100; 4 x 8000
     ([100, 48000, 900, 152], 2, 0, 0), ([100, 48000, 900, 153], 2, 0, 0),           # of the points, nearly all in one split
     ([18000], 10, 0, 0), ([18300], 10, 0, 0)])
 @pytest.mark.parametrize("kind", ["uniform", "same", "flat"])
