@@ -86,13 +86,22 @@ inline bool takes_small_path(int64_t n, int32_t k) { return n <= kSmallN && k <=
 // Sizes up to which the group kernel (one wavefront for two or four queries) serves a call: it fills the chip from a few thousand
 // points on, where the kernels of one wavefront for 64 queries have fewer wavefronts than SIMDs and the densest tile sets their
 // end, but it does not share a query's candidates with 64 others.  The lines are those of uniform points, which suit the others
-// best.  Query stage of one uniform split, the other kernels against the group kernel, in us:
-//   d = 2, K = 10: 5k points 27 against 20, 10k 31 / 24, 20k 32 / 37; K = 40: 20k 69 / 39      d = 3, K = 10: 5k 45 / 25, 20k 47 / 48; K = 40: 20k 102 / 66, 40k 111 / 111
-//   d = 4, K = 10: 40k 123 / 117; K = 40: 40k 184 / 168      d = 5, K = 10: 80k 423 / 349; K = 40: 80k 533 / 510
+// best (up to 15 % beyond, where clusters would lose as much to the launches of a choice), and depend on K with the size of the tile kernel's lists (K = 16, 32 and 64, whose rows leave from its registers, are its best).
+// Query stage, tile + list kernel or leaf kernel against the group kernel, in us, uniform points of one split:
+//   d = 2, K = 10: 5k points 29 / 21, 10k 29 / 27, 16k 29 / 36 (the quicker binning of few points makes up for that); K = 24: 20k 46 / 41, 26k 46 / 50;
+//     K = 32: 13k 36 / 34, 20k 38 / 42, 33k 40 / 56; K = 40: 26k 70 / 54, 33k 72 / 60; K = 64: 20k 63 / 54, 26k 63 / 64, 33k 65 / 72
+//   d = 3, K = 10: 5k 44 / 25, 16k 45 / 46, 20k 47 / 53; K = 32: 16k 61 / 60, 20k 62 / 68, 41k 68 / 120; K = 40: 26k 102 / 89, 33k 104 / 107, 41k 109 / 125;
+//     K = 64: 26k 106 / 101, 33k 107 / 122; K = 100: 41k 331 / 282
+//   d = 4, K = 10: 30k 117 / 107, 41k 121 / 135; K = 32: 30k 151 / 146, 35k 139 / 165; K = 40: 35k 197 / 176, 41k 183 / 200; K = 100: 41k 620 / 472
+//   d = 5, K = 10: 60k 349 / 313, 80k 386 / 413; K = 32: 50k 457 / 366, 60k 386 / 418; K = 40: 60k 536 / 454, 70k 488 / 511; K = 100: 80k 1423 / 1409
 //   d = 6, K = 10: 40k 363 / 272, 80k 423 / 566; K = 40: 80k 916 / 801      d = 7, K = 10: 40k 597 / 403, 80k 743 / 909
 //   d = 8: 40k, K = 10 608 / 524, K = 40 861 / 722      d = 9, K = 40: 40k 924 / 969      d = 10, K = 40: 20k 546 / 442, 40k 906 / 1125
-// In 16 splits: d = 4 80k 162 / 159 and 247 / 221, d = 5 160k 451 / 441 and 720 / 611.  Clusters, where a tile's queries differ most:
-// 55k points in showers, d = 3, K = 9 437 / 81; 16k, K = 70 581 / 77; 59k in a mixture, d = 6, K = 37 683 / 203.
+// of 16 splits: d = 4, K = 32 50k 155 / 150, 65k 161 / 186; K = 40 65k 207 / 205; K = 100 65k 761 / 498; d = 5, K = 24 100k 486 / 376, 130k 471 / 506;
+//   K = 40 130k 565 / 566, 180k 696 / 817; K = 100 130k 1572 / 1374; of 64: d = 4, K = 24 81k 206 / 163, 120k 193 / 249; d = 5, K = 24 140k 468 / 366, 180k 488 / 496.
+// Clusters, where a tile's queries differ most, gain far beyond: 55k points in showers, d = 3, K = 9 437 / 81; 59k in a mixture, d = 6, K = 37 683 / 203; so
+// above these lines the device decides where it can (asks_votes; from 65,537 points on always).  Of many splits in four and five dimensions it does not
+// see them (mixture, 16 splits: d = 4, K = 10 70k 302 / 135; d = 5, K = 10 180k 1515 / 386, which estimates give to the tile kernel): there the
+// lines lie where uniform points already lose a quarter.
 // Splits of a few points (K < 24): up to five dimensions a grid of one bin, which the tile kernel scans for 64 queries at once, best
 // where the lists fill; beyond, few leaves for a tile of many splits.  A group has two or four queries to share what it costs
 // to start.  Query stage, the other kernels against the group kernel, in us:
@@ -113,18 +122,38 @@ inline bool few_points_a_split(int64_t n, int32_t d, int32_t n_segments, int32_t
     return 100 * n <= splits * k * percent;
 }
 
+inline int64_t group_kernel_line(int64_t n, int32_t d, int32_t n_segments, int32_t k)
+{
+    // by K: below 24, below 36, up to 65 (one list), more (two passes of the tile kernel)
+    static constexpr int32_t kLine[4][6] = {{0, 0, 16384, 20480, 40960, 80000}, {0, 0, 28000, 25000, 37500, 72000},
+                                            {0, 0, 32768, 35000, 40960, 76000}, {0, 0, 32768, 40960, 40960, 84000}};
+    static constexpr int32_t kLeaf[11] = {0, 0, 0, 0, 0, 0, 61440, 61440, 49152, 36864, 28672};
+    if (d >= 6) return kLeaf[d];
+    if (d >= 4 && n <= (int64_t)n_segments * 16384) return d == 4 ? 81920 : 180224;
+    return kLine[k < 24 ? 0 : (k < 36 ? 1 : (k <= 65 ? 2 : 3))][d];
+}
 inline bool takes_group_kernel(int64_t n, int32_t d, int32_t n_segments, int32_t k)
 {
-    static constexpr int32_t kMost[11] = {0, 0, 16384, 20480, 40960, 90112, 61440, 61440, 49152, 36864, 28672};
-    int64_t most = kMost[d];
-    if (d <= 3 && k >= 24) most *= 2;
-    if ((d == 4 || d == 5) && n <= (int64_t)n_segments * 16384) most *= 2;
-    return n <= most && !few_points_a_split(n, d, n_segments, k);
+    return n <= group_kernel_line(n, d, n_segments, k) && !few_points_a_split(n, d, n_segments, k);
 }
 
 // Few points: binned in one launch before the scatter (figures in fg_binning.hip), and the query stage asks for the tiles' votes.
 constexpr int32_t kFewN = 49152;
 inline bool few_points(int64_t n, int32_t d, int32_t n_segments) { return n <= kFewN && n * (d + 8) <= (int64_t)n_segments * 327680; }
+
+// Up to 1024 tiles are not ranked.  Their estimates are made all the same, to vote whether the call is the group kernel's, where clusters are known
+// to gain by it: for few points, and for some way beyond the group kernel's lines.  Two launches, 6 to 9 us of such a call's 60 to 400 on uniform
+// points and 20 on clusters, which then take a third or a sixth of their time (30k points: mixture, d = 3, K = 12 275 / 130 us; showers in 16
+// splits 570 / 86; 41k points, d = 3, K = 32: showers 583 / 171, uniform points 101 / 107, by the group kernel 143 and 153).  Elsewhere up to
+// 65,536 points uniform calls would be 6 to 12 us slower, 8 % (60k, d = 2, K = 16 66 / 72; d = 4, K = 20 170 / 182); clusters would gain as much.
+// In splits of less than kVotesSplit points nothing is dense: a tile's candidates are its splits' points (40k points, d = 3, K = 10 in
+// splits of 20 99 / 107 us a call without and with the votes).
+constexpr int32_t kVotesFrom = 16384, kVotesTo = 65536, kVotesSplit = 64;
+inline bool asks_votes(int64_t n, int32_t d, int32_t n_segments, int32_t k)
+{
+    if (d > 5 || n <= kVotesFrom || n > kVotesTo || n < (int64_t)n_segments * kVotesSplit) return false;
+    return few_points(n, d, n_segments) || (d == 3 && k >= 24 && n <= 40960) || (d == 4 && k >= 24 && n <= 40960);
+}
 
 // Two dimensions and many points: the densest tiles are the leaf kernel's (dense_class_for), and the points of dense cells are
 // ordered for it when they are binned.  (Ordered in three to five dimensions, too, the kernels that search by boxes gained 0 to 5 %

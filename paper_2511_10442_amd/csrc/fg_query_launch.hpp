@@ -62,15 +62,6 @@ __device__ __forceinline__ int32_t tile_class(int32_t work)
 
 constexpr int kTilesPerWave = 16, kTilesPerWaveFew = 8;      // the second up to kFewTiles tiles: one round of the chain of loads instead of two
 constexpr int kFewTiles = 8192;
-// Up to 1024 tiles are not ranked.  Their estimates are made all the same, to vote whether the call is the group kernel's, from kVotesMin
-// tiles on and while the points are few (few_points): two launches, 5 us of such a call's 50 to 80 on uniform points, against a third or a
-// sixth of its time on clusters (30k points: mixture, d = 3, K = 12 275 / 130 us; showers in 16 splits 570 / 86).  From there to 65,536
-// points uniform calls would be 6 to 12 us slower, 8 % (60k, d = 2, K = 16 66 / 72; d = 4, K = 20 170 / 182); clusters would gain as much.
-// In splits of less than kVotesSplit points nothing is dense: a tile's candidates are its splits' points (40k points, d = 3, K = 10 in
-// splits of 20 99 / 107 us a call without and with the votes).
-constexpr int kVotesMin = 256;
-constexpr int kVotesSplit = 64;
-
 // How many tiles, the first of the order, another kernel takes: those of dense_class and above, or, with all_from > 0, all if so many
 // are of it, else none.
 struct TileShare {
@@ -341,7 +332,7 @@ static hipError_t launch_query_pass(QueryArgs& a, hipStream_t stream)
     const int grid = (a.n + kQueryBlock - 1) / kQueryBlock;
     const bool leaf = D == 2 && takes_dense_order(a.n, D);             // the dense tiles the leaf kernel's
     int32_t* const order = a.tile_order;
-    if (!LOWER && D <= kClustersMaxD && !COUNT && a.algo == 0 && a.bin_idx && (grid > 1024 || (grid > kVotesMin && few_points(a.n, D, a.n_segments) && a.n >= (int64_t)a.n_segments * kVotesSplit)))
+    if (!LOWER && D <= kClustersMaxD && !COUNT && a.algo == 0 && a.bin_idx && (grid > 1024 || asks_votes(a.n, D, a.n_segments, a.k)))
         a.dense_class = leaf ? dense_class_for(a.k_list) : clusters_class_for(a.n, D, a.k_list);
     const bool ranked = a.bin_idx && grid > 1024;                      // else a few waves per SIMD: nothing to reorder
     const bool clusters = a.dense_class > 0 && !leaf;                  // all tiles the group kernel's, perhaps

@@ -82,7 +82,7 @@ def test_many_splits(splits):
 
 # the default takes it up to a line in n: the last size on this side, the first on the other, through the entry points that
 # take it, the first against the kernels of the second
-@pytest.mark.parametrize("d,k,splits,line", [(2, 10, 1, 16384), (3, 24, 1, 40960), (4, 10, 4, 40960), (4, 10, 5, 81920), (6, 70, 3, 61440), (10, 12, 1, 28672)])
+@pytest.mark.parametrize("d,k,splits,line", [(2, 10, 1, 16384), (3, 24, 1, 40960), (4, 10, 4, 40960), (4, 10, 5, 81920), (6, 70, 3, 61440), (10, 12, 1, 28672), (2, 32, 1, 28000), (3, 32, 1, 25000), (3, 65, 1, 35000), (4, 30, 2, 37500), (5, 20, 1, 80000), (5, 70, 1, 84000)])
 def test_default_on_both_sides_of_the_line(d, k, splits, line):
     for n in (line, line + 1):
         x, rs = W.uniform(n, d, seed=n, sizes=[n // splits] * (splits - 1) + [n - n // splits * (splits - 1)])
