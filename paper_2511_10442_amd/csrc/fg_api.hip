@@ -289,7 +289,8 @@ static fg_status bin_points_impl(const float* coords, const int32_t* row_splits,
                                   (uint32_t*)(ws + L.keys), (float*)(ws + L.geom), (int32_t*)(ws + L.bin_idx),
                                   (int32_t*)(sc + S.rank), (int32_t*)(ws + L.perm), (float*)(ws + L.rec),
                                   (int32_t*)(ws + L.bounds), (int32_t*)(ws + L.partials), morton_bits,
-                                  morton_bits == 0 ? (int32_t*)(sc + S.tile_order) + 2 * ((n + 63) / 64) : nullptr, ordered ? &order : nullptr,
+                                  morton_bits == 0 ? (int32_t*)(sc + S.tile_order) + 2 * ((n + 63) / 64) : nullptr,
+                                  morton_bits == 0 && counts_crowd(n, d) ? (int32_t*)(sc + S.work_count) + 2 : nullptr, ordered ? &order : nullptr,
                                   (hipStream_t)stream);
     return e == hipSuccess ? FG_OK : FG_ERR_LAUNCH;
 }

@@ -40,8 +40,10 @@ __device__ __forceinline__ float key_to_float(uint32_t k)
 
 __global__ void __launch_bounds__(kBlock)
 k_prepare(int32_t* __restrict__ counters, int64_t n_counters, uint32_t* __restrict__ bbox_keys, int32_t n_keys,
-          int32_t* __restrict__ tile_counters, int32_t* __restrict__ order_counters /* of the lists of dense cells; nullptr: not asked */)
+          int32_t* __restrict__ tile_counters, int32_t* __restrict__ order_counters /* of the lists of dense cells; nullptr: not asked */,
+          int32_t* __restrict__ crowd /* [2], or nullptr */)
 {
+    if (crowd && blockIdx.x == 0 && threadIdx.x < 2) crowd[threadIdx.x] = 0;
     if (tile_counters && blockIdx.x == 0 && threadIdx.x < 2 * kTileClasses) tile_counters[threadIdx.x] = 0;
     if (order_counters && blockIdx.x == 0 && threadIdx.x < 3) order_counters[threadIdx.x] = 0;
     int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -416,8 +418,10 @@ template <int DB>
 __global__ void __launch_bounds__(kFewThreads)
 k_bin_few(const float* __restrict__ coords, const int32_t* __restrict__ row_splits, int32_t n, int32_t d, int32_t n_segments,
           int32_t n_bins, int32_t sub_shift, int32_t cells_per_segment, int32_t morton_bits, float* __restrict__ geom,
-          int32_t* __restrict__ bin_idx, int32_t* __restrict__ rank, int32_t* __restrict__ bounds, int32_t* __restrict__ tile_counters)
+          int32_t* __restrict__ bin_idx, int32_t* __restrict__ rank, int32_t* __restrict__ bounds, int32_t* __restrict__ tile_counters,
+          int32_t* __restrict__ crowd)
 {
+    if (crowd && blockIdx.x == 0 && threadIdx.x < 2) crowd[threadIdx.x] = 0;
     if (tile_counters && blockIdx.x == 0 && threadIdx.x < 2 * kTileClasses) tile_counters[threadIdx.x] = 0;
     extern __shared__ uint32_t cnt[];             // two counters a word
     __shared__ float red[2][kFewThreads / 64][DB];
@@ -498,13 +502,30 @@ k_bin_few(const float* __restrict__ coords, const int32_t* __restrict__ row_spli
 // ROWS_ONLY (the backward's row order): only the permutation; for D = 3 the record area instead receives the
 // rows in their original order padded to four floats, which the backward kernel gathers with one load per
 // neighbour.
+// What takes the choice between leaf and group kernel (counts_crowd): points of every kCrowdSample-th block whose rank in their cell is `from` or
+// more, and whether a tile of 64 sorted points lies across two splits (the first kBlock boundaries).
+constexpr int kCrowdSample = 8;
+struct Crowd { int32_t* count; int32_t from; const int32_t* row_splits; int32_t n_segments; };
+
 template <int D, bool ROWS_ONLY>
 __global__ void __launch_bounds__(kBlock)
 k_scatter(const float* __restrict__ coords, int32_t n, const int32_t* __restrict__ bin_idx,
           const int32_t* __restrict__ rank, const int32_t* __restrict__ bounds,
-          int32_t* __restrict__ perm, float* __restrict__ rec)
+          int32_t* __restrict__ perm, float* __restrict__ rec, Crowd crowd)
 {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if constexpr (D >= 6 && !ROWS_ONLY) {
+        if (crowd.count && blockIdx.x % kCrowdSample == 0) {
+            const int32_t late = __popcll(__ballot(i < n && rank[i] >= crowd.from));
+            const int32_t s = (int32_t)i + 1;              // the first boundaries, by the first block
+            const int32_t cut = s < crowd.n_segments && blockIdx.x == 0 ? crowd.row_splits[s] : 0;
+            const bool across = __any((cut & 63) != 0 && cut < n);
+            if ((threadIdx.x & 63) == 0) {
+                if (late) atomicAdd(&crowd.count[0], late * kCrowdSample);
+                if (late || across) atomicAdd(&crowd.count[1], late * kCrowdSample + (across ? n : 0));
+            }
+        }
+    }
     if (i >= n) return;
     const int32_t pos = bounds[bin_idx[i]] + rank[i];
     const float* p = coords + i * D;
@@ -549,15 +570,15 @@ static hipError_t launch_bbox_assign(bool assign, const float* coords, const int
 
 template <int D>
 static hipError_t launch_scatter(bool rows_only, const float* coords, int32_t n, const int32_t* bin_idx, const int32_t* rank,
-                           const int32_t* bounds, int32_t* perm, float* rec, hipStream_t stream)
+                           const int32_t* bounds, int32_t* perm, float* rec, const Crowd& crowd, hipStream_t stream)
 {
     const unsigned grid = (unsigned)(((int64_t)n + kBlock - 1) / kBlock);
     if (rows_only)
         FG_LAUNCH((k_scatter<D, true>), dim3(grid), dim3(kBlock), 0, stream, coords, n, bin_idx, rank, bounds,
-                  perm, rec);
+                  perm, rec, crowd);
     else
         FG_LAUNCH((k_scatter<D, false>), dim3(grid), dim3(kBlock), 0, stream, coords, n, bin_idx, rank, bounds,
-                  perm, rec);
+                  perm, rec, crowd);
     return hipSuccess;
 }
 
@@ -565,7 +586,8 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
                           int32_t n_segments, int32_t n_bins, int32_t d_bin, int32_t sub_shift, int64_t total_bins,
                           uint32_t* bbox_keys, float* geom, int32_t* bin_idx, int32_t* rank,
                           int32_t* perm, float* rec, int32_t* bounds,
-                          int32_t* scan_partials, int32_t morton_bits, int32_t* tile_counters, const OrderArgs* order, hipStream_t stream)
+                          int32_t* scan_partials, int32_t morton_bits, int32_t* tile_counters, int32_t* crowd_count, const OrderArgs* order,
+                          hipStream_t stream)
 {
     const int64_t n_counters = total_bins + 1;
     const int32_t n_keys = n_segments * d_bin;
@@ -576,7 +598,7 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
     if (cells_per_segment > kFewCellsFree)                                                                                               \
         FG_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_bin_few<DB>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));  \
     FG_LAUNCH(k_bin_few<DB>, dim3(n_segments), dim3(kFewThreads), lds, stream, coords, row_splits, n, d, n_segments, n_bins, sub_shift,   \
-              cells_per_segment, morton_bits, geom, bin_idx, rank, bounds, tile_counters)
+              cells_per_segment, morton_bits, geom, bin_idx, rank, bounds, tile_counters, crowd_count)
         switch (d_bin) {
             case 2: FG_FEW(2); break;
             case 3: FG_FEW(3); break;
@@ -591,7 +613,7 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
         int64_t grid = (work + kBlock - 1) / kBlock;
         if (grid > 4096) grid = 4096;
         FG_LAUNCH(k_prepare, dim3((unsigned)grid), dim3(kBlock), 0, stream, bounds, n_counters, bbox_keys,
-                  n_keys, tile_counters, order ? order->counters : nullptr);
+                  n_keys, tile_counters, order ? order->counters : nullptr, crowd_count);
     }
 #define FG_DB_SWITCH(ASSIGN)                                                                                       \
     switch (d_bin) {                                                                                               \
@@ -625,16 +647,17 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
 #undef FG_APPLY
     }
     }
+    const Crowd crowd{crowd_count, (int32_t)(4 * (((int64_t)n + total_bins - 1) / total_bins) + 8), row_splits, n_segments};
     switch (d) {
-        case 2: FG_TRY(launch_scatter<2>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
-        case 3: FG_TRY(launch_scatter<3>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
-        case 4: FG_TRY(launch_scatter<4>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
-        case 5: FG_TRY(launch_scatter<5>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
-        case 6: FG_TRY(launch_scatter<6>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
-        case 7: FG_TRY(launch_scatter<7>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
-        case 8: FG_TRY(launch_scatter<8>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
-        case 9: FG_TRY(launch_scatter<9>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
-        case 10: FG_TRY(launch_scatter<10>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, stream)); break;
+        case 2: FG_TRY(launch_scatter<2>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, crowd, stream)); break;
+        case 3: FG_TRY(launch_scatter<3>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, crowd, stream)); break;
+        case 4: FG_TRY(launch_scatter<4>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, crowd, stream)); break;
+        case 5: FG_TRY(launch_scatter<5>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, crowd, stream)); break;
+        case 6: FG_TRY(launch_scatter<6>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, crowd, stream)); break;
+        case 7: FG_TRY(launch_scatter<7>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, crowd, stream)); break;
+        case 8: FG_TRY(launch_scatter<8>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, crowd, stream)); break;
+        case 9: FG_TRY(launch_scatter<9>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, crowd, stream)); break;
+        case 10: FG_TRY(launch_scatter<10>(morton_bits > 0, coords, n, bin_idx, rank, bounds, perm, rec, crowd, stream)); break;
         default: return hipErrorInvalidValue;
     }
     return order ? launch_order(*order, stream) : hipSuccess;

@@ -22,7 +22,7 @@ struct QueryArgs {
     float* out_d2;             // [n][k]
     int32_t* out_cand;         // [n] or nullptr
     int32_t* work_list;        // [n] sorted positions of handed-over queries, in bin order; before that the leaf kernel's boxes
-    int32_t* work_count;       // [2] queries on the work list; dense tiles (see dense_class)
+    int32_t* work_count;       // [4] queries on the work list; dense tiles (see dense_class); points of crowded cells, the same and n if a tile lies across splits
     uint64_t* handed;          // [ceil(n/64)] per tile: which of its 64 queries the tile (or leaf) kernel hands over
     const int32_t* bin_idx;    // [n] flat bin of each point, original row order
     int32_t* tile_order;       // [2*ceil(n/64) + 128]: tile order, tile classes, class histogram, class cursors
@@ -41,7 +41,7 @@ struct QueryArgs {
     int32_t dense_class;       // > 0: tiles of this work class and above decide which are not the tile kernel's (the first work_count[1] of the order)
     int32_t few_ask;           // leaf kernel: tiles of which no more queries than this ask (direction flags) are handed over
     const float* coords;       // [n][d] the points in their original order: given (and rec not) where nothing was binned, else nullptr
-    const int32_t* votes;      // few tiles, which are not ranked: as many of them are of dense_class and above; votes_for of them and all are the group kernel's
+    const int32_t* votes;      // few tiles, which are not ranked: as many of them are of dense_class and above (d >= 6: points of crowded cells); votes_for and all are the group kernel's
     int32_t votes_for;
 };
 
@@ -72,6 +72,7 @@ hipError_t launch_binning(const float* coords, const int32_t* row_splits, int32_
                                                  only perm is written, plus for d = 3 a copy of coords in the original
                                                  order padded to float4 in place of the records */,
                           int32_t* tile_counters /* [2 * kTileClasses] of the query stage, cleared; nullptr with morton_bits */,
+                          int32_t* crowd /* [2] for counts_crowd, else nullptr */,
                           const OrderArgs* order /* dense cells' points are put in order, nullptr: not */,
                           hipStream_t stream);
 
@@ -94,8 +95,8 @@ inline bool takes_small_path(int64_t n, int32_t k) { return n <= kSmallN && k <=
 //     K = 64: 26k 106 / 101, 33k 107 / 122; K = 100: 41k 331 / 282
 //   d = 4, K = 10: 30k 117 / 107, 41k 121 / 135; K = 32: 30k 151 / 146, 35k 139 / 165; K = 40: 35k 197 / 176, 41k 183 / 200; K = 100: 41k 620 / 472
 //   d = 5, K = 10: 60k 349 / 313, 80k 386 / 413; K = 32: 50k 457 / 366, 60k 386 / 418; K = 40: 60k 536 / 454, 70k 488 / 511; K = 100: 80k 1423 / 1409
-//   d = 6, K = 10: 40k 363 / 272, 80k 423 / 566; K = 40: 80k 916 / 801      d = 7, K = 10: 40k 597 / 403, 80k 743 / 909
-//   d = 8: 40k, K = 10 608 / 524, K = 40 861 / 722      d = 9, K = 40: 40k 924 / 969      d = 10, K = 40: 20k 546 / 442, 40k 906 / 1125
+//   d = 6, K = 20: 41k 358 / 347; K = 64: 55k 847 / 716      d = 7, K = 20: 41k 523 / 503      d = 8, K = 20: 36k 565 / 559      d = 9, K = 20: 25k 493 / 478
+//   d = 10, K = 20: 16k 412 / 381, 20k 430 / 453
 // of 16 splits: d = 4, K = 32 50k 155 / 150, 65k 161 / 186; K = 40 65k 207 / 205; K = 100 65k 761 / 498; d = 5, K = 24 100k 486 / 376, 130k 471 / 506;
 //   K = 40 130k 565 / 566, 180k 696 / 817; K = 100 130k 1572 / 1374; of 64: d = 4, K = 24 81k 206 / 163, 120k 193 / 249; d = 5, K = 24 140k 468 / 366, 180k 488 / 496.
 // Clusters, where a tile's queries differ most, gain far beyond: 55k points in showers, d = 3, K = 9 437 / 81; 59k in a mixture, d = 6, K = 37 683 / 203; so
@@ -122,13 +123,34 @@ inline bool few_points_a_split(int64_t n, int32_t d, int32_t n_segments, int32_t
     return 100 * n <= splits * k * percent;
 }
 
+// Six dimensions and more: up to the first line the group kernel, beyond the second the leaf kernel, in between the leaf kernel only if
+// the points are spread evenly and no tile lies across two splits, for the leaf kernel's slowest tile sets its end.  A tile of two distant
+// parts takes twice as long, one in a cluster several times.  The scatter of the binning counts the points that find four times the
+// mean and eight before them in their cell, of every eighth block: of 8 clouds from one Gaussian to 5000 clusters 1 to 90 %, of
+// uniform points none.  Query stage, leaf kernel against group kernel, in us, K = 12 and 40:
+//   45k, d = 6: uniform 406 / 379 and 556 / 509, one Gaussian 808 / 486 and 1208 / 666, 50 clusters 718 / 226 and 1638 / 293; K = 20 uniform 55k 452 / 536
+//   61k, d = 6 in 16 splits of whole tiles: uniform 142 / 214 and 232 / 274, clusters 214 / 152 and 426 / 166; of 8 (61,111) uniform 1.2 times
+//   50k, d = 7 in 16: uniform 150 / 202 and 222 / 249, clusters 232 / 140 and 362 / 149      61k, one split: uniform K = 10 678 / 763
+//   49k, d = 8: uniform 768 / 817 and 979 / 1065, clusters 953 / 302 and 1726 / 374; in 16: uniform 142 / 221 and 234 / 271, clusters 235 / 145 and 513 / 159
+//   30k, d = 9: uniform 610 / 580 and 758 / 744; 37k K = 20 0.88 times      29k, d = 10: uniform 587 / 664 and 704 / 830, clusters 821 / 224 and 1420 / 276
+//   55k, d = 6, one split, K = 12: group kernel 0.88 times; K = 20 in 16 splits across tiles: 45k, d = 6 216 / 183 (whole call), 24k, d = 10 176 / 132
+constexpr int32_t kCrowdTo[11] = {0, 0, 0, 0, 0, 0, 61440, 61440, 49152, 36864, 28672};
+constexpr int32_t kCrowdAcross[11] = {0, 0, 0, 0, 0, 0, 52000, 46000, 40000, 34000, 28672};      // K < 36, 16 splits and more: beyond, tiles across splits do not count
+inline int64_t crowd_from(int32_t d, int32_t n_segments, int32_t k)
+{
+    static constexpr int32_t kOne[3][5] = {{56000, 48000, 32000, 32000, 21000}, {44000, 44000, 30000, 26000, 20000}, {61440, 57000, 42000, 33000, 23000}};   // K up to 17, 35, more
+    static constexpr int32_t kMany[2][5] = {{44000, 42000, 30000, 26000, 20000}, {57000, 55000, 42000, 33000, 23000}};
+    if (n_segments == 1) return kOne[k <= 17 ? 0 : (k < 36 ? 1 : 2)][d - 6];
+    return d >= 9 && k >= 36 && n_segments >= 12 ? kCrowdTo[d] : kMany[k < 36 ? 0 : 1][d - 6];
+}
+inline bool counts_crowd(int64_t n, int32_t d) { return d >= 6 && n > 20000 && n <= kCrowdTo[d]; }
+
 inline int64_t group_kernel_line(int64_t n, int32_t d, int32_t n_segments, int32_t k)
 {
     // by K: below 24, below 36, up to 65 (one list), more (two passes of the tile kernel)
     static constexpr int32_t kLine[4][6] = {{0, 0, 16384, 20480, 40960, 80000}, {0, 0, 28000, 25000, 37500, 72000},
                                             {0, 0, 32768, 35000, 40960, 76000}, {0, 0, 32768, 40960, 40960, 84000}};
-    static constexpr int32_t kLeaf[11] = {0, 0, 0, 0, 0, 0, 61440, 61440, 49152, 36864, 28672};
-    if (d >= 6) return kLeaf[d];
+    if (d >= 6) return crowd_from(d, n_segments, k);
     if (d >= 4 && n <= (int64_t)n_segments * 16384) return d == 4 ? 81920 : 180224;
     return kLine[k < 24 ? 0 : (k < 36 ? 1 : (k <= 65 ? 2 : 3))][d];
 }
@@ -153,6 +175,11 @@ inline bool asks_votes(int64_t n, int32_t d, int32_t n_segments, int32_t k)
 {
     if (d > 5 || n <= kVotesFrom || n > kVotesTo || n < (int64_t)n_segments * kVotesSplit) return false;
     return few_points(n, d, n_segments) || (d == 3 && k >= 24 && n <= 40960) || (d == 4 && k >= 24 && n <= 40960);
+}
+
+inline bool asks_crowd(int64_t n, int32_t d, int32_t n_segments, int32_t k)
+{
+    return counts_crowd(n, d) && n > group_kernel_line(n, d, n_segments, k) && !few_points_a_split(n, d, n_segments, k);
 }
 
 // Two dimensions and many points: the densest tiles are the leaf kernel's (dense_class_for), and the points of dense cells are

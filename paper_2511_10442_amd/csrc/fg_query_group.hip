@@ -30,10 +30,11 @@ constexpr int kGroupPend = 128;                 // kept candidates of a query be
 
 template <int D>
 static __global__ void __launch_bounds__(1024)
-k_group_boxes(const float4* __restrict__ rec, int32_t n, GroupTree tree, int32_t* __restrict__ work_count)
+k_group_boxes(QueryArgs a, GroupTree tree)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *work_count = 0;         // nothing is handed over on this path
-    group_boxes<D, 16>(rec, n, tree, blockIdx.x);
+    if (a.votes && *a.votes < a.votes_for) return;                      // the leaf kernel has served the call
+    if (blockIdx.x == 0 && threadIdx.x == 0) *a.work_count = 0;       // nothing is handed over on this path
+    group_boxes<D, 16>(a.rec, a.n, tree, blockIdx.x);
 }
 
 __device__ __forceinline__ int32_t uniform_i32(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -254,7 +255,7 @@ __device__ __forceinline__ void group_queries(const QueryArgs& a, const GroupTre
                 const int32_t i = node64 + lane;
                 node64 += 64;
                 nodes = __ballot(i <= nb);
-                if (nb - na > 1 && !a.votes) {                         // (with votes the nodes have no boxes)
+                if (nb - na > 1 && (D > kClustersMaxD || !a.votes)) {   // (with the tiles' votes the nodes have no boxes)
                     measure(tree.node, min(i, nb));
                     uint64_t hit = 0;
 #pragma unroll
@@ -357,7 +358,7 @@ __device__ __forceinline__ void group_queries(const QueryArgs& a, const GroupTre
     }
 }
 
-// With a.dense_class only if the tiles are this kernel's, all or none; ranked tiles in their order, of which the workgroups take groups in turn,
+// With a.dense_class (d >= 6: votes) only if the tiles are this kernel's, all or none; ranked tiles in their order, of which the workgroups take groups in turn,
 // and those of a tile meet in one XCD's L2 (workgroups are dealt round robin to 8).
 template <int D, int Q, bool LOWER>
 __global__ void __launch_bounds__(kQueryBlock)
@@ -365,7 +366,7 @@ k_query_group(QueryArgs a, GroupTree tree)
 {
     constexpr int kPerTile = kQueryBlock / Q;
     __shared__ uint64_t pend[Q][kGroupPend];
-    const bool asked = D <= kClustersMaxD && a.dense_class > 0, ranked = asked && !a.votes;
+    const bool asked = D <= kClustersMaxD ? a.dense_class > 0 : a.votes != nullptr, ranked = asked && !a.votes;
     const int32_t count = asked ? dense_tiles(a) : 0;
     if (asked && count == 0) return;
     const int32_t rounds = ranked ? (count + 7) >> 3 : 0;
@@ -405,7 +406,7 @@ static hipError_t launch_group(const QueryArgs& a_in, hipStream_t stream)
 {
     QueryArgs a = a_in;
     const GroupTree tree = group_tree<D>(a.work_list, a.n);
-    FG_LAUNCH(k_group_boxes<D>, dim3(tree.n_node), dim3(1024), 0, stream, a.rec, a.n, tree, a.work_count);
+    FG_LAUNCH(k_group_boxes<D>, dim3(tree.n_node), dim3(1024), 0, stream, a, tree);
     const int32_t cap = a.k - 1;
     for (a.slot0 = 0; a.slot0 == 0 || a.slot0 < cap; a.slot0 += 64) {
         a.k_list = cap - a.slot0 < 64 ? cap - a.slot0 : 64;

@@ -409,6 +409,11 @@ static hipError_t launch_query_impl(const QueryArgs& a_in, hipStream_t stream)
     a.k_list = cap < 64 ? cap : 64;
     if constexpr (!COUNT) {
         if (a.algo == 3 || (a.algo == 0 && D >= kLeafMinD)) {
+            const bool either = a.algo == 0 && a.bin_idx && asks_crowd(a.n, D, a.n_segments, a.k);      // decided on the device
+            if (either) {
+                a.votes = a.work_count + (a.n_segments < 16 || a.k >= 36 || a.n <= kCrowdAcross[D] ? 3 : 2);
+                a.votes_for = a.n / 64;
+            }
             FG_TRY((launch_leaf_pass<D, false>(a, stream)));
             if (a.dir) FG_TRY((launch_handed<D, DB, false>(a, stream)));
             if (cap > 64) {
@@ -417,7 +422,7 @@ static hipError_t launch_query_impl(const QueryArgs& a_in, hipStream_t stream)
                 FG_TRY((launch_leaf_pass<D, true>(a, stream)));
                 if (a.dir) FG_TRY((launch_handed<D, DB, false>(a, stream)));
             }
-            return hipSuccess;
+            return either ? launch_query_group(a, stream) : hipSuccess;
         }
     }
     FG_TRY((launch_query_pass<D, DB, COUNT, false>(a, stream)));

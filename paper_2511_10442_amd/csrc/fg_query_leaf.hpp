@@ -66,6 +66,9 @@ __device__ __forceinline__ float leaf_step(float x)
     return fabsf(x - __int_as_float(__builtin_amdgcn_update_dpp(v, v, 0x138, 0xf, 0xf, false)));    // wave_shr:1
 }
 
+// the whole call is the group kernel's
+template <int D> __device__ __forceinline__ bool leaf_not_asked(const QueryArgs& a) { return D > kClustersMaxD && a.votes && dense_tiles(a) > 0; }
+
 template <int D>
 static __global__ void __launch_bounds__(256) k_leaf_boxes(QueryArgs a, float4* __restrict__ boxes)
 {
@@ -73,6 +76,7 @@ static __global__ void __launch_bounds__(256) k_leaf_boxes(QueryArgs a, float4* 
     const int32_t n = a.n;
     if (a.dense_class > 0 && dense_tiles(a) == 0) return;
     if (a.dense_class == 0 && blockIdx.x == 0 && threadIdx.x == 0) *a.work_count = 0;        // nothing is handed over on this path
+    if (leaf_not_asked<D>(a)) return;
     for (int64_t p0 = (int64_t)blockIdx.x * 256; p0 < n; p0 += (int64_t)gridDim.x * 256) {
     const int32_t p = (int32_t)p0 + threadIdx.x;
     float x[D];
@@ -114,7 +118,7 @@ template <int D>
 static __global__ void __launch_bounds__(256) k_node_boxes(QueryArgs a, const float4* __restrict__ below, int32_t n_below, float4* __restrict__ boxes,
                                                            int32_t n_nodes)
 {
-    if (a.dense_class > 0 && dense_tiles(a) == 0) return;
+    if ((a.dense_class > 0 && dense_tiles(a) == 0) || leaf_not_asked<D>(a)) return;
     const int32_t node = blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (node >= n_nodes) return;
@@ -738,6 +742,10 @@ __global__ void __launch_bounds__(kQueryBlock) __attribute__((amdgpu_waves_per_e
 k_query_leaf(QueryArgs a, LeafTree tree)
 {
     extern __shared__ uint64_t lds64[];
+    if (leaf_not_asked<D>(a)) {
+        if (a.dir && threadIdx.x == 0) a.handed[blockIdx.x] = 0;
+        return;
+    }
     const bool dense = D == 2 && a.dense_class > 0;      // only the heaviest tiles, in the order of the ranking kernels
     const int32_t count = dense ? dense_tiles(a) : 0;
     int32_t i = blockIdx.x;

@@ -43,6 +43,27 @@ def test_either_kernel(kind, n, d, k):
     assert np.array_equal(got[0].cpu().numpy()[rows], oi) and np.array_equal(got[1].cpu().numpy()[rows].view(np.uint32), od.view(np.uint32))
 
 
+# six dimensions and more: leaf or group kernel by the crowd that the binning counts and by tiles across splits; both passes of a long list, flags
+@pytest.mark.parametrize("kind", ["uniform", "clusters", "copies"])
+@pytest.mark.parametrize("n,d,k,cuts", [(44_001, 6, 20, []), (61_440, 6, 100, [30_720]), (61_440, 6, 12, [30_721]), (49_152, 8, 40, list(range(3072, 49_152, 3072))), (36_864, 9, 66, [0, 36_864]),
+                                         (28_672, 10, 10, [100, 200]), (43_000, 8, 10, list(range(1000, 43_000, 1000)))])
+def test_leaf_or_group_kernel(kind, n, d, k, cuts):
+    x = cloud(kind, n, d)
+    rs = np.array([0] + cuts + [n], dtype=np.int32)
+    xt, rt = torch.from_numpy(x).to(DEV), torch.from_numpy(rs).to(DEV)
+    bn = B.fg_bin_points(xt, rt, k)
+    flags = torch.from_numpy(np.random.Generator(np.random.PCG64(k)).integers(0, 4, size=n).astype(np.int32)).to(DEV)
+    for direction in (None, flags, torch.where(torch.arange(n, device=DEV) % 37 == 5, 3, 0).int()):
+        ref = B.fg_query_binned(bn, rt, k, direction=direction, algo=3 if kind != "copies" else 5)
+        for _ in range(2):
+            got = B.fg_query_binned(bn, rt, k, direction=direction)
+            assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+    whole = B.fg_binned_select_knn(xt, rt, k)
+    rows = np.linspace(0, n - 1, 12).astype(np.int64)
+    oi, od = oracle.knn_rows(x, rs, k, rows)
+    assert np.array_equal(whole[0].cpu().numpy()[rows], oi) and np.array_equal(whole[1].cpu().numpy()[rows].view(np.uint32), od.view(np.uint32))
+
+
 # clusters, on which the tile kernel alone takes 2 to 6 times as long; uniform points, on which the group kernel takes twice as long
 @pytest.mark.parametrize("kind,n,d,k", [("clusters", 100_000, 4, 20), ("clusters", 100_000, 5, 20), ("uniform", 100_000, 3, 20), ("uniform", 100_000, 2, 20),
                                           ("clusters", 24_000, 3, 12)])
