@@ -24,7 +24,8 @@ hipError_t launch_query(const QueryArgs& a, int32_t d, int32_t d_bin, hipStream_
 {
     if (!a.out_cand) {
         if (a.algo == 0 && takes_small_path(a.n, a.k)) return launch_query_small(a, stream);
-        if (a.algo == 5 || (a.algo == 0 && takes_group_kernel(a.n, d, a.n_segments, a.k))) return launch_query_group(a, stream);
+        if (a.algo == 5 || (a.algo == 0 && takes_group_kernel(a.n, d, a.n_segments, a.k) && !(a.dir && asks_crowd(a.n, d, a.n_segments, a.k, true))))
+            return launch_query_group(a, stream);
     }
     switch (d) {
         case 2: return launch_query_d2(a, d_bin, stream);

@@ -401,6 +401,28 @@ static hipError_t launch_group_pass(const QueryArgs& a, const GroupTree& tree, h
 // two, in us: 10k points, K = 40: d = 3 49 against 40, d = 5 (20k) 142 / 142; 40k, d = 3 111 / 116, d = 5 267 / 268, d = 8 831 / 722.
 constexpr int32_t kGroupPairsN = 16384;
 
+// Direction flags, six dimensions and more: a.votes and, where half of the points ask, as many more as make the call the group kernel's.
+// (One workgroup, some 8 us for 60,000 flags.)
+static __global__ void __launch_bounds__(1024) k_ask_votes(QueryArgs a, const int32_t* __restrict__ votes, int32_t* __restrict__ out)
+{
+    __shared__ int32_t total;
+    if (threadIdx.x == 0) total = 0;
+    __syncthreads();
+    int32_t ask = 0;
+#pragma unroll 4
+    for (int32_t i = threadIdx.x; i < a.n; i += 1024) ask += dir_is_query(a.dir[i]) ? 1 : 0;
+    ask = wave_sum_i32(ask);
+    if ((threadIdx.x & 63) == 0) atomicAdd(&total, ask);
+    __syncthreads();
+    if (threadIdx.x == 0) *out = *votes + (2 * total >= a.n ? a.n : 0);
+}
+
+hipError_t launch_ask_votes(const QueryArgs& a, const int32_t* votes, int32_t* out, hipStream_t stream)
+{
+    FG_LAUNCH(k_ask_votes, dim3(1), dim3(1024), 0, stream, a, votes, out);
+    return hipSuccess;
+}
+
 template <int D>
 static hipError_t launch_group(const QueryArgs& a_in, hipStream_t stream)
 {

@@ -409,10 +409,14 @@ static hipError_t launch_query_impl(const QueryArgs& a_in, hipStream_t stream)
     a.k_list = cap < 64 ? cap : 64;
     if constexpr (!COUNT) {
         if (a.algo == 3 || (a.algo == 0 && D >= kLeafMinD)) {
-            const bool either = a.algo == 0 && a.bin_idx && asks_crowd(a.n, D, a.n_segments, a.k);      // decided on the device
+            const bool either = a.algo == 0 && a.bin_idx && asks_crowd(a.n, D, a.n_segments, a.k, a.dir != nullptr);      // decided on the device
             if (either) {
                 a.votes = a.work_count + (a.n_segments < 16 || a.k >= 36 || a.n <= kCrowdAcross[D] ? 3 : 2);
                 a.votes_for = a.n / 64;
+                if (a.dir && a.n <= group_kernel_line(a.n, D, a.n_segments, a.k)) {
+                    FG_TRY(launch_ask_votes(a, a.votes, a.work_count + 4, stream));
+                    a.votes = a.work_count + 4;
+                }
             }
             FG_TRY((launch_leaf_pass<D, false>(a, stream)));
             if (a.dir) FG_TRY((launch_handed<D, DB, false>(a, stream)));

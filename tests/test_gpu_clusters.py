@@ -45,7 +45,7 @@ def test_either_kernel(kind, n, d, k):
 
 # six dimensions and more: leaf or group kernel by the crowd that the binning counts and by tiles across splits; both passes of a long list, flags
 @pytest.mark.parametrize("kind", ["uniform", "clusters", "copies"])
-@pytest.mark.parametrize("n,d,k,cuts", [(44_001, 6, 20, []), (61_440, 6, 100, [30_720]), (61_440, 6, 12, [30_721]), (49_152, 8, 40, list(range(3072, 49_152, 3072))), (36_864, 9, 66, [0, 36_864]),
+@pytest.mark.parametrize("n,d,k,cuts", [(20_001, 6, 70, [64, 128]), (30_000, 10, 30, [5]), (44_001, 6, 20, []), (61_440, 6, 100, [30_720]), (61_440, 6, 12, [30_721]), (49_152, 8, 40, list(range(3072, 49_152, 3072))), (36_864, 9, 66, [0, 36_864]),
                                          (28_672, 10, 10, [100, 200]), (43_000, 8, 10, list(range(1000, 43_000, 1000)))])
 def test_leaf_or_group_kernel(kind, n, d, k, cuts):
     x = cloud(kind, n, d)

@@ -96,6 +96,19 @@ def test_default_on_both_sides_of_the_line(d, k, splits, line):
         assert np.array_equal(ref[0].cpu().numpy()[rows], oi) and np.array_equal(ref[1].cpu().numpy()[rows].view(np.uint32), od.view(np.uint32))
 
 
+# few, half and nearly all of the points ask, in runs and scattered; lists of one and two passes; tiles and splits that end anywhere
+@pytest.mark.parametrize("d", [2, 5, 6, 7, 10])
+@pytest.mark.parametrize("k", [1, 12, 65, 90])
+@pytest.mark.parametrize("share", [0.0, 0.01, 0.1, 0.5, 0.97, "runs"])
+def test_points_that_ask(d, k, share):
+    sizes = [1300, 5, 0, 63, 64, 65, 1, 900, 127, 2500]
+    n = sum(sizes)
+    x, rs = W.uniform(n, d, seed=900 + d + k, sizes=sizes)
+    rng = np.random.Generator(np.random.PCG64(d * 131 + k))
+    asks = (np.argsort(x[:, 0]) % 300 < 40) if share == "runs" else rng.random(n) < share
+    check(x, rs, k, np.where(asks, rng.choice([1, 3], size=n), rng.choice([0, 2], size=n)).astype(np.int32))
+
+
 # splits of a few points: the kernel for 64 queries serves them up to a grid of one bin (up to five dimensions), of up to 48 points (beyond)
 @pytest.mark.parametrize("n,d,k,per", [(15_000, 2, 16, 14), (15_000, 2, 16, 15), (20_000, 3, 10, 1), (20_000, 3, 10, 2), (20_000, 3, 10, 11), (20_000, 3, 10, 13), (20_000, 3, 10, 14), (10_000, 8, 16, 6), (10_000, 8, 16, 7),
                                         (40_000, 4, 8, 12), (40_000, 4, 8, 13), (40_000, 5, 16, 15), (40_000, 5, 16, 20), (40_000, 5, 16, 40), (40_000, 8, 16, 2),

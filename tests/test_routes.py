@@ -43,3 +43,10 @@ def test_splits_of_a_few_points(n, d, k, splits, expect):
     (28_673, 10, 10, 1, "leaf")])
 def test_lines_in_the_number_of_points(n, d, k, splits, expect):
     assert served(n, d, k, splits) == expect
+
+
+# with direction flags, from six dimensions on, the share that asks decides, too: below the lines as well
+@pytest.mark.parametrize("n,d,k,splits,expect", [(20_000, 6, 20, 1, "group"), (20_001, 6, 20, 1, "group or leaf"), (61_440, 6, 40, 1, "group or leaf"), (61_441, 6, 40, 1, "leaf"),
+                                                  (28_672, 10, 40, 12, "group or leaf"), (30_000, 6, 16, 625, "leaf"), (40_000, 5, 20, 1, "group")])
+def test_direction_flags(n, d, k, splits, expect):
+    assert served(n, d, k, splits, 1) == expect
