@@ -168,12 +168,4 @@ __device__ __forceinline__ uint32_t wave_sort64_words(uint32_t v, int lane)
     return word_exchange<1>(v, u0);
 }
 
-// a bitonic sequence of words becomes ascending
-__device__ __forceinline__ uint32_t wave_merge64_words(uint32_t v, int lane)
-{
-    v = word_exchange<32>(v, lane & 32); v = word_exchange<16>(v, lane & 16); v = word_exchange<8>(v, lane & 8);
-    v = word_exchange<4>(v, lane & 4); v = word_exchange<2>(v, lane & 2);
-    return word_exchange<1>(v, lane & 1);
-}
-
 }  // namespace fg
