@@ -11,7 +11,8 @@
 //                   records written.
 // The lists of cells come from the prefix sum (k_scan_apply).  Without dense cells the two launches find empty lists: some 5 us.
 // What bounds it: the fullest cell, whose first steps one workgroup takes alone (184 us where a split of a million has 5 10^4
-// points in a cell), then the sorts (136 us for 1.3 10^6 points).  5M such points, d = 2, K = 16: fg_bin_points 680 -> 970 us, query
+// points in a cell; a far outlier that puts nearly all points of a split into one cell leaves the ordering to one CU, at some
+// 3.7 ns a point), then the sorts (136 us for 1.3 10^6 points).  5M such points, d = 2, K = 16: fg_bin_points 680 -> 970 us, query
 // 10,750 -> 2700, backward (whose rows follow the order) 1130 -> 613.
 #include "fg_internal.hpp"
 #include "fg_order.hpp"
