@@ -19,8 +19,8 @@ training step bins its points once).  The headline workload is configuration 3: 
   cpu_baseline  the CPU oracle as it stands, timed on this machine's host cores on a bounded sample of the same
                 workload, all cores and one core (a reported baseline, not a target)
   stages        mean milliseconds of binning / query / backward, the kernel that serves the query stage, and the
-                candidate counts and evaluations/s of tile + list kernel (timed by themselves, tile_list_ms, where
-                another kernel is the default: the counts are theirs)
+                candidate counts and evaluations/s of tile + list kernel (asked for by name and timed by themselves,
+                tile_list_ms: the counts are theirs, whichever kernel is the default)
   configs       with --all-configs: the same stage figures for all five configurations
 
 --sweep uniform: the paper's own benchmark shape (Section 4: uniformly distributed random vectors, 1e3 .. 5e6
@@ -81,13 +81,19 @@ def _copy_bandwidth(torch, dev):
     return 2.0 * a.numel() * 4 / (ms * 1e-3) / 1e9
 
 
-def _default_kernel(n, d, k):
-    """What serves the query stage by default (fg_query_options::algo = 0)."""
+def _default_kernel(n, d, k, handed, handed_by_tile):
+    """What served the query stage by default (fg_query_options::algo = 0).  The choice between tile and group kernel is made on the
+    device; it shows in the queries handed to the list kernel (handed): the group kernel hands over none where the tile kernel
+    (handed_by_tile, of algo = 4) does."""
     if n <= 4096 and k <= 65:
         return "all pairs"
     if d >= 6:
-        return "leaf"
-    return "tile + list, dense tiles leaf" if d == 2 and n > 1 << 20 else "tile + list"
+        return "leaf" if n > 61440 else "leaf or group"
+    if d == 2 and n > 1 << 20:
+        return "tile + list, dense tiles leaf"
+    if handed_by_tile == 0:
+        return "tile + list or group"
+    return "tile + list" if handed > 0 else "group"
 
 
 class _Workload:
@@ -122,11 +128,12 @@ class _Workload:
         n, d, k = w.n, w.d, w.k
         ms_bin = _timed(torch, self.bin, reps)
         binning = self.bin()
-        ms_query = ms_tile = _timed(torch, lambda: B.fg_query_binned(binning, self.rs, k, self.out_idx, self.out_d2), reps)
-        kernel = _default_kernel(n, d, k)
-        if kernel != "tile + list":                                   # candidates are counted by these kernels only
-            ms_tile = _timed(torch, lambda: B.fg_query_binned(binning, self.rs, k, self.out_idx, self.out_d2, algo=4), reps)
-        deferred = int(binning.work_count.item())                     # of the timed launches of tile + list kernel
+        ms_query = _timed(torch, lambda: B.fg_query_binned(binning, self.rs, k, self.out_idx, self.out_d2), reps)
+        handed = int(binning.work_count.item())
+        # by themselves: candidates are counted by these kernels only
+        ms_tile = _timed(torch, lambda: B.fg_query_binned(binning, self.rs, k, self.out_idx, self.out_d2, algo=4), reps)
+        deferred = int(binning.work_count.item())
+        kernel = _default_kernel(n, d, k, handed, deferred)
         B.fg_query_binned(binning, self.rs, k, self.out_idx, self.out_d2, self.cand)      # counting instantiation, never timed
         torch.cuda.synchronize()
         total_cand = int(self.cand.to(torch.int64).sum().item())
