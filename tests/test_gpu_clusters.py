@@ -15,15 +15,16 @@ def cloud(kind, n, d):
     rng = np.random.Generator(np.random.PCG64(n + d))
     x = rng.random((n, d))
     if kind == "clusters": x = x[:40][rng.integers(0, 40, size=n)] + 0.01 * rng.standard_normal((n, d))
+    if kind == "hits": x[: n * 9 // 10] = x[:40][rng.integers(0, 40, size=n * 9 // 10)] + 0.01 * rng.standard_normal((n * 9 // 10, d))
     if kind == "spot": x[: n // 50] = 0.3 + 0.004 * x[: n // 50]
     if kind == "copies": x = x[rng.integers(0, n // 300, size=n)]
     return np.ascontiguousarray(x[rng.permutation(n)].astype(np.float32))
 
 
-# sizes that are not ranked, with votes and without, the smallest that is and one above the last full tile; both passes of a long list; the largest size of the group kernel in
-# three dimensions and the first beyond it
+# sizes that are not ranked, with votes (the smallest and the largest of them, too) and without, the smallest that is ranked and one above the last full
+# tile; both passes of a long list; the largest size with a choice in three dimensions and the first beyond it
 @pytest.mark.parametrize("kind", ["uniform", "clusters", "spot", "copies"])
-@pytest.mark.parametrize("n,d,k", [(16_385, 2, 12), (20_500, 3, 10), (41_000, 3, 100), (44_000, 4, 70), (65_536, 4, 20), (65_537, 2, 9), (65_600, 3, 100), (70_001, 4, 65), (81_920, 4, 24), (100_003, 5, 20), (1 << 17, 3, 16), ((1 << 17) + 1, 3, 16)])
+@pytest.mark.parametrize("n,d,k", [(16_385, 2, 12), (20_500, 3, 10), (41_000, 3, 100), (44_000, 3, 70), (49_152, 2, 20), (49_153, 2, 20), (65_537, 2, 9), (65_600, 3, 100), (70_001, 4, 65), (81_920, 4, 24), (100_003, 5, 20), (1 << 17, 3, 16), ((1 << 17) + 1, 3, 16)])
 def test_either_kernel(kind, n, d, k):
     x = cloud(kind, n, d)
     rs = np.array([0, n // 3, n // 3, n // 3 + 7, n], dtype=np.int32)
@@ -62,6 +63,36 @@ def test_leaf_or_group_kernel(kind, n, d, k, cuts):
     rows = np.linspace(0, n - 1, 12).astype(np.int64)
     oi, od = oracle.knn_rows(x, rs, k, rows)
     assert np.array_equal(whole[0].cpu().numpy()[rows], oi) and np.array_equal(whole[1].cpu().numpy()[rows].view(np.uint32), od.view(np.uint32))
+
+
+# Which kernel it was: the group kernel hands no query to the list kernel, the tile kernel does on both clouds (of the scattered points among
+# the clusters).  Votes (below 65,537 points) and ranked tiles; both passes of a long list
+@pytest.mark.parametrize("n,d,k", [(24_000, 3, 12), (70_001, 3, 100), (70_001, 4, 24), (100_003, 5, 20), (100_003, 4, 90)])
+@pytest.mark.parametrize("kind", ["uniform", "hits"])
+def test_the_choice(kind, n, d, k):
+    xt = torch.from_numpy(cloud(kind, n, d)).to(DEV)
+    rt = torch.tensor([0, n], dtype=torch.int32, device=DEV)
+    bn = B.fg_bin_points(xt, rt, k)
+    handed = []
+    for algo in (4, 0, 4, 0):
+        B.fg_query_binned(bn, rt, k, algo=algo)
+        handed.append(int(bn.work_count.item()))
+    assert handed[0] > 0 and handed[2:] == handed[:2]
+    assert (handed[1] == 0) == (kind == "hits"), handed
+
+
+# six dimensions and more: with direction flags the leaf kernel hands over tiles of which few ask, the group kernel none
+@pytest.mark.parametrize("n,d,k", [(44_001, 6, 20), (61_440, 7, 20), (36_000, 8, 70), (28_672, 10, 12)])
+@pytest.mark.parametrize("kind", ["uniform", "clusters"])
+def test_the_choice_with_flags(kind, n, d, k):
+    xt = torch.from_numpy(cloud(kind, n, d)).to(DEV)
+    rt = torch.tensor([0, n], dtype=torch.int32, device=DEV)
+    bn = B.fg_bin_points(xt, rt, k)
+    few = torch.where(torch.arange(n, device=DEV) % 37 == 5, 3, 0).int()
+    B.fg_query_binned(bn, rt, k, direction=few, algo=3)
+    assert int(bn.work_count.item()) > 0
+    B.fg_query_binned(bn, rt, k, direction=few)
+    assert (int(bn.work_count.item()) == 0) == (kind == "clusters")
 
 
 # clusters, on which the tile kernel alone takes 2 to 6 times as long; uniform points, on which the group kernel takes twice as long
