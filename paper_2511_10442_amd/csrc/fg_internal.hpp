@@ -22,7 +22,7 @@ struct QueryArgs {
     float* out_d2;             // [n][k]
     int32_t* out_cand;         // [n] or nullptr
     int32_t* work_list;        // [n] sorted positions of handed-over queries, in bin order; before that the leaf kernel's boxes
-    int32_t* work_count;       // [5] queries on the work list; dense tiles (see dense_class); points of crowded cells, the same and n if a tile lies across splits; either and n if half of the points ask
+    int32_t* work_count;       // [5] queries on the work list; dense tiles (see dense_class); points of crowded cells, the same and n if a tile lies across splits; either and n if half of the points ask or few are neighbours
     uint64_t* handed;          // [ceil(n/64)] per tile: which of its 64 queries the tile (or leaf) kernel hands over
     const int32_t* bin_idx;    // [n] flat bin of each point, original row order
     int32_t* tile_order;       // [2*ceil(n/64) + 128]: tile order, tile classes, class histogram, class cursors
@@ -177,7 +177,7 @@ inline bool asks_votes(int64_t n, int32_t d, int32_t n_segments, int32_t k)
     return few_points(n, d, n_segments) || (d == 3 && k >= 24 && n <= 40960) || (d == 4 && k >= 24 && n <= 40960);
 }
 
-// With direction flags below the lines, too, if fewer than half of the points ask (counted by a kernel of one workgroup): the leaf kernel hands tiles of few
+// With direction flags below the lines, too, if fewer than half of the points ask (counted by a kernel of one workgroup; with few neighbours, too, the group kernel): the leaf kernel hands tiles of few
 // queries to the list kernel.  Whole call, leaf and list against group kernel, uniform points, K = 24: 40k, d = 6, one in ten 153 / 240 us, three in
 // ten 213 / 344, eight in ten 508 / 470; 30k, one in a hundred 135 / 155; 10k, one in ten 130 / 100; a mixture, 40k, one in ten 195 / 157.
 inline bool asks_crowd(int64_t n, int32_t d, int32_t n_segments, int32_t k, bool dir)
@@ -201,7 +201,7 @@ hipError_t launch_query_clusters(const QueryArgs& a, hipStream_t stream);
 // every pair compared: takes_small_path
 hipError_t launch_query_small(const QueryArgs& a, hipStream_t stream);
 
-// votes, and n more where half of the points ask (a.dir)
+// votes, and n more where half of the points ask or few are neighbours (a.dir)
 hipError_t launch_ask_votes(const QueryArgs& a, const int32_t* votes, int32_t* out, hipStream_t stream);
 
 // the group kernel, whatever the size (with a.votes, if they say so)

@@ -402,20 +402,33 @@ static hipError_t launch_group_pass(const QueryArgs& a, const GroupTree& tree, h
 // two, in us: 10k points, K = 40: d = 3 49 against 40, d = 5 (20k) 142 / 142; 40k, d = 3 111 / 116, d = 5 267 / 268, d = 8 831 / 722.
 constexpr int32_t kGroupPairsN = 16384;
 
-// Direction flags, six dimensions and more: a.votes and, where half of the points ask, as many more as make the call the group kernel's.
-// (One workgroup, some 8 us for 60,000 flags.)
+// Direction flags, six dimensions and more: a.votes and, where half of the points ask or few are anyone's neighbours, as many more as make
+// the call the group kernel's.  (One workgroup, some 5 us for 60,000 flags.)  Few neighbours lie far apart, and the leaf kernel hands
+// its queries to the list kernel, which goes through the empty bins between them.  Whole call, leaf and list against group kernel, uniform points of which
+// the same share asks and is neighbour, in us: d = 6, K = 24, 22k, 1 % 995 / 304, 10 % 476 / 270, 40k, 1 % 947 / 508, 10 % 313 / 426; d = 8, K = 40, 40k, 1 %
+// 617 / 471, 10 % 521 / 700.
+constexpr int32_t kFewNeighbours = 2500;
+
 static __global__ void __launch_bounds__(1024) k_ask_votes(QueryArgs a, const int32_t* __restrict__ votes, int32_t* __restrict__ out)
 {
-    __shared__ int32_t total;
-    if (threadIdx.x == 0) total = 0;
+    __shared__ int32_t total[2];
+    if (threadIdx.x < 2) total[threadIdx.x] = 0;
     __syncthreads();
-    int32_t ask = 0;
+    int32_t ask = 0, answer = 0;
 #pragma unroll 4
-    for (int32_t i = threadIdx.x; i < a.n; i += 1024) ask += dir_is_query(a.dir[i]) ? 1 : 0;
+    for (int32_t i = threadIdx.x; i < a.n; i += 1024) {
+        const int32_t flag = a.dir[i];
+        ask += dir_is_query(flag) ? 1 : 0;
+        answer += dir_is_neighbour(flag) ? 1 : 0;
+    }
     ask = wave_sum_i32(ask);
-    if ((threadIdx.x & 63) == 0) atomicAdd(&total, ask);
+    answer = wave_sum_i32(answer);
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&total[0], ask);
+        atomicAdd(&total[1], answer);
+    }
     __syncthreads();
-    if (threadIdx.x == 0) *out = *votes + (2 * total >= a.n ? a.n : 0);
+    if (threadIdx.x == 0) *out = *votes + (2 * total[0] >= a.n || total[1] < kFewNeighbours ? a.n : 0);
 }
 
 hipError_t launch_ask_votes(const QueryArgs& a, const int32_t* votes, int32_t* out, hipStream_t stream)

@@ -95,6 +95,20 @@ def test_the_choice_with_flags(kind, n, d, k):
     assert (int(bn.work_count.item()) == 0) == (kind == "clusters")
 
 
+# below the lines the flags decide: half of the points ask, or few are neighbours, and the call is the group kernel's
+@pytest.mark.parametrize("n,d,k", [(20_001, 6, 20), (40_000, 6, 70), (30_000, 8, 20)])
+@pytest.mark.parametrize("few,rest,group", [(3, 0, False), (1, 2, True), (3, 2, True), (0, 3, True)])
+def test_the_choice_by_flags(n, d, k, few, rest, group):
+    xt = torch.from_numpy(cloud("uniform", n, d)).to(DEV)
+    rt = torch.tensor([0, n], dtype=torch.int32, device=DEV)
+    bn = B.fg_bin_points(xt, rt, k)
+    flags = torch.where(torch.arange(n, device=DEV) % 37 == 5, few, rest).int()
+    ref = B.fg_query_binned(bn, rt, k, direction=flags, algo=3)
+    got = B.fg_query_binned(bn, rt, k, direction=flags)
+    assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+    assert (int(bn.work_count.item()) == 0) == group
+
+
 # clusters, on which the tile kernel alone takes 2 to 6 times as long; uniform points, on which the group kernel takes twice as long
 @pytest.mark.parametrize("kind,n,d,k", [("clusters", 100_000, 4, 20), ("clusters", 100_000, 5, 20), ("uniform", 100_000, 3, 20), ("uniform", 100_000, 2, 20),
                                           ("clusters", 24_000, 3, 12)])
