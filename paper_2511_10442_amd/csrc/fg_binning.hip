@@ -70,7 +70,8 @@ __device__ __forceinline__ float wave_max(float v)
 // one pair per wavefront, split and dimension, or per lane.  Same-address atomics serialise, so their number matters.
 // Few points per thread: the launch needs well over 256 blocks to keep loads in flight; but every block of a row split adds to the
 // queue at its keys (some 20 ns each: 5M points of one split, 4883 blocks, 98 us), so no more than some kBboxBlocks a split
-// (fg_bin_points of 5M uniform points, d = 3, 459 -> 380 us, of 1M, d = 5, 111 -> 98.5).
+// (fg_bin_points of 5M uniform points, d = 3, 459 -> 380 us, of 1M, d = 5, 111 -> 98.5; for 128 / 192 / 384 / 768 blocks, d = 3,
+// calls of a Python program back to back: 1M 108.3 / 107.9 / 109.3 / 111.9, 5M 432 / 433 / 436 / 439, 5M in five splits 461 / 446 / 426 / 420).
 constexpr int kBboxItems = 4, kBboxMostItems = 64;
 constexpr int kBboxBlocks = 384;
 constexpr int kBboxSplits = 24;   // more row splits than this in a wavefront's 64 points: atomics per lane

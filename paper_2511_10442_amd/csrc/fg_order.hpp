@@ -5,7 +5,9 @@
 
 namespace fg {
 
-constexpr int kOrderMin = 96;            // cells of more points than this are ordered
+// Cells of more points than this are ordered.  Points of strongly varying density, binning + query + backward for 48 / 96 / 192, in us: 1.1M in one split,
+// K = 16 1244 / 1237 / 1220; 2M in four, K = 8 1535 / 1471 / 1476, K = 16 1685 / 1625 / 1616; 5M in five, K = 8 3658 / 3560 / 3506, K = 16 3986 / 3922 / 3901.
+constexpr int kOrderMin = 96;
 constexpr int kOrderWindowShift = 10;
 constexpr int kOrderChunk = 2 << kOrderWindowShift;      // points sorted in LDS at a time
 

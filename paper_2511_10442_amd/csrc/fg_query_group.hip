@@ -11,9 +11,9 @@
 //     sort of a word per lane) has cap candidates at or below it.  Lists that fill from empty kept twice as many.
 //   * Then the leaves that still reach: those eight, the ones within half the bound's distance, the rest.  Kept candidates
 //     wait in LDS until 64 are there (or the sweep ends) and are sorted and merged across the lanes (fg_wavesort.hpp).
-// What bounds it: vector issue, 50 to 75 % of the SIMD's slots, from 20,000 points on some 1200 instructions a query at d = 3,
-// K = 32 (100k uniform points): a third the sorts (230 each), a third distances (14 for 64 candidates), the rest box tests
-// and bounds; below, the chain of one group.  A bound from a first pass over the near leaves as well (nothing kept until
+// What bounds it: vector issue, 69 % of the SIMDs' slots at 20,000 uniform points, d = 3, K = 32, and 94 % at 100,000 (1130 and 1330
+// instructions a query by the counters; as the code has it a third the sorts of 230 each, a third distances, 14 for 64 candidates,
+// the rest box tests and bounds); below, the chain of one group.  A bound from a first pass over the near leaves as well (nothing kept until
 // then, then one sort a query) cost more distances than it saved sorts: +10 to +80 %.  Figures beside the rule,
 // takes_group_kernel.
 #include "fg_query_tile.hpp"
@@ -22,7 +22,9 @@
 
 namespace fg {
 
-constexpr int kGroupStart = 8;                  // leaves that a first bound comes from
+// Leaves that a first bound comes from.  Query stage for 4 / 8 / 16, in us: uniform points, d = 3, 20k, K = 32 108 / 69 / 69, 100k 277 / 257 / 315; d = 4, 40k, K = 40
+// 206 / 184 / 192; d = 6, 40k, K = 20 366 / 358 / 359; 100k points in showers, K = 32 341 / 228 / 265, in a mixture, d = 4, K = 40 475 / 381 / 402.
+constexpr int kGroupStart = 8;
 // Most workgroups where there may be nothing to do: an empty launch of 8192, 16384 and 25,000 takes 3, 5 and 7 us, and clusters of 100k
 // points, d = 4, K = 40 455, 395 and 385 (each takes further groups, whose number differs by one).
 constexpr int32_t kRankedGrid = 16384;

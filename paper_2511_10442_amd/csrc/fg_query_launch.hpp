@@ -272,6 +272,9 @@ static void allow_lds(K kernel, size_t bytes)
 // of four) lie in bins that hold far more than their share, and go to the leaf kernel, whose boxes prune there because the points of
 // such bins are put in order when they are binned.  Bins are made for K points, so the class rises with K (two classes are a
 // factor of two).  Whole training step of 5M points of strongly varying density, K = 16, tile kernel alone against both 18 -> 4.1 ms.
+// Query stage of such points for class 14 / 16 / 18 / 20 / 22, in us: 1.1M points in one split, K = 8 909 / 889 / 577 / 579 / 585, K = 16 1257 / 1246 /
+// 682 / 697 / 709, K = 32 1255 / 1020 / 945 / 967 / 1015; 2M in four, K = 16 1271 / 994 / 995 / 1042 / 1056; 5M in five, K = 8 2477 / 2309 / 2087 / 2105 /
+// 2146, K = 16 2674 / 2427 / 2415 / 2462 / 2517.
 // Where no tile qualifies the four launches cost some 10 us from 1M points on (6 at 200k): of a whole call on uniform
 // points 3 % at 1M and 1 % at 4M, so the line lies at 2^20 (kDenseMinN).
 constexpr int32_t kDenseClass = 18;
