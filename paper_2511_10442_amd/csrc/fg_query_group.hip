@@ -45,7 +45,7 @@ __device__ __forceinline__ int32_t uniform_i32(int32_t v) { return __builtin_amd
 // a wave-uniform value kept in a vector register: the scalar ones are what this kernel is short of
 __device__ __forceinline__ float in_vector(float v) { asm("" : "+v"(v)); return v; }
 
-template <int D, int Q, bool LOWER>
+template <int D, int Q, bool LOWER, bool CHOICE>
 __device__ __forceinline__ void group_queries(const QueryArgs& a, const GroupTree& tree, const int32_t p0, uint64_t (*pend)[kGroupPend])
 {
     constexpr int NV = rec_vecs(D);
@@ -258,7 +258,7 @@ __device__ __forceinline__ void group_queries(const QueryArgs& a, const GroupTre
                 const int32_t i = node64 + lane;
                 node64 += 64;
                 nodes = __ballot(i <= nb);
-                if (nb - na > 1 && (D > kClustersMaxD || !a.votes)) {   // (with the tiles' votes the nodes have no boxes)
+                if (nb - na > 1 && ((CHOICE && D > kClustersMaxD) || !a.votes)) {   // (with the tiles' votes the nodes have no boxes)
                     measure(tree.node, min(i, nb));
                     uint64_t hit = 0;
 #pragma unroll
@@ -363,13 +363,15 @@ __device__ __forceinline__ void group_queries(const QueryArgs& a, const GroupTre
 
 // With a.dense_class (d >= 6: votes) only if the tiles are this kernel's, all or none; ranked tiles in their order, of which the workgroups take groups in turn,
 // and those of a tile meet in one XCD's L2 (workgroups are dealt round robin to 8).
-template <int D, int Q, bool LOWER>
+// CHOICE: the device decides whether it does anything (from six dimensions on an instantiation of its own, as its tests move the loops of every call:
+// 24k points in a mixture, d = 6, K = 50 309 -> 313 us).
+template <int D, int Q, bool LOWER, bool CHOICE>
 __global__ void __launch_bounds__(kQueryBlock)
 k_query_group(QueryArgs a, GroupTree tree)
 {
     constexpr int kPerTile = kQueryBlock / Q;
     __shared__ uint64_t pend[Q][kGroupPend];
-    const bool asked = D <= kClustersMaxD ? a.dense_class > 0 : a.votes != nullptr, ranked = asked && !a.votes;
+    const bool asked = CHOICE && (D > kClustersMaxD || a.dense_class > 0), ranked = asked && !a.votes;
     const int32_t count = asked ? dense_tiles(a) : 0;
     if (asked && count == 0) return;
     const int32_t rounds = ranked ? (count + 7) >> 3 : 0;
@@ -382,7 +384,7 @@ k_query_group(QueryArgs a, GroupTree tree)
             const int32_t j = i >> 3, at = (j / kPerTile) * 8 + (i & 7);
             p0 = at < count ? (a.tile_order[at] & ((1 << kOrderFlagBit) - 1)) * kQueryBlock + (j % kPerTile) * Q : a.n;
         }
-        if (p0 < a.n) group_queries<D, Q, LOWER>(a, tree, p0, pend);
+        if (p0 < a.n) group_queries<D, Q, LOWER, CHOICE>(a, tree, p0, pend);
         if (!ranked) break;
         __syncthreads();
     }
@@ -394,8 +396,14 @@ static hipError_t launch_group_pass(const QueryArgs& a, const GroupTree& tree, h
     int32_t blocks = (a.n + Q - 1) / Q;
     if (a.dense_class > 0 && blocks > kRankedGrid) blocks = kRankedGrid;       // its workgroups take further groups
     const dim3 grid(blocks);
-    if (a.slot0 == 0) FG_LAUNCH((k_query_group<D, Q, false>), grid, dim3(kQueryBlock), 0, stream, a, tree);
-    else FG_LAUNCH((k_query_group<D, Q, true>), grid, dim3(kQueryBlock), 0, stream, a, tree);
+    constexpr bool either = D <= kClustersMaxD;      // one instantiation for both
+    if (either || a.votes) {
+        if (a.slot0 == 0) FG_LAUNCH((k_query_group<D, Q, false, true>), grid, dim3(kQueryBlock), 0, stream, a, tree);
+        else FG_LAUNCH((k_query_group<D, Q, true, true>), grid, dim3(kQueryBlock), 0, stream, a, tree);
+    } else {
+        if (a.slot0 == 0) FG_LAUNCH((k_query_group<D, Q, false, either>), grid, dim3(kQueryBlock), 0, stream, a, tree);
+        else FG_LAUNCH((k_query_group<D, Q, true, either>), grid, dim3(kQueryBlock), 0, stream, a, tree);
+    }
     return hipSuccess;
 }
 
